@@ -104,7 +104,11 @@ typedef struct {
                                 driven on the device, several per host
                                 round trip (full sweep, no filtering); 3
                                 the same, replayed from a captured HIP
-                                graph                                        */
+                                graph; 4 rounds over a contracted edge list,
+                                light edges first: rounds, hooks and
+                                active_nnz (two per live edge) list the
+                                rounds on the light edges, then those on the
+                                edges left between their trees              */
     int64_t runs;            /* key-sorted runs of the adjacency (0: none)   */
     /* Device time (events) and algorithmic bytes of one-launch passes, 0
        when not run.  Index 0: placement of the two-level build (per stored
@@ -136,7 +140,9 @@ typedef struct {
     /* msf_solve with the two-level build: the adjacency build alone (device
        events from the solve's start to the end of the placement; build_ms
        also holds the head sweep's run set-up and the host step between
-       them); 0 with the other builds. */
+       them).  On path 4 there is no adjacency matrix: the selection of the
+       light edges' list, and build_ms also holds the first round's edge
+       pass.  0 with the other builds. */
     double adjacency_ms;
 } msf_stats;
 

@@ -71,7 +71,8 @@ msf_status ws_get(Ctx *c, Slot s, size_t bytes, void **out)
 
 msf_status read_counters(Ctx *c)
 {
-    MSF_HIP(hipMemcpyAsync(c->hcnt, c->dcnt, sizeof(Counters), hipMemcpyDeviceToHost, c->stream));
+    MSF_HIP(hipMemcpyAsync(c->hcnt, c->dcnt, offsetof(Counters, ct), hipMemcpyDeviceToHost,
+                           c->stream));
     MSF_HIP(hipStreamSynchronize(c->stream));
     return MSF_OK;
 }
@@ -168,6 +169,7 @@ msf_status ctx_init(Ctx *c, int device, hipStream_t stream, bool async_alloc)
     if (const char *f = getenv("MSF_GRAPH_ROUNDS")) c->graph_rounds = atoi(f);
     if (const char *f = getenv("MSF_GRAPH_ROUNDS_MAX_N")) c->graph_rounds_max_n = atoll(f);
     if (const char *f = getenv("MSF_TL_ROW_IN_COL")) c->tl_row_in_col = atoi(f);
+    if (const char *f = getenv("MSF_CONTRACT")) c->contract = atoi(f);
     if (const char *f = getenv("MSF_TEST_FAIL_ALLOC_AFTER")) c->fail_alloc_after = atoll(f);
     return MSF_OK;
 }

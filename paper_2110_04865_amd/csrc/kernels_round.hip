@@ -617,8 +617,10 @@ __device__ __forceinline__ uint32_t count_flags(const uint32_t (&fw)[OUT_IT / 4]
 // Pass 1 (tile = workgroup): the tile's forest-edge count.
 __global__ __launch_bounds__(OUT_NT) void k_output_count(const uint8_t *__restrict__ flags,
                                                         int64_t m,
-                                                        uint32_t *__restrict__ tile_cnt)
+                                                        uint32_t *__restrict__ tile_cnt,
+                                                        const uint32_t *go)
 {
+    if (go && !*go) return;
     __shared__ uint64_t s_lds[OUT_NT / 64 + 1];
     const uint32_t tile = blockIdx.x;
     const int64_t base = (int64_t)tile * OUT_TILE + (int64_t)threadIdx.x * OUT_IT;
@@ -632,8 +634,10 @@ __global__ __launch_bounds__(OUT_NT) void k_output_count(const uint8_t *__restri
 __global__ __launch_bounds__(OUT_NT) void k_output_ids(const uint8_t *__restrict__ flags,
                                                       int64_t m,
                                                       const uint32_t *__restrict__ tile_off,
-                                                      int32_t *__restrict__ ids)
+                                                      int32_t *__restrict__ ids,
+                                                      const uint32_t *go)
 {
+    if (go && !*go) return;
     __shared__ uint32_t s_lds[OUT_NT / 64 + 1];
     const uint32_t tile = blockIdx.x;
     const int64_t base = (int64_t)tile * OUT_TILE + (int64_t)threadIdx.x * OUT_IT;
@@ -672,7 +676,7 @@ size_t output_part_bytes(int64_t m)
 }
 
 msf_status launch_output(Ctx *c, const uint8_t *in_forest, int64_t m, const void *w,
-                         msf_wtype wt, int32_t *ids, void *part)
+                         msf_wtype wt, int32_t *ids, void *part, const uint32_t *go)
 {
     const int64_t ntiles = output_tiles(m);
     if (ntiles == 0) return MSF_OK;
@@ -681,10 +685,10 @@ msf_status launch_output(Ctx *c, const uint8_t *in_forest, int64_t m, const void
     // per-tile counts, then their exclusive scan
     uint32_t *tcnt = reinterpret_cast<uint32_t *>(part);
     uint32_t *toff = tcnt + ntiles;
-    k_output_count<<<(unsigned)ntiles, OUT_NT, 0, s>>>(in_forest, m, tcnt);
+    k_output_count<<<(unsigned)ntiles, OUT_NT, 0, s>>>(in_forest, m, tcnt, go);
     MSF_TRY(scan_u32(c, tcnt, toff, ntiles, &c->dcnt->count));
-    k_output_ids<<<(unsigned)ntiles, OUT_NT, 0, s>>>(in_forest, m, toff, ids);
-    k_total<<<1, 64, 0, s>>>(c->dcnt, (int)wt);
+    k_output_ids<<<(unsigned)ntiles, OUT_NT, 0, s>>>(in_forest, m, toff, ids, go);
+    if (!go) k_total<<<1, 64, 0, s>>>(c->dcnt, (int)wt);
     MSF_HIP(hipGetLastError());
     return MSF_OK;
 }

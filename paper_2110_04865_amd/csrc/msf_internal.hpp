@@ -25,6 +25,9 @@ namespace msf {
 
 constexpr uint64_t KEY_INF = ~0ull;
 constexpr int MAX_SLICES = 8;
+// rounds a contracted edge list can take, with room: every round at least
+// halves its vertices (n < 2^31)
+constexpr int CT_ROUNDS = 40;
 constexpr uint32_t NONE32 = 0xFFFFFFFFu;
 
 // Sweep geometry: a workgroup of SWEEP_BLOCK lanes handles SWEEP_E
@@ -141,6 +144,23 @@ struct Counters {
     uint32_t gpad;
     uint32_t ghist[64];
     uint64_t long_entries;  // stored entries in rows of at least WAVE_ROW entries
+    // rounds over a contracted edge list (kernels_contract.hip), per phase
+    struct {
+        uint32_t L[2][CT_ROUNDS];      // vertices at the start of a round
+        uint32_t E[2][CT_ROUNDS];      // live edges of a round
+        uint32_t hooks[2][CT_ROUNDS];  // kept hooks
+        uint32_t ran[2][CT_ROUNDS];    // the edge pass ran
+        uint32_t done[2][CT_ROUNDS];   // the round is complete
+        uint32_t tick[2][CT_ROUNDS];   // workgroups through the edge pass
+        uint32_t dead[2];              // finished trees
+        uint32_t tl[2];                // 1 + first round finished by one workgroup
+        uint32_t phdone[2];            // the phase is complete
+        uint32_t wl;                   // weight keys listed by those rounds
+        uint32_t giant;                // the tree most sampled edges lie in
+        uint32_t fin;                  // every phase complete, total known
+        uint32_t pad;
+        uint64_t T;                    // phase 0 takes keys up to this one
+    } ct;
 };
 
 // Key-sorted runs for the head sweep: every 64-entry chunk of the
@@ -203,7 +223,8 @@ void set_chunks(Adj *a);
 
 struct SolveState {
     int phase = 0;  // 0 idle, 1 build, 2 roots, 3 round, 4 output, 5 done,
-                    // 6 device-driven rounds, 7 build and runs (head sweep)
+                    // 6 device-driven rounds, 7 build and runs (head sweep),
+                    // 8 rounds over a contracted edge list
     int32_t n = 0;
     int64_t m = 0;
     const int32_t *edges = nullptr;
@@ -225,6 +246,9 @@ struct SolveState {
     const uint32_t *perm = nullptr;
     Runs runs;
     uint32_t nruns = 0;
+    bool two_phase = false;   // contracted edge list: light edges first
+    size_t ct_words = 0;      // its buffers: words of the flags
+    uint32_t ct_W = 0;        // its list segments
     int ri = 0, ai = 0, rounds = 0;
     int sweep_events = 0;     // rounds whose sweep start/end events were recorded
     double live_frac = 1.0;
@@ -287,6 +311,11 @@ struct Ctx {
     // the high bits of its column word when column bits + L2 <= 32 (1), or
     // in a separate 2-byte array (0)
     int tl_row_in_col = 1;
+    // rounds over a contracted edge list, light edges first, instead of an
+    // adjacency matrix: 0 never, 1 for graphs too large for one workgroup
+    // while the settings above have their defaults (small_m above 0), 2
+    // always
+    int contract = 1;
     // failure-path test hook (MSF_TEST_FAIL_ALLOC_AFTER): after this many
     // workspace allocations the next one is refused once, without calling
     // the allocator (-1: never)
@@ -454,8 +483,10 @@ msf_status build_runs(Ctx *c, const Runs &R, const uint32_t *row_ptr, int32_t n,
                       const uint32_t *col, const uint64_t *key, uint32_t nnz_max, int eb);
 void launch_heads(hipStream_t s, const Runs &R, uint32_t nruns, const uint32_t *col,
                   const uint64_t *key, const uint32_t *p, uint64_t *r, Counters *dcnt, int parity);
+// go (nullable, device): nothing is written while it is 0, and the total has
+// been rounded already.
 msf_status launch_output(Ctx *c, const uint8_t *in_forest, int64_t m, const void *w,
-                         msf_wtype wt, int32_t *ids, void *part);
+                         msf_wtype wt, int32_t *ids, void *part, const uint32_t *go = nullptr);
 
 // Shortcut of an arbitrary parent vector (msf_shortcut).
 void launch_check_parents(hipStream_t s, const uint32_t *p, int32_t n, Counters *dcnt);

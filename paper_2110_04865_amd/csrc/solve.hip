@@ -18,7 +18,9 @@
 #include <algorithm>
 #include <cmath>
 
+#include "contract.hpp"
 #include "msf_internal.hpp"
+#include "persist.hpp"
 
 namespace msf {
 
@@ -143,7 +145,9 @@ constexpr int64_t HEADS_MIN_DEG = 16;
 static msf_status end_step(Ctx *c, int next_phase)
 {
     MSF_HIP(hipGetLastError());
-    MSF_HIP(hipMemcpyAsync(c->hcnt, c->dcnt, sizeof(Counters), hipMemcpyDeviceToHost, c->stream));
+    // the contracted rounds' counters only for their own phase
+    const size_t bytes = next_phase == 8 ? sizeof(Counters) : offsetof(Counters, ct);
+    MSF_HIP(hipMemcpyAsync(c->hcnt, c->dcnt, bytes, hipMemcpyDeviceToHost, c->stream));
     MSF_HIP(hipEventRecord(c->ev[3], c->stream));
     c->ss.phase = next_phase;
     return MSF_OK;
@@ -151,6 +155,172 @@ static msf_status end_step(Ctx *c, int next_phase)
 
 static msf_status enqueue_round_state(Ctx *c);
 static int edge_bits(int64_t m);
+
+// ------------------------------------- rounds over a contracted edge list --
+
+static bool contract_eligible(const Ctx *c, int32_t n, int64_t m)
+{
+    if (n < 2 || m < 1 || c->contract == 0) return false;
+    if (c->contract == 2) return true;
+    const bool defaults = c->heads == 1 && c->filter_mode == 1 && !c->check_rounds &&
+                          c->first_round == 2 && c->bucketed_build == 1 && c->slices == 0 &&
+                          c->graph_rounds == 2;
+    return defaults && c->small_m > 0 && !small_eligible(c, n, m);
+}
+
+// Edges of phase 0: n ln(4 m / n) / 2 of the lightest.  With f n random
+// edges a fraction of about 2 exp(-2 f) of the rest still joins different
+// trees (Erdos-Renyi), so this balances the edges of the two phases; on
+// R-MAT and grids the two are within a factor of two of each other there.
+static int64_t contract_light(int32_t n, int64_t m)
+{
+    const double f = 0.5 * std::log(std::max(1.0, 4.0 * (double)m / (double)n));
+    return std::max<int64_t>(1, (int64_t)(f * (double)n));
+}
+
+static msf_status contract_args(Ctx *c, CtArgs *A)
+{
+    const SolveState &S = c->ss;
+    const size_t nn = (size_t)S.n;
+    const size_t cap = (size_t)S.ct_W * ct_segcap(S.m, S.ct_W);
+    void *v[12];
+    const struct {
+        Slot s;
+        size_t bytes;
+    } req[12] = {
+        {WS_KEY, sizeof(CtEdge) * cap},  {WS_WLIVE, 4 * (size_t)S.ct_W},
+        {WS_R, 8 * nn},                  {WS_HEDGE, 8 * (nn / 2 + 64)},
+        {WS_H, 4 * nn},                  {WS_RL, 4 * nn},
+        {WS_RL2, 4 * ct_maps_words(S.n)}, {WS_HWK, 4 * 3 * CT_SMALL},
+        {WS_FLAGS, 4 * S.ct_words},      {WS_PART, ct_wpart_bytes() + output_part_bytes(S.m)},
+        {WS_P, 4 * nn},                  {WS_STATUS, 8 * ((nn + 63) / 64)},
+    };
+    for (int i = 0; i < 12; ++i) MSF_TRY(ws_get(c, req[i].s, req[i].bytes, &v[i]));
+    A->n = S.n;
+    A->m = S.m;
+    A->wt = S.wt;
+    A->edges = reinterpret_cast<const int2 *>(S.edges);
+    A->w = (const uint32_t *)S.w;
+    A->list = (CtEdge *)v[0];
+    A->cw = (uint32_t *)v[1];
+    A->W = S.ct_W;
+    A->segcap = (uint32_t)ct_segcap(S.m, S.ct_W);
+    A->r[0] = (uint64_t *)v[2];
+    A->r[1] = (uint64_t *)v[3];
+    A->h = (uint32_t *)v[4];
+    A->map0 = (uint32_t *)v[5];
+    A->maps = (uint32_t *)v[6];
+    A->cum = (uint32_t *)v[7];
+    A->wlist = A->cum + CT_SMALL;
+    A->flags = (uint8_t *)v[8];
+    A->wpart = (int64_t *)v[9];
+    A->cnt = c->dcnt;
+    return MSF_OK;
+}
+
+// Enqueue a phase's rounds from round k0 on (bound: the most vertices that
+// round can have, expect: those it is likely to have).  A round keeps about
+// a quarter of its vertices, at most half; seven more take CT_SMALL to one.
+static msf_status contract_rounds(Ctx *c, const CtArgs &A, int k0, uint32_t bound, double expect)
+{
+    const int end = CT_ROUNDS - 2;
+    int small = 7;
+    for (int k = k0; k < end && small > 0; ++k, expect /= 4.0) {
+        const bool big = expect > CT_SMALL;
+        if (!big) --small;
+        ct_round(c->stream, A, k, big, bound >> (k - k0));
+        // the first round of a solve ends its build interval
+        if (A.ph == 0 && k == 0) MSF_HIP(hipEventRecord(c->ev[1], c->stream));
+    }
+    return MSF_OK;
+}
+
+// Everything from phase `ph`, round k0 on, to the end of the solve: what
+// has to wait for a phase that is not complete returns at once.
+static msf_status contract_enqueue(Ctx *c, int ph, int k0, uint32_t bound)
+{
+    SolveState &S = c->ss;
+    CtArgs A;
+    MSF_TRY(contract_args(c, &A));
+    void *vcomp = c->ws[WS_P].ptr, *vbits = c->ws[WS_STATUS].ptr;
+    for (int p = ph; p < (S.two_phase ? 2 : 1); ++p) {
+        A.ph = p;
+        A.comp = p ? (const uint32_t *)vcomp : nullptr;
+        if (p == 1 && ph == 0) ct_between(c->stream, A, (uint32_t *)vcomp, (uint32_t *)vbits);
+        const bool mid = p == ph && (k0 > 0 || ph > 0);
+        MSF_TRY(contract_rounds(c, A, mid ? k0 : 0, mid ? bound : (uint32_t)S.n,
+                                mid ? (double)bound : (double)S.n / (p ? 2.0 : 1.0)));
+    }
+    ct_total(c->stream, A, S.two_phase ? 1 : 0);
+    MSF_TRY(launch_output(c, S.b.flags, S.m, S.w, S.wt, S.ids,
+                          (uint8_t *)c->ws[WS_PART].ptr + ct_wpart_bytes(), &c->dcnt->ct.fin));
+    MSF_HIP(hipEventRecord(c->ev[2], c->stream));
+    return end_step(c, 8);
+}
+
+static msf_status contract_start(Ctx *c)
+{
+    SolveState &S = c->ss;
+    const int64_t tiles = (S.m + CT_TILE - 1) / CT_TILE;
+    S.ct_W = (uint32_t)std::min<int64_t>(CT_MAX_WAVES, (tiles + 15) / 16 * 16);
+    S.ct_words = ((size_t)S.m + 3) / 4;
+    const int64_t light = contract_light(S.n, S.m);
+    S.two_phase = light * 10 <= S.m * 6;
+    CtArgs A;
+    MSF_TRY(contract_args(c, &A));
+    S.b.flags = A.flags;
+    MSF_HIP(hipEventRecord(c->ev[0], c->stream));
+    ct_init(c->stream, A, S.ct_words);
+    if (S.two_phase) ct_threshold(c->stream, A, light);
+    ct_select(c->stream, A);
+    // the light edges' list stands in for the adjacency matrix; the build
+    // interval also holds the set-up of the rounds
+    MSF_HIP(hipEventRecord(c->kev[1], c->stream));
+    return contract_enqueue(c, 0, 0, (uint32_t)S.n);
+}
+
+static msf_status contract_advance(Ctx *c)
+{
+    SolveState &S = c->ss;
+    const Counters *h = c->hcnt;
+    if (h->err & ERR_CYCLE) {
+        set_error("internal error: hook cycle detected");
+        return MSF_EDEVICE;
+    }
+    MSF_TRY(decode_err(h->err));
+    if (!h->ct.fin) {
+        // more rounds than were enqueued: go on from the first open one
+        const int ph = h->ct.phdone[0] ? 1 : 0;
+        int k = 0;
+        while (k < CT_ROUNDS && h->ct.done[ph][k]) ++k;
+        if (k >= CT_ROUNDS - 2) {
+            set_error("internal error: rounds did not end");
+            return MSF_EDEVICE;
+        }
+        return contract_enqueue(c, ph, k, h->ct.L[ph][k]);
+    }
+    int rounds = 0;
+    for (int ph = 0; ph < (S.two_phase ? 2 : 1); ++ph)
+        for (int k = 0; k < CT_ROUNDS && h->ct.done[ph][k]; ++k, ++rounds) {
+            if (rounds >= 64) continue;
+            S.st.hooks[rounds] = h->ct.hooks[ph][k];
+            S.st.active_nnz[rounds] = 2 * (int64_t)h->ct.E[ph][k];
+            if (h->ct.hooks[ph][k]) ++S.st.hook_rounds;
+        }
+    S.rounds = rounds;
+    S.st.rounds = rounds;
+    S.st.path = 4;
+    float ms = 0.f;
+    (void)hipEventElapsedTime(&ms, c->ev[0], c->kev[1]);
+    S.st.adjacency_ms = ms;
+    (void)hipEventElapsedTime(&ms, c->ev[0], c->ev[1]);
+    S.st.build_ms = ms;
+    (void)hipEventElapsedTime(&ms, c->ev[1], c->ev[2]);
+    S.st.rounds_ms = ms;
+    c->stats = S.st;
+    S.phase = 5;
+    return MSF_OK;
+}
 
 msf_status solve_start(Ctx *c, int32_t n, int64_t m, const int32_t *d_edges, const void *d_w,
                        msf_wtype wt, int32_t *d_ids)
@@ -164,6 +334,7 @@ msf_status solve_start(Ctx *c, int32_t n, int64_t m, const int32_t *d_edges, con
     S.w = d_w;
     S.wt = wt;
     S.ids = d_ids;
+    if (contract_eligible(c, n, m)) return contract_start(c);
     const int slices = choose_slices(n, m, c->slices);
     MSF_TRY(get_solve_bufs(c, n, m, slices, &S.b));
     // head sweep: 1 from HEADS_MIN_NNZ stored entries on, 2 always
@@ -536,6 +707,8 @@ msf_status solve_advance(Ctx *c)
         S.nR = nRn;
         return more_rounds(S) ? enqueue_round(c) : enqueue_output(c);
     }
+    case 8:  // contracted edge list: everything enqueued has run
+        return contract_advance(c);
     case 4: {  // output ready
         if (h->err & ERR_STAR) {
             set_error("internal error: a tree is not a star after the last round");

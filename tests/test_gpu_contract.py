@@ -1,0 +1,211 @@
+"""Rounds over a contracted edge list (msf_solve's default above one
+workgroup's size) against the oracle: bit-exact ids, count and totals."""
+import math
+import os
+
+import numpy as np
+import pytest
+
+import gen
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+U32, F32 = oracle.W_U32, oracle.W_F32
+
+
+@pytest.fixture(scope="module")
+def pkg():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2110_04865_amd as p
+    p.lib()
+    return p
+
+
+@pytest.fixture(scope="module")
+def ctx(pkg):
+    """Every solve through the contracted rounds, whatever its size."""
+    old = {k: os.environ.get(k) for k in ("MSF_CONTRACT", "MSF_SMALL_M")}
+    os.environ.update(MSF_CONTRACT="2", MSF_SMALL_M="0")
+    try:
+        c = pkg.Context(0)
+    finally:
+        for k, v in old.items():
+            if v is None:
+                os.environ.pop(k, None)
+            else:
+                os.environ[k] = v
+    yield c
+    c.close()
+
+
+def dev(a):
+    a = np.ascontiguousarray(a)
+    if a.dtype == np.uint32:
+        a = a.view(np.int32)
+    return torch.from_numpy(a.reshape(-1).copy()).to("cuda:0")
+
+
+def check(c, n, e, w, wt, label, path=4):
+    print("[gpu-case]", label, f"n={n} m={len(e)} wt={wt}", flush=True)
+    want_ids, want_cnt, want_tot = oracle.msf(n, e, w, wt)
+    ids, cnt, tot = c.solve(n, dev(e), dev(w), wtype=wt)
+    torch.cuda.synchronize()
+    assert cnt == want_cnt, label
+    assert np.array_equal(ids.cpu().numpy().astype(np.int64), want_ids), label
+    assert wt == F32 or tot[0] == want_tot[0], label
+    assert tot[1] == want_tot[1] or (math.isnan(tot[1]) and math.isnan(want_tot[1])), label
+    st = c.stats()
+    assert st["path"] == path, (label, st["path"])
+    assert sum(st["hooks"]) == cnt, label  # every kept hook is one forest edge
+    return st
+
+
+def path_graph(n, w):
+    e = np.stack([np.arange(n - 1), np.arange(1, n)], 1).astype(np.int32)
+    return n, e, np.asarray(w, np.uint32)
+
+
+def ruler(n):
+    """Path whose trees only double every round: weight ctz(i + 1)."""
+    i = np.arange(1, n)
+    return path_graph(n, np.log2((i & -i).astype(np.float64)).astype(np.uint32))
+
+
+# vertices around the sizes where minima move to LDS (4096), one workgroup
+# finishes a round (8192) and a tie tile of 4 x 512 ends; edges around a
+# wave's tile (256) and a sweep of every wave over one tile
+@pytest.mark.parametrize("n,m", [(2, 1), (3, 255), (60, 256), (300, 257), (2047, 9000),
+                                 (2049, 6000), (4096, 4095), (4097, 40000), (8191, 30000),
+                                 (8192, 30000), (8193, 30000), (16385, 20000),
+                                 (70001, 200003), (33000, 900001)])
+def test_random_multigraphs(ctx, n, m):
+    rng = np.random.default_rng(n + m)
+    e = rng.integers(0, n, size=(m, 2)).astype(np.int32)  # loops and parallel edges among them
+    check(ctx, n, e, rng.integers(0, 1 << 32, size=m, dtype=np.uint64).astype(np.uint32), U32,
+          "u32")
+    check(ctx, n, e, rng.integers(0, 3, size=m).astype(np.uint32), U32, "three weights")
+    w = rng.standard_normal(m).astype(np.float32)
+    w[::7] = -0.0
+    w[1::7] = 0.0
+    if m > 1000:
+        w[5] = np.inf
+    check(ctx, n, e, w, F32, "f32")
+
+
+def test_shapes(ctx):
+    rng = np.random.default_rng(5)
+    n = 30000
+    star = np.stack([np.zeros(n - 1), np.arange(1, n)], 1).astype(np.int32)
+    check(ctx, n, star, np.full(n - 1, 9, np.uint32), U32, "star, equal weights")
+    check(ctx, *path_graph(n, np.arange(n - 1, 0, -1)), U32, "path, one long chain of hooks")
+    check(ctx, *path_graph(n, np.full(n - 1, 4)), U32, "path, equal weights")
+    e = np.zeros((5, 2), np.int32)
+    check(ctx, 4, e, np.arange(5).astype(np.uint32), U32, "loops only")
+    e = np.array([[0, 1], [2999999, 5]], np.int32)
+    check(ctx, 3000000, e, np.array([2, 1], np.uint32), U32, "isolated vertices")
+    # weights in the order of the edges, and equal ones: the light edges are
+    # then a stretch of the input
+    e, _ = gen.er(20000, 200000, seed=3)
+    check(ctx, 20000, e, np.arange(200000).astype(np.uint32), U32, "sorted weights")
+    check(ctx, 20000, e, np.arange(200000, 0, -1).astype(np.uint32), U32, "falling weights")
+    check(ctx, 20000, e, np.ones(200000, np.uint32), U32, "equal weights")
+
+
+def test_more_rounds_than_enqueued(ctx):
+    """Trees that only double every round need more rounds than a round's
+    usual shrinking suggests: the solve goes on from the first open round, in
+    the first phase and (with parallel heavier edges) where two phases run."""
+    n, e, w = ruler(1 << 17)
+    st = check(ctx, n, e, w, U32, "ruler path")
+    assert st["hook_rounds"] == 17 and st["hooks"][:2] == [1 << 16, 1 << 15], st
+    e4 = np.concatenate([e, e, e, e])
+    w4 = np.concatenate([w, w + 40, w + 50, w + 60]).astype(np.uint32)
+    check(ctx, n, e4, w4, U32, "ruler path with parallel edges")
+    # light edges that leave the ruler to the second phase
+    loops = np.stack([np.arange(n), np.arange(n)], 1).astype(np.int32)
+    e5 = np.concatenate([loops, loops, loops, e])
+    w5 = np.concatenate([np.zeros(3 * n), w + 100]).astype(np.uint32)
+    check(ctx, n, e5, w5, U32, "ruler path among light loops")
+
+
+@pytest.mark.parametrize("label", ["rmat14", "rmat17", "grid24", "grid 12, 40% dropped",
+                                   "many vertices"])
+def test_families(ctx, label):
+    if label.startswith("rmat"):
+        n, e, w = gen.rmat(int(label[4:]), 16, seed=7)
+        check(ctx, n, e, w, F32, label)
+    elif label == "many vertices":  # lookups through the bits of the largest tree
+        n = (1 << 20) + 77
+        e, w = gen.er(n, 3 * n, seed=8)
+        check(ctx, n, e, w, U32, label)
+    else:
+        s, drop = (24, 0.05) if label == "grid24" else (12, 0.4)
+        n, e, w = gen.grid(s, s, s, drop, seed=9)
+        check(ctx, n, e, w, U32, label)
+
+
+def test_default_route_and_bad_input(pkg):
+    """A default context takes this path above 2^17 edges; bad input ends
+    with MSF_EINVAL, the output untouched and the context still solving."""
+    c = pkg.Context(0)
+    n, m = 40000, (1 << 17) + 1
+    e, w = gen.er(n, m, seed=11)
+    check(c, n, e, w, U32, "default route")
+    wf = gen.weights(m, gen.W_F32, seed=12)
+    out = torch.full((n,), -7, dtype=torch.int32, device="cuda:0")
+    for what in ("endpoint", "negative", "nan"):
+        be, bw = e.copy(), wf.copy()
+        if what == "endpoint":
+            be[m - 1, 1] = n
+        elif what == "negative":
+            be[m // 2, 0] = -1
+        else:
+            bw[m // 3] = np.nan
+        with pytest.raises(pkg.MSFError) as ex:
+            c.solve(n, dev(be), dev(bw), wtype=F32, out=out)
+        assert ex.value.status == 1, what
+        torch.cuda.synchronize()
+        assert bool((out == -7).all()), what
+        check(c, n, e, wf, F32, "valid after " + what)
+    c.close()
+
+
+def test_refused_allocations(pkg):
+    """Every workspace allocation of the path refused in turn: MSF_ENOMEM,
+    the output untouched, and the next solve right."""
+    n, e, w = gen.rmat(13, 16, seed=13)
+    want_ids, want_cnt, _ = oracle.msf(n, e, w, F32)
+    de, dw = dev(e), dev(w)
+    for k in range(40):
+        keys = dict(MSF_CONTRACT="2", MSF_SMALL_M="0", MSF_TEST_FAIL_ALLOC_AFTER=str(k))
+        old = {q: os.environ.get(q) for q in keys}
+        os.environ.update(keys)
+        try:
+            c = pkg.Context(0)
+        finally:
+            for q, v in old.items():
+                if v is None:
+                    os.environ.pop(q, None)
+                else:
+                    os.environ[q] = v
+        out = torch.full((n,), -7, dtype=torch.int32, device="cuda:0")
+        failed = False
+        try:
+            c.solve(n, de, dw, wtype=F32, out=out)
+        except pkg.MSFError as ex:
+            assert ex.status == 2
+            failed = True
+        torch.cuda.synchronize()
+        if failed:
+            assert bool((out == -7).all()), k
+        ids, cnt, _ = c.solve(n, de, dw, wtype=F32)
+        torch.cuda.synchronize()
+        assert cnt == want_cnt and np.array_equal(ids.cpu().numpy().astype(np.int64), want_ids), k
+        c.close()
+        if not failed:
+            break
+    assert 5 <= k < 39
