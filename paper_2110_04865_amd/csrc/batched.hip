@@ -142,7 +142,9 @@ msf_status batched_persistent(Ctx *c, int32_t G, const int64_t *vtx_off, const i
         });
         // a sample with the batch's size mix for the tuner: every k-th graph
         std::vector<uint32_t> sample;
-        const uint32_t step = std::max<uint32_t>(1, Gs / 256);
+        // (about four per compute unit, so that a configuration with several
+        // workgroups on each shows what it gains)
+        const uint32_t step = std::max<uint32_t>(1, Gs / 1024);
         for (uint32_t i = 0; i < Gs; i += step) sample.push_back(order[i]);
         int cus = 0;
         MSF_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
@@ -181,7 +183,6 @@ msf_status batched_persistent(Ctx *c, int32_t G, const int64_t *vtx_off, const i
         A.tot_f64 = d_tf;
         A.scratch = (uint8_t *)vscr;
         A.slot_bytes = slot_bytes;
-        A.m_cap = m_cap;
         auto grid_of = [&](int i, uint32_t graphs) {
             return (unsigned)std::max<uint32_t>(
                 1, std::min<uint32_t>({graphs, slots, (uint32_t)std::max(1, cus * bpc[i])}));
@@ -284,7 +285,6 @@ msf_status solve_small(Ctx *c, int32_t n, int64_t m, const int32_t *d_edges, con
     A.out = d_ids;
     A.scratch = (uint8_t *)vscr;
     A.slot_bytes = persist_slot_bytes((uint32_t)n, (uint32_t)m);
-    A.m_cap = (uint32_t)m;
     A.lds_bytes = SMALL_LDS;
     launch_small_setup(s, (int64_t *)A.vtx_off, (int64_t *)A.edge_off, (uint32_t *)A.order, n, m);
     MSF_HIP(hipEventRecord(c->ev[0], s));

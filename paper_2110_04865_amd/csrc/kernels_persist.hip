@@ -7,35 +7,37 @@
 // with a workgroup barrier between the steps of a round and a per-graph
 // termination test, so no round boundary involves the host:
 //
-//   sweep     the multilinear kernel of section 3.1 with the projection of
-//             Algorithm 2, over the graph's edge list: an edge {u, v} with
-//             key k and roots a = p[u] != b = p[v] lowers r[a] and r[b] to k
-//             (both stored directions of the adjacency matrix at once).
-//             From the second round on, the sweep also writes the edges it
-//             found live, as (a, b, key), and the next round sweeps only
-//             those (their endpoints are roots of the previous round, whose
-//             parents are the current roots): intra-component edges are
-//             filtered out round by round.
-//   hook      every root with r != empty hooks onto the root at the other
-//             end of its minimum edge (Algorithm 2, hooking step);
-//   tie break of two roots that hooked onto each other, the smaller id
-//             stays root (Algorithm 2, tie-breaking step; section 2.3); the
-//             kept hooks' edges are flagged and their weights summed;
-//   shortcut  pointer jumping over the hook forest until every tree is a
-//             star (complete shortcutting, section 4.2), then p <- h[p];
-//   stop      after a round in which nothing hooks.
+//   list      the graph's live edges, dense and in edge-id order, with their
+//             ends renumbered every round (0 .. L - 1); a pass maps the ends,
+//             drops the edges that became internal, in place, and lowers the
+//             minima of both ends (the multilinear kernel of section 3.1 with
+//             the projection of Algorithm 2, both stored directions at once);
+//   hook      every vertex hooks onto the other end of its minimum edge;
+//   tie break of two vertices that hooked onto each other the smaller stays
+//             root (Algorithm 2, tie-breaking step; section 2.3);
+//   shortcut  complete shortcutting (section 4.2), then new numbers for the
+//             roots that can still hook;
+//   stop      when no live edge is left.
+// Once 128 or fewer vertices are left, one pass takes the minimum key of
+// every pair of them into a matrix in LDS and the remaining rounds run on
+// that.  From PERSIST_TWO_PHASE_M edges on the lightest edges go first (see
+// kernels_contract.hip): their forest is built, one pass over the graph
+// drops every edge inside one of its trees, and a second phase finishes.
 //
-// State of a graph with n vertices and m edges: r u64[n], p u32[n] (a
-// parent chain: a vertex that stops being a root points to the root that
-// absorbed it), h u32[n], the list of roots that can still hook u32[n] and
-// the forest flags as a bitmask u32[ceil(m/32)], in LDS when
-// 20 n + 4 ceil(m/32) bytes fit the launch's dynamic LDS, else in the
-// workgroup's slot of a global scratch area (same code, the address space
-// is fixed per instantiation).  The live-edge lists of the later rounds
-// (16 bytes per edge, two buffers) are always in the slot.  Keys use the
-// graph's local edge ids, so each graph's forest is the one msf_solve finds
-// on that graph alone.  Outputs: the forest's local edge ids in ascending
-// order from out + vtx_off[g], count and exact totals.
+// A round's minima, hook records and map take 10 bytes of LDS per vertex of
+// the round; where that does not fit (the first round of a graph of more
+// than 15K vertices in 150 KB) the minima are taken by ranges of vertices,
+// one pass over the list each.  The list and the larger maps are in the
+// workgroup's slot of a global scratch area (at most 32 m + 20 n bytes).
+// Keys use the graph's local edge ids, so each graph's forest is the one
+// msf_solve finds on that graph alone.  Outputs: the forest's local edge ids
+// in ascending order from out + vtx_off[g], count and exact totals.
+//
+// Measured on 10^4 Erdos-Renyi graphs (64 to 65536 vertices, 382M edges):
+// 42.3 -> 7.6 ms against the earlier form, which swept the edge list with a
+// parent vector in LDS and the minima in global memory (10.7 cycles an edge
+// visit there, and 23 visits per vertex instead of 9).  It moves 37 GB (27
+// read, 10 written) in that time, 4.8 TB/s: bound by memory.
 #include <algorithm>
 #include <map>
 #include <mutex>
@@ -47,21 +49,14 @@
 #include "persist.hpp"
 #include "wave.hpp"
 
-// Graphs whose state does not fit the launch's LDS keep their parent
-// vector there as 16-bit ids when it fits (1).
-#ifndef PERSIST_P16
-#define PERSIST_P16 1
+// Edges from which a graph takes its light edges first.
+#ifndef PERSIST_TWO_PHASE_M
+#define PERSIST_TWO_PHASE_M 2048
 #endif
 
 namespace msf {
 
 namespace {
-
-// One live edge of a later round: roots of the previous round and the key.
-struct __align__(16) LiveEdge {
-    uint32_t a, b;
-    uint64_t key;
-};
 
 __device__ __forceinline__ uint64_t ld_min_u64(uint64_t *p, uint64_t v)
 {
@@ -82,310 +77,819 @@ __device__ __forceinline__ uint32_t weight_key(uint32_t bits, int wt)
     return wt == MSF_W_F32 ? wkey_f32_bits(bits) : bits;
 }
 
-// Shared control words of a workgroup.
-struct Ctl {
-    uint32_t g;          // graph being solved (NONE32: queue empty)
-    uint32_t live;       // live edges written by the current sweep
-    uint32_t hooks;      // kept hooks of the current round
-    uint32_t changed[2]; // shortcut passes, alternating
-    uint32_t err;        // ERR_* seen by this workgroup
-    uint32_t gerr;       // the current graph failed validation
+// The list keeps the order of the edge ids, so (weight key, position in the
+// list) compares like (weight key, edge id): a minimum names its edge's
+// place in the list, where the hook finds both ends.
+
+struct PEdge {
+    uint32_t a, b, w, e;
 };
 
-// P16: the state is in the workgroup's slot except p, which is kept in LDS
-// as 16-bit vertex ids (pstate; graphs of at most 2^16 vertices): the sweep
-// looks up p at both ends of every edge, and the hook follows p chains.
-template <int NT, int EPT, int WT, bool IN_LDS, bool P16>
-__device__ __forceinline__ void solve_graph(const PersistArgs &A, uint32_t g, uint8_t *state,
-                                            uint16_t *pstate, LiveEdge *buf0, LiveEdge *buf1,
-                                            Ctl &ctl, int64_t *s_sum, int64_t *s_tot,
-                                            uint32_t *s_scan)
+// The list as arrays of words: with P16 both ends in one word (12 bytes an
+// edge), else a word each.  At most 2^22 edges, so byte offsets fit 32 bits
+// and the accesses take a scalar base.
+template <bool P16>
+struct PList {
+    uint32_t *ab, *b, *w, *e;
+    __device__ __forceinline__ static uint32_t ld(const uint32_t *p, uint32_t j)
+    {
+        return *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(p) + (j << 2));
+    }
+    __device__ __forceinline__ static void st(uint32_t *p, uint32_t j, uint32_t v)
+    {
+        *reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(p) + (j << 2)) = v;
+    }
+    __device__ __forceinline__ PList(uint8_t *at, uint32_t m)
+    {
+        ab = reinterpret_cast<uint32_t *>(at);
+        b = ab + m;
+        w = b + m;
+        e = w + m;
+    }
+    __device__ __forceinline__ PEdge get(uint32_t j) const
+    {
+        const uint32_t x = ld(ab, j);
+        if (P16) return PEdge{x & 0xFFFFu, x >> 16, ld(w, j), ld(e, j)};
+        return PEdge{x, ld(b, j), ld(w, j), ld(e, j)};
+    }
+    __device__ __forceinline__ void put(uint32_t j, const PEdge &x) const
+    {
+        if (P16) {
+            st(ab, j, x.a | (x.b << 16));
+        } else {
+            st(ab, j, x.a);
+            st(b, j, x.b);
+        }
+        st(w, j, x.w);
+        st(e, j, x.e);
+    }
+};
+
+constexpr uint32_t PC_MARK = 0xFFFFFFFFu;
+constexpr int PC_LEVELS = 40;
+
+// Shared control words of the contracted solve.
+constexpr uint32_t PC_MAT = 128;  // most vertices a pair matrix takes
+template <int NT>
+struct PCtl {
+    uint32_t cnt[2][NT / 64];  // kept edges per wave, alternating tiles
+    uint32_t hist[256];
+    uint32_t bin, rank;
+    uint32_t live, dead, hooks;
+    uint32_t g;     // graph being solved (NONE32: queue empty)
+    uint32_t err;   // ERR_* seen by this workgroup
+    uint32_t gerr;  // the current graph failed validation
+    uint32_t off[PC_LEVELS];
+    // rounds on a pair matrix: minima, component and target per vertex
+    uint64_t mr[PC_MAT];
+    uint32_t mc[PC_MAT], mh[PC_MAT];
+};
+
+// A value that every lane of every wave reads alike, in a scalar register
+// (what comes from LDS is taken for a vector value otherwise, and with it
+// every size, pointer and loop bound derived from it).
+__device__ __forceinline__ uint32_t uniform(uint32_t v)
 {
-    static_assert(!(IN_LDS && P16), "p in LDS on its own only when the rest is not");
-    using PT = typename std::conditional<P16, uint16_t, uint32_t>::type;
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+
+// Items of a tile: wave w takes the 64 U consecutive ones from 64 U w on,
+// item q of lane l being 64 q + l of them.  From each wave's count of kept
+// items, this wave's first place in the tile; *total gets the tile's count.
+// One barrier; the counts alternate between two buffers (par).
+template <int NT>
+__device__ __forceinline__ uint32_t wave_place(uint32_t c, PCtl<NT> &pc, int par, uint32_t *total)
+{
+    constexpr int NW = NT / 64;
+    static_assert(NW <= 16, "one row of lanes");
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (__lane_id() == 0) pc.cnt[par][w] = c;
+    __syncthreads();
+    uint32_t v = __lane_id() < NW ? pc.cnt[par][__lane_id()] : 0u;
+    v += dpp_move<DPP_ROW_SHR1>(v);
+    if (NW > 2) v += dpp_move<DPP_ROW_SHR2>(v);
+    if (NW > 4) v += dpp_move<DPP_ROW_SHR4>(v);
+    if (NW > 8) v += dpp_move<DPP_ROW_SHR8>(v);
+    *total = (uint32_t)__builtin_amdgcn_readlane((int)v, NW - 1);
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, w) - c;
+}
+
+// A thread's first item (item q is 64 q further).  Opaque, so that each pass
+// computes its own offsets: shared by all the passes inlined into the kernel
+// they cost some 40 registers everywhere.
+template <int U>
+__device__ __forceinline__ uint32_t tile_item0()
+{
+    uint32_t t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return (t >> 6) * (64u * U) + (t & 63u);
+}
+
+// How a pass lowers minima: not at all; r[end] by an LDS atomic each; the
+// same behind a read (few vertices: most edges change nothing, and atomics
+// on few addresses serialise); only ends in [lo, lo + len), behind a read;
+// the pair's entry of a matrix, behind a read (nothing else is kept).
+enum { PM_NONE, PM_MIN, PM_MINF, PM_RANGE, PM_MAT };
+
+struct PMinArgs {
+    uint64_t *r = nullptr;  // minima, or the matrix (rows of 1 << lo entries)
+    uint32_t lo = 0, len = 0;
+};
+
+template <int MODE, int U>
+__device__ __forceinline__ void lower_ends(const PMinArgs &M, const PEdge (&x)[U],
+                                           const bool (&live)[U], const uint32_t (&pos)[U])
+{
+    if (MODE == PM_MIN) {
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            if (!live[q]) continue;
+            const uint64_t key = ((uint64_t)x[q].w << 32) | pos[q];
+            ld_min_u64(M.r + x[q].a, key);
+            ld_min_u64(M.r + x[q].b, key);
+        }
+    }
+    if (MODE == PM_MINF || MODE == PM_RANGE) {
+        uint32_t ia[U], ib[U];
+        uint64_t ra[U], rb[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            ia[q] = x[q].a - (MODE == PM_RANGE ? M.lo : 0u);
+            ib[q] = x[q].b - (MODE == PM_RANGE ? M.lo : 0u);
+            const bool in = live[q];
+            ra[q] = M.r[in && (MODE != PM_RANGE || ia[q] < M.len) ? ia[q] : 0u];
+            rb[q] = M.r[in && (MODE != PM_RANGE || ib[q] < M.len) ? ib[q] : 0u];
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            if (!live[q]) continue;
+            const uint64_t key = ((uint64_t)x[q].w << 32) | pos[q];
+            if (MODE != PM_RANGE || ia[q] < M.len) lower(M.r, ia[q], ra[q], key);
+            if (MODE != PM_RANGE || ib[q] < M.len) lower(M.r, ib[q], rb[q], key);
+        }
+    }
+    if (MODE == PM_MAT) {
+        uint32_t at[U];
+        uint64_t cur[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            at[q] = live[q] ? (min(x[q].a, x[q].b) << M.lo) + max(x[q].a, x[q].b) : 0u;
+            cur[q] = M.r[at[q]];
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            if (live[q]) lower(M.r, at[q], cur[q], ((uint64_t)x[q].w << 32) | x[q].e);
+    }
+}
+
+// One pass over the list.  MAP: ends go through the map (MT in LDS, or u32 in
+// the slot) and only edges between different vertices stay, in place (not
+// with a matrix: the list is not needed after it).  Returns the edges kept.
+template <int NT, int U, bool MAP, int MODE, typename MT, bool P16>
+__device__ __forceinline__ uint32_t list_pass(const PList<P16> list, uint32_t E, const MT *map,
+                                              const PMinArgs M, PCtl<NT> &pc)
+{
+    constexpr bool KEEP = MAP && MODE != PM_MAT;
+    const uint32_t me = tile_item0<U>();
+    uint32_t out = 0;
+    int par = 0;
+    PEdge nx[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) nx[q] = list.get(min((me + 64u * q), E - 1));
+    for (uint32_t base = 0; base < E; base += NT * U) {
+        PEdge x[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) x[q] = nx[q];
+        // the next tile's loads are in flight while this one is worked on
+        // (in place: a tile's edges are written below its own end only)
+        if (base + NT * U < E) {
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                nx[q] = list.get(min(base + NT * U + (me + 64u * q), E - 1));
+        }
+        if (MAP) {
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                x[q].a = map[x[q].a];
+                x[q].b = map[x[q].b];
+            }
+        }
+        bool live[U];
+        uint32_t pos[U];
+        uint32_t c = 0;
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const uint32_t j = base + (me + 64u * q);
+            live[q] = j < E && x[q].a != x[q].b;
+            pos[q] = j;
+            if (KEEP) {
+                const uint64_t mask = __ballot(live[q]);
+                pos[q] = c + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                c += (uint32_t)__popcll(mask);
+            }
+        }
+        if (KEEP) {
+            uint32_t tot;
+            const uint32_t first = out + wave_place<NT>(c, pc, par, &tot);
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                pos[q] += first;
+                if (live[q]) list.put(pos[q], x[q]);
+            }
+            out += tot;
+            par ^= 1;
+        }
+        lower_ends<MODE, U>(M, x, live, pos);
+    }
+    __syncthreads();
+    return KEEP ? out : E;
+}
+
+// Hook records of the vertices [lo, lo + len) from their minima r (weight
+// key, place in the list), in place: x = target, y = edge, PC_MARK for none.
+// With many vertices per edge one more pass over the list lets every edge
+// that is a minimum leave its other end there (streamed, 12 bytes an edge);
+// otherwise each vertex reads its edge (two cache lines a vertex).
+template <int NT, int U, bool P16>
+__device__ __forceinline__ void hook_records(const PList<P16> list, uint32_t E, uint64_t *r,
+                                             uint32_t lo, uint32_t len, uint32_t L)
+{
+    const uint32_t tid = threadIdx.x;
+    constexpr uint32_t DONE = 0x80000000u;  // places stay below it
+    const bool pass = (uint64_t)L * 8 > E;
+    if (pass && E) {
+        const uint32_t me = tile_item0<U>();
+        PEdge nx[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) nx[q] = list.get(min((me + 64u * q), E - 1));
+        for (uint32_t base = 0; base < E; base += NT * U) {
+            PEdge x[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) x[q] = nx[q];
+            if (base + NT * U < E) {
+#pragma unroll
+                for (int q = 0; q < U; ++q)
+                    nx[q] = list.get(min(base + NT * U + (me + 64u * q), E - 1));
+            }
+            uint64_t ra[U], rb[U];
+            uint32_t ia[U], ib[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const bool in = base + (me + 64u * q) < E;
+                ia[q] = in ? x[q].a - lo : len;
+                ib[q] = in ? x[q].b - lo : len;
+                ra[q] = r[ia[q] < len ? ia[q] : 0u];
+                rb[q] = r[ib[q] < len ? ib[q] : 0u];
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const uint64_t key = ((uint64_t)x[q].w << 32) | (base + (me + 64u * q));
+                if (ia[q] < len && ra[q] == key) r[ia[q]] = ((uint64_t)x[q].e << 32) | DONE | x[q].b;
+                if (ib[q] < len && rb[q] == key) r[ib[q]] = ((uint64_t)x[q].e << 32) | DONE | x[q].a;
+            }
+        }
+        __syncthreads();
+    }
+    for (uint32_t i = tid; i < len; i += NT) {
+        const uint64_t key = r[i];
+        uint64_t v = ((uint64_t)PC_MARK << 32) | (lo + i);
+        if (key != KEY_INF) {
+            if (pass) {
+                v = key & ~(uint64_t)DONE;
+            } else {
+                const PEdge x = list.get((uint32_t)key);
+                v = ((uint64_t)x.e << 32) | (x.a == lo + i ? x.b : x.a);
+            }
+        }
+        r[i] = v;
+    }
+    __syncthreads();
+}
+
+// The remaining rounds of a graph with L <= 128 vertices on the matrix of
+// its pairs' minimum keys (rows of 1 << sh entries, upper triangle).  Every
+// vertex ends in a finished tree; with did, did[i] = its number.
+template <int NT>
+__device__ __forceinline__ void matrix_rounds(const uint64_t *mat, uint32_t L, int sh,
+                                              uint8_t *flags, uint32_t *did, PCtl<NT> &pc,
+                                              uint32_t *round_hooks, uint32_t &nrounds)
+{
+    const uint32_t tid = threadIdx.x, cells = L << sh, colm = (1u << sh) - 1u;
+    if (tid < L) pc.mc[tid] = tid;
+    for (;;) {
+        if (tid < L) pc.mr[tid] = KEY_INF;
+        if (tid == 0) pc.hooks = 0;
+        __syncthreads();
+        for (uint32_t x = tid; x < cells; x += NT) {
+            const uint32_t i = x >> sh, j = x & colm;
+            if (j <= i || j >= L) continue;
+            const uint64_t key = mat[x];
+            const uint32_t a = pc.mc[i], b = pc.mc[j];
+            if (key == KEY_INF || a == b) continue;
+            lower(pc.mr, a, pc.mr[a], key);
+            lower(pc.mr, b, pc.mr[b], key);
+        }
+        __syncthreads();
+        // keys are distinct: exactly one pair has each minimum
+        for (uint32_t x = tid; x < cells; x += NT) {
+            const uint32_t i = x >> sh, j = x & colm;
+            if (j <= i || j >= L) continue;
+            const uint64_t key = mat[x];
+            const uint32_t a = pc.mc[i], b = pc.mc[j];
+            if (key == KEY_INF || a == b) continue;
+            if (pc.mr[a] == key) pc.mh[a] = b;
+            if (pc.mr[b] == key) pc.mh[b] = a;
+        }
+        __syncthreads();
+        bool hook = false;
+        if (tid < L && pc.mc[tid] == tid) {
+            const uint64_t key = pc.mr[tid];
+            if (key == KEY_INF) {
+                pc.mh[tid] = tid;
+            } else {
+                const uint32_t t = pc.mh[tid];
+                // (the larger of a mutual pair never reverts)
+                if (tid < t && pc.mh[t] == tid) {
+                    pc.mh[tid] = tid;
+                } else {
+                    flags[(uint32_t)key] = 1;
+                    hook = true;
+                }
+            }
+        }
+        const uint64_t mk = __ballot(hook);
+        if (__lane_id() == 0 && mk) atomicAdd(&pc.hooks, (uint32_t)__popcll(mk));
+        __syncthreads();
+        const uint32_t hooks = uniform(pc.hooks);
+        if (!hooks) break;
+        if (round_hooks && tid == 0 && nrounds < 64) round_hooks[nrounds] = hooks;
+        ++nrounds;
+        uint32_t x = 0;
+        if (tid < L) {
+            x = pc.mc[tid];
+            while (pc.mh[x] != x) x = pc.mh[x];
+        }
+        __syncthreads();
+        if (tid < L) pc.mc[tid] = x;
+    }
+    if (did) {
+        // numbers of the trees, by their roots
+        const bool root = tid < L && pc.mc[tid] == tid;
+        const uint64_t mk = __ballot(root);
+        uint32_t at = 0;
+        if (__lane_id() == 0 && mk) at = atomicAdd(&pc.dead, (uint32_t)__popcll(mk));
+        at = __shfl(at, 0, 64);
+        if (root) pc.mh[tid] = at + __popcll(mk & lanemask_lt());
+        __syncthreads();
+        if (tid < L) did[tid] = pc.mh[pc.mc[tid]];
+    }
+    __syncthreads();
+}
+
+// Targets of a round's vertices: 16-bit in LDS, or the x words of the hook
+// records in the slot (more than 2^16 vertices, or a launch with little LDS).
+struct H16 {
+    uint16_t *h;
+    __device__ __forceinline__ uint32_t get(uint32_t i) const
+    {
+        return __hip_atomic_load(h + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ void set(uint32_t i, uint32_t v) const
+    {
+        __hip_atomic_store(h + i, (uint16_t)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+};
+struct HRec {
+    uint2 *h;
+    __device__ __forceinline__ uint32_t get(uint32_t i) const
+    {
+        return __hip_atomic_load(&h[i].x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ void set(uint32_t i, uint32_t v) const
+    {
+        __hip_atomic_store(&h[i].x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+};
+
+// Tie break and shortcut over the targets h of a round's L vertices and the
+// hooked edges in rec[i].y (PC_MARK: no edge).  Afterwards h[i] is i's root,
+// and rec[root].y the root's number in the next round; a vertex without an
+// edge gets dead number did[i] (if wanted) and rec[i].y = PC_MARK.
+template <int NT, typename H, typename C>
+__device__ __forceinline__ void tie_and_chase(const H h, uint2 *rec, uint32_t L, uint8_t *flags,
+                                              uint32_t *did, C &pc)
+{
+    if (threadIdx.x == 0) pc.live = pc.hooks = 0;
+    __syncthreads();
+    uint32_t kept = 0;
+    for (uint32_t i = threadIdx.x; i < L; i += NT) {
+        const uint32_t e = rec[i].y;
+        if (e == PC_MARK) continue;
+        const uint32_t t = h.get(i);
+        // the larger of a mutual pair never reverts, whatever it reads
+        if (i < t && h.get(t) == i) {
+            h.set(i, i);
+        } else {
+            flags[e] = 1;
+            ++kept;
+        }
+    }
+    kept = wave_sum(kept);
+    if (__lane_id() == 0 && kept) atomicAdd(&pc.hooks, kept);
+    __syncthreads();
+    // each vertex follows its chain to the root, writing improvements back
+    for (uint32_t i = threadIdx.x; i < L; i += NT) {
+        uint32_t x = h.get(i);
+        if (x == i) continue;
+        for (;;) {
+            const uint32_t y = h.get(x);
+            if (y == x) break;
+            x = y;
+            h.set(i, x);
+        }
+    }
+    __syncthreads();
+    // numbers: roots with an edge from 0, finished trees from pc.dead
+    for (uint32_t base = 0; base < L; base += NT) {
+        const uint32_t i = base + threadIdx.x;
+        const bool root = i < L && h.get(i) == i;
+        const bool dead = root && rec[i].y == PC_MARK, stay = root && !dead;
+        const uint64_t ms = __ballot(stay), md = __ballot(dead);
+        uint32_t as = 0, ad = 0;
+        if (__lane_id() == 0) {
+            if (ms) as = atomicAdd(&pc.live, (uint32_t)__popcll(ms));
+            if (md && did) ad = atomicAdd(&pc.dead, (uint32_t)__popcll(md));
+        }
+        as = __shfl(as, 0, 64);
+        ad = __shfl(ad, 0, 64);
+        if (stay) rec[i].y = as + __popcll(ms & lanemask_lt());
+        if (dead && did) did[i] = ad + __popcll(md & lanemask_lt());
+    }
+    __syncthreads();
+}
+
+// The forest of graph g; flags (one byte per edge, in the slot) are set for
+// its edges.  Returns false if the graph failed validation.
+template <int NT, int U, int WT, bool P16>
+__device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t g, uint8_t *smem,
+                                                 uint8_t *slot, PCtl<NT> &pc, int64_t *s_sum, int64_t *s_tot, uint32_t *s_scan)
+{
     const uint32_t tid = threadIdx.x;
     const int64_t v0 = A.vtx_off[g];
     const uint32_t n = (uint32_t)(A.vtx_off[g + 1] - v0);
     const int64_t e0 = A.edge_off[g];
     const uint32_t m = (uint32_t)(A.edge_off[g + 1] - e0);
-    const uint32_t nw = (m + 31) / 32;
-    // r: root minima; p: parent chain (a root points to itself; a vertex
-    // that stopped being a root points to the root that absorbed it, after
-    // that round's shortcut); h: hook targets; L: the current roots
-    uint64_t *r = reinterpret_cast<uint64_t *>(state);
-    PT *p;
-    uint32_t *h;
-    if constexpr (P16) {
-        p = pstate;
-        h = reinterpret_cast<uint32_t *>(state + 8 * (size_t)n);
-    } else {
-        p = reinterpret_cast<PT *>(state + 8 * (size_t)n);
-        h = reinterpret_cast<uint32_t *>(p + n);
-    }
-    uint32_t *L = h + n;
-    uint32_t *fb = L + n;
     const int2 *E = reinterpret_cast<const int2 *>(A.edges) + e0;
     const uint32_t *W = A.w + e0;
-
-    for (uint32_t i = tid; i < n; i += NT) {
-        r[i] = KEY_INF;
-        p[i] = (PT)i;
-        L[i] = i;
+    const size_t S = A.lds_bytes;
+    // light edges: n ln(4 m / n) / 2 (kernels_contract.hip); below a few
+    // thousand edges, or with few edges per vertex, every edge at once
+    const uint32_t light = (uint32_t)(0.5f * n * __logf(4.0f * (float)m / (float)(n ? n : 1u)));
+    const bool two = !A.round_hooks && m >= PERSIST_TWO_PHASE_M && m >= 2 * n && light * 5ull <= m * 3ull;
+    // the slot: list 16 m, flags m (16 at a time), hook records 8 n, maps 8 n
+    // (all levels), with two phases tree numbers 8 n: at most 32 m + 20 n
+    // bytes (two phases only with m >= 2 n)
+    const PList<P16> list(slot, m);
+    uint8_t *flags = slot + 16 * (size_t)m;
+    uint4 *fw = reinterpret_cast<uint4 *>(flags);
+    const uint32_t nw = (m + 15) / 16;
+    uint2 *rec = reinterpret_cast<uint2 *>(fw + nw);
+    uint32_t *mapg = reinterpret_cast<uint32_t *>(rec + n);
+    uint32_t *didg = mapg + 2 * (size_t)n;
+    for (uint32_t k = tid; k < nw; k += NT) fw[k] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid == 0) {
+        pc.gerr = 0;
+        pc.dead = 0;
     }
-    uint32_t nroots = n;
-    for (uint32_t k = tid; k < nw; k += NT) fb[k] = 0u;
-    if (tid == 0) ctl.gerr = 0;
-    uint32_t err = 0;
-    WSum ws;
-    uint32_t nlive = m;
+    uint32_t T = 0xFFFFFFFFu;
+    if (two) {
+        // the threshold: the weight at the light edges' share of a sample
+        const uint32_t pos = (uint32_t)((uint64_t)m * tid / NT) +
+                             (tid * 0x9E3779B9u >> 8) % max(1u, m / NT);
+        const uint32_t wk = weight_key(W[min(pos, m - 1)], WT);
+        uint32_t pre = 0, want = (uint32_t)((uint64_t)light * NT / m);
+        for (int sh = 24; sh >= 0; sh -= 8) {
+            for (uint32_t k = tid; k < 256; k += NT) pc.hist[k] = 0;
+            __syncthreads();
+            if (sh == 24 || (wk >> (sh + 8)) == pre) atomicAdd(&pc.hist[(wk >> sh) & 255u], 1u);
+            __syncthreads();
+            if (tid < 64) {
+                uint32_t c[4], t = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) t += c[q] = pc.hist[tid * 4 + q];
+                uint32_t ex = wave_incl_sum(t) - t;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (want >= ex && want < ex + c[q]) {
+                        pc.bin = tid * 4 + q;
+                        pc.rank = want - ex;
+                    }
+                    ex += c[q];
+                }
+            }
+            __syncthreads();
+            pre = (pre << 8) | uniform(pc.bin);
+            want = uniform(pc.rank);
+            __syncthreads();
+        }
+        T = pre;
+    }
     __syncthreads();
-
-    for (uint32_t round = 0;; ++round) {
-        if (tid == 0) {
-            ctl.live = 0;
-            ctl.hooks = 0;
-        }
-        __syncthreads();
-        // ---- sweep -------------------------------------------------------
-        LiveEdge *dst = (round & 1) ? buf0 : buf1;
-        const LiveEdge *src = (round & 1) ? buf1 : buf0;
-        // Each step of a sweep runs in phases over the thread's EPT edges:
-        // every load first, then the parent lookups, then the minima, so
-        // the loads of all EPT edges are in flight together.  Indices past
-        // the end are clamped (the loads stay in bounds) and the edge is
-        // masked off.
-        if (round <= 1) {
-            for (uint32_t base = 0; base < m; base += NT * EPT) {
-                int2 uv[EPT];
-                uint32_t wb[EPT];
+    // the list: every edge read and checked, those up to the threshold kept;
+    // the first round's minima in the same pass where they fit LDS
+    uint64_t *r = reinterpret_cast<uint64_t *>(smem);
+    uint32_t Ec = 0, err = 0;
+    bool ready = 10 * (size_t)n + 16 <= S;
+    if (ready)
+        for (uint32_t i = tid; i < n; i += NT) r[i] = KEY_INF;
+    __syncthreads();
+    {
+        const uint32_t me = tile_item0<U>();
+        int par = 0;
+        int2 uv[U];
+        uint32_t wn[U];
+        if (m > 0) {
 #pragma unroll
-                for (int k = 0; k < EPT; ++k) {
-                    const uint32_t e = base + k * NT + tid;
-                    const uint32_t ec = e < m ? e : m - 1;
-                    uv[k] = E[ec];
-                    wb[k] = W[ec];
-                }
-                uint32_t a[EPT], b[EPT];
-                bool ok[EPT];
-#pragma unroll
-                for (int k = 0; k < EPT; ++k) {
-                    const uint32_t e = base + k * NT + tid;
-                    a[k] = (uint32_t)uv[k].x;
-                    b[k] = (uint32_t)uv[k].y;
-                    ok[k] = e < m;
-                    if (ok[k] && (a[k] >= n || b[k] >= n)) {
-                        err |= ERR_ENDPOINT;
-                        ok[k] = false;
-                    }
-                    if (ok[k] && WT == MSF_W_F32 && (wb[k] & 0x7FFFFFFFu) > 0x7F800000u) {
-                        err |= ERR_NAN;
-                        ok[k] = false;
-                    }
-                    if (!ok[k]) a[k] = b[k] = 0;
-                }
-                if (round == 1) {
-#pragma unroll
-                    for (int k = 0; k < EPT; ++k) {
-                        a[k] = p[a[k]];
-                        b[k] = p[b[k]];
-                    }
-                }
-                uint64_t ra[EPT], rb[EPT];
-#pragma unroll
-                for (int k = 0; k < EPT; ++k) {
-                    ra[k] = r[a[k]];
-                    rb[k] = r[b[k]];
-                }
-#pragma unroll
-                for (int k = 0; k < EPT; ++k) {
-                    const uint32_t e = base + k * NT + tid;
-                    const uint64_t key = ((uint64_t)weight_key(wb[k], WT) << 32) | e;
-                    const bool live = ok[k] && a[k] != b[k];
-                    if (live) {
-                        lower(r, a[k], ra[k], key);
-                        lower(r, b[k], rb[k], key);
-                    }
-                    if (round == 1) {
-                        // keep the live edges for the next round
-                        const uint64_t mask = __ballot(live);
-                        uint32_t at = 0;
-                        if (__lane_id() == 0 && mask)
-                            at = atomicAdd(&ctl.live, (uint32_t)__popcll(mask));
-                        at = __shfl(at, 0, 64);
-                        if (live)
-                            dst[at + __popcll(mask & lanemask_lt())] = LiveEdge{a[k], b[k], key};
-                    }
-                }
-            }
-        } else {
-            for (uint32_t base = 0; base < nlive; base += NT * EPT) {
-                LiveEdge x[EPT];
-#pragma unroll
-                for (int k = 0; k < EPT; ++k) {
-                    const uint32_t j = base + k * NT + tid;
-                    x[k] = src[j < nlive ? j : nlive - 1];
-                }
-                uint32_t a[EPT], b[EPT];
-#pragma unroll
-                for (int k = 0; k < EPT; ++k) {
-                    a[k] = p[x[k].a];
-                    b[k] = p[x[k].b];
-                }
-                uint64_t ra[EPT], rb[EPT];
-#pragma unroll
-                for (int k = 0; k < EPT; ++k) {
-                    ra[k] = r[a[k]];
-                    rb[k] = r[b[k]];
-                }
-#pragma unroll
-                for (int k = 0; k < EPT; ++k) {
-                    const uint32_t j = base + k * NT + tid;
-                    const bool live = j < nlive && a[k] != b[k];
-                    if (live) {
-                        lower(r, a[k], ra[k], x[k].key);
-                        lower(r, b[k], rb[k], x[k].key);
-                    }
-                    const uint64_t mask = __ballot(live);
-                    uint32_t at = 0;
-                    if (__lane_id() == 0 && mask)
-                        at = atomicAdd(&ctl.live, (uint32_t)__popcll(mask));
-                    at = __shfl(at, 0, 64);
-                    if (live)
-                        dst[at + __popcll(mask & lanemask_lt())] = LiveEdge{a[k], b[k], x[k].key};
-                }
+            for (int q = 0; q < U; ++q) {
+                const uint32_t e = min((me + 64u * q), m - 1);
+                uv[q] = E[e];
+                wn[q] = W[e];
             }
         }
-        __syncthreads();
-        if (round >= 1) nlive = ctl.live;
-        // ---- hook: every root onto the root across its minimum edge ------
-        // The other endpoint's root at the start of this round is the end
-        // of its parent chain (one step per round since it stopped being a
-        // root); p is not written in this step, so the chains are stable.
-        for (uint32_t k = tid; k < nroots; k += NT) {
-            const uint32_t i = L[k];
-            const uint64_t key = r[i];
-            uint32_t t = i;
-            if (key != KEY_INF) {
-                const int2 uv = E[(uint32_t)key];
-                uint32_t a = (uint32_t)uv.x, b = (uint32_t)uv.y;
-                while (p[a] != a) a = p[a];
-                while (p[b] != b) b = p[b];
-                t = a == i ? b : a;
+        for (uint32_t base = 0; base < m; base += NT * U) {
+            PEdge x[U];
+            uint32_t pos[U], c = 0;
+            bool keep[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                x[q] = PEdge{(uint32_t)uv[q].x, (uint32_t)uv[q].y, wn[q],
+                             base + (me + 64u * q)};
+            if (base + NT * U < m) {  // the next tile's loads in flight meanwhile
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    const uint32_t e = min(base + NT * U + (me + 64u * q), m - 1);
+                    uv[q] = E[e];
+                    wn[q] = W[e];
+                }
             }
-            h[i] = t;
-        }
-        __syncthreads();
-        // ---- tie break, forest flags and weights -------------------------
-        // The larger root of a mutual pair never reverts, whatever it reads,
-        // so reverting the smaller one in place is race-free.
-        uint32_t kept = 0;
-        for (uint32_t k = tid; k < nroots; k += NT) {
-            const uint32_t i = L[k];
-            const uint32_t t = h[i];
-            if (t == i) continue;
-            if (i < t && h[t] == i) {
-                h[i] = i;
-                continue;
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                uint32_t bad = x[q].a >= n || x[q].b >= n ? ERR_ENDPOINT : 0u;
+                if (WT == MSF_W_F32 && (x[q].w & 0x7FFFFFFFu) > 0x7F800000u) bad |= ERR_NAN;
+                err |= bad;
+                x[q].w = weight_key(x[q].w, WT);
+                keep[q] = base + (me + 64u * q) < m && !bad && x[q].a != x[q].b && x[q].w <= T;
+                const uint64_t mask = __ballot(keep[q]);
+                pos[q] = c + (uint32_t)__popcll(mask & lanemask_lt());
+                c += (uint32_t)__popcll(mask);
             }
-            const uint64_t key = r[i];
-            const uint32_t e = (uint32_t)key;
-            atomicOr(fb + (e >> 5), 1u << (e & 31));
-            wsum_add<WT>(ws, (uint32_t)(key >> 32));
-            ++kept;
+            uint32_t tot;
+            const uint32_t first = Ec + wave_place<NT>(c, pc, par, &tot);
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                pos[q] += first;
+                if (keep[q]) list.put(pos[q], x[q]);
+            }
+            if (ready) lower_ends<PM_MIN, U>(PMinArgs{r, 0, 0}, x, keep, pos);
+            Ec += tot;
+            par ^= 1;
         }
-        kept = wave_sum(kept);
-        if (__lane_id() == 0 && kept) atomicAdd(&ctl.hooks, kept);
-        __syncthreads();
-        if (A.round_hooks && tid == 0 && round < 64) A.round_hooks[round] = ctl.hooks;
-        if (ctl.hooks == 0) {
-            if (A.round_hooks && tid == 0) A.round_hooks[64] = round + 1;
-            break;
-        }
-        // the roots that can still hook at least halve every round, so a
-        // graph of at most 2^31 vertices needs fewer than 33 rounds
-        if (round >= 40) {
-            err |= ERR_CYCLE;
-            break;
-        }
-        // ---- complete shortcutting over the roots ------------------------
-        for (uint32_t pass = 0;; ++pass) {
-            if (tid == 0) ctl.changed[pass & 1] = 0;
+    }
+    if (err) atomicOr(&pc.gerr, err);
+    __syncthreads();
+    const bool bad = uniform(pc.gerr) != 0;
+    uint32_t nrounds = 0;
+    for (int ph = 0; ph < (two ? 2 : 1) && !bad; ++ph) {
+        const bool trees = two && ph == 0;  // tree numbers wanted
+        uint32_t L = n, off = 0;
+        int lev = 0;
+        if (ph == 1) {
+            // a tree number per vertex: from the last level's vertices down
+            for (int k = (int)uniform(pc.bin) - 2; k >= 0; --k) {
+                const uint32_t ok = uniform(pc.off[k]), o1 = uniform(pc.off[k + 1]), Lk = o1 - ok;
+                for (uint32_t i = tid; i < Lk; i += NT) {
+                    const uint32_t x = mapg[ok + i];
+                    if (x != PC_MARK) didg[ok + i] = didg[o1 + x];
+                }
+                __syncthreads();
+            }
+            L = uniform(pc.dead);
+            // the edges between different trees, again in edge-id order
+            // (tree numbers at the top of LDS, minima below where both fit)
+            const bool lds = 2 * ((size_t)n + 8) <= S && n <= 65536u;
+            uint16_t *c16 = reinterpret_cast<uint16_t *>(smem + S) - ((n + 7) & ~7u);
+            if (lds)
+                for (uint32_t i = tid; i < n; i += NT) c16[i] = (uint16_t)didg[i];
+            ready = lds && 8 * (size_t)L + 2 * ((size_t)n + 8) <= S;
+            if (ready)
+                for (uint32_t i = tid; i < L; i += NT) r[i] = KEY_INF;
             __syncthreads();
-            uint32_t any = 0;
-            for (uint32_t k = tid; k < nroots; k += NT) {
-                const uint32_t i = L[k];
-                const uint32_t x = h[i];
-                const uint32_t y = h[x];
-                if (y != x) {
-                    h[i] = y;
-                    any = 1;
-                }
+            Ec = 0;
+            const uint32_t me = tile_item0<U>();
+            int par = 0;
+            int2 uv[U];
+            uint32_t wn[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const uint32_t e = min((me + 64u * q), m - 1);
+                uv[q] = E[e];
+                wn[q] = W[e];
             }
-            if (__ballot(any) && __lane_id() == 0) ctl.changed[pass & 1] = 1;
+            for (uint32_t base = 0; base < m; base += NT * U) {
+                PEdge x[U];
+                uint32_t pos[U], c = 0;
+                bool keep[U];
+                if (lds) {
+#pragma unroll
+                    for (int q = 0; q < U; ++q) {
+                        x[q].a = c16[uv[q].x];
+                        x[q].b = c16[uv[q].y];
+                    }
+                } else {
+#pragma unroll
+                    for (int q = 0; q < U; ++q) {
+                        x[q].a = didg[uv[q].x];
+                        x[q].b = didg[uv[q].y];
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < U; ++q) x[q].w = weight_key(wn[q], WT);
+                if (base + NT * U < m) {
+#pragma unroll
+                    for (int q = 0; q < U; ++q) {
+                        const uint32_t e = min(base + NT * U + (me + 64u * q), m - 1);
+                        uv[q] = E[e];
+                        wn[q] = W[e];
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    x[q].e = base + (me + 64u * q);
+                    keep[q] = x[q].e < m && x[q].a != x[q].b;
+                    const uint64_t mask = __ballot(keep[q]);
+                    pos[q] = c + (uint32_t)__popcll(mask & lanemask_lt());
+                    c += (uint32_t)__popcll(mask);
+                }
+                uint32_t tot;
+                const uint32_t first = Ec + wave_place<NT>(c, pc, par, &tot);
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    pos[q] += first;
+                    if (keep[q]) list.put(pos[q], x[q]);
+                }
+                if (ready) lower_ends<PM_MINF, U>(PMinArgs{r, 0, 0}, x, keep, pos);
+                Ec += tot;
+                par ^= 1;
+            }
             __syncthreads();
-            if (!ctl.changed[pass & 1]) break;
-            if (pass > 64) {  // the hook forest is acyclic: cannot happen
+        }
+        // ready: this round's minima were taken when the list was written
+        for (uint32_t round = 0; L > 0 && (Ec > 0 || trees); ++round) {
+            if (round >= PC_LEVELS - 1) {  // every round halves the vertices with an edge
                 err |= ERR_CYCLE;
                 break;
             }
-        }
-        if (err & ERR_CYCLE) break;
-        // ---- p <- h at the old roots; the roots that stay, compacted -----
-        // in place, one tile at a time: every read of a tile happens before
-        // the barrier, and writes land below the tile's end (at most as
-        // many roots stay as were read so far)
-        if (tid == 0) ctl.live = 0;
-        __syncthreads();
-        for (uint32_t base = 0; base < nroots; base += NT) {
-            const uint32_t k = base + tid;
-            const uint32_t i = k < nroots ? L[k] : NONE32;
-            bool stay = false;
-            if (i != NONE32) {
-                const uint32_t t = h[i];
-                p[i] = (PT)t;
-                // a root without an outgoing edge spans its whole component:
-                // no edge can reach it again, so it leaves the list
-                stay = t == i && r[i] != KEY_INF;
-                r[i] = KEY_INF;
+            if (10 * (size_t)L + 16 <= S) {
+                // minima, targets, numbers and the map (2 L at the top) in LDS
+                if (!ready) {
+                    for (uint32_t i = tid; i < L; i += NT) r[i] = KEY_INF;
+                    __syncthreads();
+                    if (Ec)
+                        list_pass<NT, U, false, PM_MINF, uint16_t>(list, Ec, nullptr,
+                                                                   PMinArgs{r, 0, 0}, pc);
+                }
+                uint2 *lrec = reinterpret_cast<uint2 *>(smem);
+                hook_records<NT, U>(list, Ec, r, 0, L, L);
+                tie_and_chase<NT>(HRec{lrec}, lrec, L, flags, trees ? didg + off : nullptr, pc);
+                uint16_t *map = reinterpret_cast<uint16_t *>(smem + S) - ((L + 7) & ~7u);
+                for (uint32_t i = tid; i < L; i += NT) {
+                    const uint32_t v = lrec[lrec[i].x].y;
+                    map[i] = (uint16_t)v;
+                    if (trees) mapg[off + i] = v;
+                }
+            } else {
+                // minima by vertex ranges that fit LDS, hook records in the slot
+                const uint32_t rs = (uint32_t)(S / 8);
+                for (uint32_t lo = 0; lo < L; lo += rs) {
+                    const uint32_t len = min(rs, L - lo);
+                    for (uint32_t i = tid; i < len; i += NT) r[i] = KEY_INF;
+                    __syncthreads();
+                    if (Ec)
+                        list_pass<NT, U, false, PM_RANGE, uint16_t>(list, Ec, nullptr,
+                                                                    PMinArgs{r, lo, len}, pc);
+                    hook_records<NT, U>(list, Ec, r, lo, len, L);
+                    for (uint32_t i = tid; i < len; i += NT) {
+                        const uint64_t v = r[i];
+                        rec[lo + i] = make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+                    }
+                    __syncthreads();
+                }
+                if (2 * ((size_t)L + 8) <= S && L <= 65536u) {
+                    uint16_t *map = reinterpret_cast<uint16_t *>(smem + S) - ((L + 7) & ~7u);
+                    for (uint32_t i = tid; i < L; i += NT) map[i] = (uint16_t)rec[i].x;
+                    __syncthreads();
+                    tie_and_chase<NT>(H16{map}, rec, L, flags, trees ? didg + off : nullptr, pc);
+                    for (uint32_t i = tid; i < L; i += NT) {
+                        const uint32_t v = rec[map[i]].y;
+                        map[i] = (uint16_t)v;  // only its own thread reads it now
+                        if (trees) mapg[off + i] = v;
+                    }
+                } else {
+                    tie_and_chase<NT>(HRec{rec}, rec, L, flags, trees ? didg + off : nullptr, pc);
+                    for (uint32_t i = tid; i < L; i += NT) mapg[off + i] = rec[rec[i].x].y;
+                }
             }
+            const uint32_t Ln = uniform(pc.live);
+            if (A.round_hooks && tid == 0 && nrounds < 64) A.round_hooks[nrounds] = pc.hooks;
+            ++nrounds;
+            if (tid == 0) pc.off[lev] = off;
+            ++lev;
+            // the next round's list, and its minima where map and minima fit;
+            // with few vertices left the pairs' minima instead, and the
+            // remaining rounds on them
+            const bool m16 = 2 * ((size_t)L + 8) <= S && L <= 65536u;
+            const uint16_t *map = reinterpret_cast<uint16_t *>(smem + S) - ((L + 7) & ~7u);
+            const uint32_t sh = Ln <= 32 ? 5u : Ln <= 64 ? 6u : 7u;
+            const bool mat = m16 && Ln > 0 && Ln <= PC_MAT &&
+                             (8ull * Ln << sh) + 2 * ((size_t)L + 8) <= S;
+            ready = m16 && 8 * (size_t)Ln + 2 * ((size_t)L + 8) <= S;
             __syncthreads();
-            const uint64_t mask = __ballot(stay);
-            uint32_t at = 0;
-            if (__lane_id() == 0 && mask) at = atomicAdd(&ctl.live, (uint32_t)__popcll(mask));
-            at = __shfl(at, 0, 64);
-            if (stay) L[at + __popcll(mask & lanemask_lt())] = i;
+            const uint32_t words = mat ? Ln << sh : ready ? Ln : 0u;
+            for (uint32_t i = tid; i < words; i += NT) r[i] = KEY_INF;
+            __syncthreads();
+            if (mat) {
+                if (Ec)
+                    list_pass<NT, U, true, PM_MAT, uint16_t>(list, Ec, map, PMinArgs{r, sh, 0},
+                                                             pc);
+                if (trees) {
+                    off += L;
+                    if (tid == 0) pc.off[lev] = off;
+                    for (uint32_t i = tid; i < Ln; i += NT) mapg[off + i] = PC_MARK;
+                }
+                matrix_rounds<NT>(r, Ln, (int)sh, flags, trees ? didg + off : nullptr, pc,
+                                  A.round_hooks, nrounds);
+                if (trees) off += Ln;
+                ++lev;
+                break;
+            }
+            if (Ec) {
+                const PMinArgs M{r, 0, 0};
+                if (ready && Ln >= 1024)
+                    Ec = list_pass<NT, U, true, PM_MIN, uint16_t>(list, Ec, map, M, pc);
+                else if (ready)
+                    Ec = list_pass<NT, U, true, PM_MINF, uint16_t>(list, Ec, map, M, pc);
+                else if (m16)
+                    Ec = list_pass<NT, U, true, PM_NONE, uint16_t>(list, Ec, map, M, pc);
+                else
+                    Ec = list_pass<NT, U, true, PM_NONE, uint32_t>(list, Ec, mapg + off, M, pc);
+            }
+            if (trees) off += L;
+            L = Ln;
+        }
+        if (tid == 0) {
+            pc.off[lev] = off;
+            pc.bin = (uint32_t)lev;  // levels of the first phase
         }
         __syncthreads();
-        nroots = ctl.live;
-        __syncthreads();
+        if (err & ERR_CYCLE) break;
+    }
+    if (A.round_hooks && tid == 0) {
+        // the round that finds no edge left
+        if (nrounds < 64) A.round_hooks[nrounds] = 0;
+        A.round_hooks[64] = nrounds + 1;
     }
 
     // ---- output: ascending forest ids, count, totals ----------------------
     // a graph that failed validation writes no ids (the call fails); its
     // count is minus its error flags
-    if (err) atomicOr(&ctl.gerr, err);
+    if (err) atomicOr(&pc.gerr, err);
     __syncthreads();
-    const bool bad = ctl.gerr != 0;
-    // each thread owns a contiguous range of flag words
-    const uint32_t per = (nw + NT - 1) / NT;
-    const uint32_t w_lo = tid * per, w_hi = min(nw, w_lo + per);
-    uint32_t cnt = 0;
-    for (uint32_t k = w_lo; k < w_hi; ++k) cnt += __popc(fb[k]);
-    uint32_t total;
-    uint32_t pos = block_excl_sum<NT>(cnt, s_scan, &total);
+    const bool failed = uniform(pc.gerr) != 0;
+    WSum ws;
+    uint32_t pos = 0;
     int32_t *out = A.out + v0;
-    for (uint32_t k = w_lo; k < w_hi && !bad; ++k) {
-        uint32_t bits = fb[k];
-        while (bits) {
-            const uint32_t b = __builtin_ctz(bits);
-            bits &= bits - 1;
-            out[pos++] = (int32_t)(k * 32 + b);
+    for (uint32_t base = 0; base < nw && !failed; base += NT) {
+        const uint32_t k = base + tid;
+        const uint4 f4 = k < nw ? fw[k] : make_uint4(0u, 0u, 0u, 0u);
+        const uint32_t f[4] = {f4.x, f4.y, f4.z, f4.w};
+        const uint32_t c = __popc(f[0]) + __popc(f[1]) + __popc(f[2]) + __popc(f[3]);
+        uint32_t total;
+        uint32_t at = pos + block_excl_sum<NT>(c, s_scan, &total);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            for (uint32_t bits = f[q]; bits; bits &= bits - 1) {
+                const uint32_t e = 16 * k + 4 * q + (__builtin_ctz(bits) >> 3);
+                out[at++] = (int32_t)e;
+                wsum_add<WT>(ws, weight_key(W[e], WT));
+            }
         }
+        pos += total;
     }
     wsum_block<NT, WT>(ws, s_sum, s_tot, 1);
-    if (err) atomicOr(&ctl.err, err);
+    if (err) atomicOr(&pc.err, err);
     if (tid == 0) {
-        A.counts[g] = bad ? -(int64_t)ctl.gerr : (int64_t)total;
+        A.counts[g] = failed ? -(int64_t)pc.gerr : (int64_t)pos;
         A.tot_u64[(size_t)g * A.tot_stride] = WT == MSF_W_U32 ? (uint64_t)s_tot[0] : 0;
         A.tot_f64[(size_t)g * A.tot_stride] = exact_total_f64((uint64_t)s_tot[0], s_tot + 1,
                                        (uint32_t)s_tot[1 + ACC_DIGITS],
@@ -400,37 +904,27 @@ template <int NT, int EPT, int WT>
 __global__ __launch_bounds__(NT) void k_persist(PersistArgs A)
 {
     extern __shared__ __align__(16) uint8_t smem[];
-    __shared__ Ctl ctl;
+    __shared__ PCtl<NT> pc;
     __shared__ int64_t s_sum[(NT / 64) * (ACC_DIGITS + 1)];
     __shared__ int64_t s_tot[WS_WORDS];
     __shared__ uint32_t s_scan[NT / 64 + 1];
     uint8_t *slot = A.scratch + (size_t)blockIdx.x * A.slot_bytes;
-    LiveEdge *buf0 = reinterpret_cast<LiveEdge *>(slot);
-    LiveEdge *buf1 = buf0 + A.m_cap;
-    uint8_t *gstate = reinterpret_cast<uint8_t *>(buf1 + A.m_cap);
-    if (threadIdx.x == 0) ctl.err = 0;
+    if (threadIdx.x == 0) pc.err = 0;
     for (;;) {
         if (threadIdx.x == 0) {
             const uint32_t k = atomicAdd(A.queue, 1u);
-            ctl.g = k < (uint32_t)A.G ? (A.order ? A.order[k] : k) : NONE32;
+            pc.g = k < (uint32_t)A.G ? (A.order ? A.order[k] : k) : NONE32;
         }
         __syncthreads();
-        const uint32_t g = ctl.g;
+        const uint32_t g = uniform(pc.g);
         if (g == NONE32) break;
-        const uint32_t n = (uint32_t)(A.vtx_off[g + 1] - A.vtx_off[g]);
-        const uint32_t m = (uint32_t)(A.edge_off[g + 1] - A.edge_off[g]);
-        if (persist_state_bytes(n, m) <= A.lds_bytes)
-            solve_graph<NT, EPT, WT, true, false>(A, g, smem, nullptr, buf0, buf1, ctl, s_sum,
-                                                  s_tot, s_scan);
-        else if (PERSIST_P16 && n <= 65536u && 2 * (size_t)n <= A.lds_bytes)
-            solve_graph<NT, EPT, WT, false, true>(A, g, gstate,
-                                                  reinterpret_cast<uint16_t *>(smem), buf0,
-                                                  buf1, ctl, s_sum, s_tot, s_scan);
+        // vertex numbers of at most 16 bits: both ends of an edge in one word
+        if (A.vtx_off[g + 1] - A.vtx_off[g] <= 65536)
+            solve_contracted<NT, EPT, WT, true>(A, g, smem, slot, pc, s_sum, s_tot, s_scan);
         else
-            solve_graph<NT, EPT, WT, false, false>(A, g, gstate, nullptr, buf0, buf1, ctl,
-                                                   s_sum, s_tot, s_scan);
+            solve_contracted<NT, EPT, WT, false>(A, g, smem, slot, pc, s_sum, s_tot, s_scan);
     }
-    if (threadIdx.x == 0 && ctl.err) atomicOr(A.err, ctl.err);
+    if (threadIdx.x == 0 && pc.err) atomicOr(A.err, pc.err);
 }
 
 // Queue counter and error word to zero (a kernel, not a memset, so the

@@ -186,7 +186,6 @@ extern "C" msf_status msf_solve_batched_noalloc(msf_ctx *ctx, int32_t G, const i
     A.tot_stride = sizeof(msf_total) / sizeof(uint64_t);
     A.scratch = (uint8_t *)base + CTRL_BYTES;
     A.slot_bytes = slot;
-    A.m_cap = std::max(h[C_MAXM], 1u);
     A.lds_bytes = cfg.lds;
     MSF_HIP(launch_persist(s, A, cfg, (int)wt, (unsigned)slots));
     c->stats = msf_stats{};

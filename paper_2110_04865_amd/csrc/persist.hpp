@@ -15,9 +15,9 @@ namespace msf {
 // Arguments of one persistent launch.  Graph g has vtx_off[g+1]-vtx_off[g]
 // vertices and edge_off[g+1]-edge_off[g] edges (local endpoint ids, weight
 // bits); order lists the graphs to solve (largest first; null: every graph
-// in index order), queue is the shared cursor into it.  Each workgroup owns slot_bytes of scratch: two
-// live-edge buffers of m_cap entries (16 bytes each), then the state of a
-// graph too large for LDS (persist_state_bytes(n_cap, m_cap)).
+// in index order), queue is the shared cursor into it.  Each workgroup owns
+// slot_bytes of scratch (persist_slot_bytes of the launch's largest n and m)
+// for its graph's edge list, forest flags and larger maps.
 struct PersistArgs {
     int32_t G = 0;
     const uint32_t *order = nullptr;
@@ -32,7 +32,6 @@ struct PersistArgs {
     double *tot_f64 = nullptr;
     uint8_t *scratch = nullptr;
     size_t slot_bytes = 0;
-    uint32_t m_cap = 0;
     uint32_t lds_bytes = 0;
     uint32_t *err = nullptr;
     // nullable: kept hooks of rounds 0..63 and, at [64], the rounds run
@@ -44,8 +43,9 @@ struct PersistArgs {
 };
 
 // A launch configuration: threads per workgroup, edges each thread loads per
-// step of a sweep, dynamic LDS per workgroup (graphs whose state fits it
-// keep their state in LDS; it also sets how many workgroups share a CU).
+// step of a pass, dynamic LDS per workgroup (rounds whose minima and map fit
+// it need one pass over the edges; it also sets how many workgroups share a
+// CU).
 struct PersistCfg {
     int nt;
     int ept;
@@ -58,6 +58,8 @@ constexpr uint32_t PERSIST_MAX_M = 1u << 22;
 // Dynamic LDS of the one-workgroup solve of a small graph (msf_solve).
 constexpr uint32_t SMALL_LDS = 150u << 10;
 
+// The size by which msf_solve and the server choose the one-workgroup path
+// (up to SMALL_LDS), and the part of a slot beside 32 bytes per edge.
 __host__ __device__ inline size_t persist_state_bytes(uint32_t n, uint32_t m)
 {
     return 20 * (size_t)n + 4 * (((size_t)m + 31) / 32);

@@ -487,7 +487,6 @@ void job_start(msf_server *s, BatchJob *j, std::vector<Request *> &&reqs)
     A.tot_f64 = (double *)vres + 2 * G;
     A.scratch = (uint8_t *)vscr;
     A.slot_bytes = slot_bytes;
-    A.m_cap = mmax;
     A.lds_bytes = cfg.lds;
     ok = ok && launch_persist(st, A, cfg, (int)wt, (unsigned)slots) == hipSuccess &&
          hipMemcpyAsync(res, vres, 24 * G, hipMemcpyDeviceToHost, st) == hipSuccess &&

@@ -93,8 +93,8 @@ bool persist_cfg_fits(int device, const PersistCfg &cfg)
         (void)hipGetLastError();
         return false;
     }
-    // room for the kernel's own static LDS (under 2 KB)
-    return (int)cfg.lds + 4096 <= maxlds;
+    // room for the kernel's own static LDS (about 5 KB)
+    return (int)cfg.lds + 6144 <= maxlds;
 }
 
 msf_status persist_pick(Ctx *c, const BatchShape &shape, int wt, const PersistTuneRun &run,

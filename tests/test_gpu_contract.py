@@ -209,3 +209,47 @@ def test_refused_allocations(pkg):
         if not failed:
             break
     assert 5 <= k < 39
+
+
+# vertices where the pair matrix starts (32, 64, 128), where a round's minima
+# and map stop fitting 32 / 64 / 150 KB of LDS (bytes / 10), where minima take
+# a second range (bytes / 8) and where vertex numbers outgrow 16 bits; edges
+# around two per vertex and the size from which light edges go first
+BATCH_SIZES = [(0, 0), (1, 0), (2, 1), (31, 90), (33, 200), (64, 300), (65, 300), (128, 900),
+               (129, 900), (511, 2047), (512, 2048), (512, 2049), (1024, 2048), (1025, 2049),
+               (3275, 4096), (3276, 4097), (3277, 20000), (4095, 16385), (4097, 9000),
+               (6552, 30000), (6553, 30000), (8193, 40000), (15358, 70000), (15359, 31000),
+               (19199, 60000), (19201, 60000), (38401, 90000), (65536, 180000),
+               (65537, 180000), (76801, 80000), (76801, 190000)]
+
+
+@pytest.mark.parametrize("config", [0, 2, 3, 6, 7])
+def test_batched_sizes(pkg, config):
+    rng = np.random.default_rng(17)
+    graphs = [rng.integers(0, max(n, 1), size=(m, 2)).astype(np.int32) for n, m in BATCH_SIZES]
+    vo = np.cumsum([0] + [n for n, _ in BATCH_SIZES]).astype(np.int64)
+    eo = np.cumsum([0] + [m for _, m in BATCH_SIZES]).astype(np.int64)
+    e = np.concatenate(graphs)
+    wide = rng.integers(0, 1 << 32, size=len(e), dtype=np.uint64).astype(np.uint32)
+    ties = rng.integers(0, 3, size=len(e)).astype(np.uint32)
+    f = rng.standard_normal(len(e)).astype(np.float32)
+    c = pkg.Context(0)
+    old = os.environ.get("MSF_BATCH_CONFIG")
+    os.environ["MSF_BATCH_CONFIG"] = str(config)
+    try:
+        for w, wt, label in ((wide, U32, "wide"), (ties, U32, "ties"), (f, F32, "float")):
+            print("[gpu-case] batched sizes", config, label, flush=True)
+            ids, counts, totals = c.solve_batched(vo, eo, dev(e), dev(w), wtype=wt)
+            torch.cuda.synchronize()
+            ids = ids.cpu().numpy()
+            for g, (n, m) in enumerate(BATCH_SIZES):
+                wi, wc, wtot = oracle.msf(n, e[eo[g]:eo[g + 1]], w[eo[g]:eo[g + 1]], wt)
+                assert counts[g] == wc, (label, n, m)
+                assert np.array_equal(ids[vo[g]:vo[g] + wc].astype(np.int64), wi), (label, n, m)
+                assert totals[g][1] == wtot[1], (label, n, m)
+    finally:
+        if old is None:
+            os.environ.pop("MSF_BATCH_CONFIG", None)
+        else:
+            os.environ["MSF_BATCH_CONFIG"] = old
+        c.close()
