@@ -110,49 +110,52 @@ __device__ inline double exact_total_f64(uint64_t su, const int64_t *acc, uint32
     if (wt == MSF_W_U32) return (double)su;
     if (pinf || ninf)
         return (pinf && ninf) ? __builtin_nan("") : (pinf ? __builtin_inf() : -__builtin_inf());
+    // every index below is a constant once unrolled: the digits stay in
+    // registers (one thread does this at the end of every solve; with the
+    // bits taken out of an indexed array it took 15 us)
     uint32_t dig[ACC_DIGITS];
     int64_t carry = 0;
+#pragma unroll
     for (int d = 0; d < ACC_DIGITS; ++d) {
         const int64_t v = acc[d] + carry;
         dig[d] = (uint32_t)(v & 0xFFFFFFFFll);
         carry = v >> 32;  // arithmetic shift: floor division
     }
     const bool neg = carry < 0;
-    if (neg) {
-        uint64_t c1 = 1;
-        for (int d = 0; d < ACC_DIGITS; ++d) {
-            const uint64_t v = (uint64_t)(uint32_t)~dig[d] + c1;
-            dig[d] = (uint32_t)v;
-            c1 = v >> 32;
-        }
+    uint64_t c1 = 1;
+#pragma unroll
+    for (int d = 0; d < ACC_DIGITS; ++d) {
+        const uint64_t v = (uint64_t)(uint32_t)~dig[d] + c1;
+        if (neg) dig[d] = (uint32_t)v;
+        c1 = v >> 32;
     }
-    int top = -1;
-    for (int d = ACC_DIGITS - 1; d >= 0 && top < 0; --d)
-        if (dig[d]) top = d * 32 + 31 - __builtin_clz(dig[d]);
-    double out = 0.0;
-    if (top >= 0) {
-        auto bit = [&](int i) -> uint32_t { return i < 0 ? 0u : (dig[i >> 5] >> (i & 31)) & 1u; };
-        uint64_t q = 0;
-        const int lo = top - 52;  // lowest kept bit
-        int scale = lo;           // value = q * 2^(scale - 149)
-        if (lo < 0) {
-            scale = 0;
-            for (int i = top; i >= 0; --i) q = (q << 1) | bit(i);
-        } else {
-            for (int i = top; i >= lo; --i) q = (q << 1) | bit(i);
-            const uint32_t rb = bit(lo - 1);
-            uint32_t sticky = 0;
-            for (int i = lo - 2; i >= 0 && !sticky; --i) sticky |= bit(i);
-            if (rb && (sticky || (q & 1u))) {
-                ++q;
-                if (q == (1ull << 53)) {
-                    q >>= 1;
-                    ++scale;
-                }
-            }
-        }
-        out = ldexp((double)q, scale - 149);
+    // the top non-zero digit, the two below it, and whether any bit is set
+    // further down
+    uint32_t w2 = 0, w1 = 0, w0 = 0, rest = 0;
+    int top = 0;
+#pragma unroll
+    for (int d = 0; d < ACC_DIGITS; ++d) {
+        if (!dig[d]) continue;
+        w2 = dig[d];
+        w1 = d >= 1 ? dig[d >= 1 ? d - 1 : 0] : 0u;
+        w0 = d >= 2 ? dig[d >= 2 ? d - 2 : 0] : 0u;
+        rest = 0;
+#pragma unroll
+        for (int q = 0; q + 2 < d; ++q) rest |= dig[q];
+        top = d * 32;
     }
+    if (!w2) return 0.0;
+    const int lz = __builtin_clz(w2);
+    top += 31 - lz;  // place of the highest bit
+    // that bit at the top of 96
+    uint64_t hi = ((uint64_t)w2 << 32) | w1;
+    hi = lz ? (hi << lz) | (w0 >> (32 - lz)) : hi;
+    const bool sticky = rest != 0 || (uint32_t)(w0 << lz) != 0;
+    // 53 bits, rounded to nearest, ties to even (a carry out makes 2^53)
+    uint64_t q = hi >> 11;
+    const uint32_t low = (uint32_t)hi & 0x7FFu;
+    if (low > 0x400u || (low == 0x400u && (sticky || (q & 1u)))) ++q;
+    const double out = ldexp((double)q, top - 52 - 149);
     return neg ? -out : out;
 }
 
