@@ -18,7 +18,8 @@ struct __align__(16) CtEdge {
 constexpr uint32_t CT_MAX_WAVES = 8192;  // list segments
 constexpr uint32_t CT_TILE = 256;        // input edges a wave takes at a time
 constexpr uint32_t CT_WSLOTS = 2048;     // partial weight sums
-constexpr uint32_t CT_SMALL = 8192;      // vertices one workgroup handles alone
+constexpr uint32_t CT_SMALL = 7680;      // vertices whose minima fit LDS (two workgroups a CU)
+constexpr uint32_t CT_PAIR = 32;         // vertices finished on their pairs' minima
 
 // Edges per list segment when the input's tiles are dealt to W waves.
 inline size_t ct_segcap(int64_t m, uint32_t W)
@@ -39,7 +40,8 @@ struct CtArgs {
     const uint32_t *comp = nullptr;  // phase 1: vertex -> tree of phase 0
     CtEdge *list = nullptr;          // W segments of segcap edges
     uint32_t *cw = nullptr;          // edges in each segment
-    uint32_t W = 0;
+    uint32_t W = 0;           // waves that write the list, one segment each
+    uint32_t pass_waves = 0;  // waves of an edge pass in phase 0 (in phase 1, W)
     uint32_t segcap = 0;
     uint64_t *r[2] = {nullptr, nullptr};  // root minima of even and odd rounds
     uint32_t *h = nullptr;
@@ -47,6 +49,7 @@ struct CtArgs {
     uint32_t *maps = nullptr;  // later rounds, one after the other
     uint32_t *cum = nullptr;   // first small round's vertices -> current ones
     uint32_t *wlist = nullptr; // weight keys of the small rounds' hooks
+    uint64_t *mat = nullptr;   // pair minima of a phase's last vertices
     uint8_t *flags = nullptr;
     int64_t *wpart = nullptr;
     Counters *cnt = nullptr;

@@ -40,9 +40,8 @@ namespace {
 
 constexpr int CE_NT = 1024;               // threads of the list kernels
 constexpr int CE_WV = CE_NT / 64;
-constexpr uint32_t CT_LDSR = 4096;        // minima kept in LDS up to this many vertices
 constexpr uint32_t CT_DEAD = 0x80000000u; // a finished tree's number
-constexpr uint32_t CT_SAMPLES = 8192;
+constexpr uint32_t CT_SAMPLES = 2048;
 
 __device__ __forceinline__ uint32_t ct_wkey(uint32_t bits, int wt)
 {
@@ -110,6 +109,7 @@ __global__ __launch_bounds__(256) void k_ct_init(CtArgs A, size_t flag_words)
     for (size_t i = i0; i < (size_t)A.n; i += stride) A.r[0][i] = KEY_INF;
     for (size_t i = i0; i < flag_words; i += stride) fl[i] = 0u;
     for (size_t i = i0; i < (size_t)CT_WSLOTS * WS_WORDS; i += stride) A.wpart[i] = 0;
+    for (size_t i = i0; i < CT_PAIR * CT_PAIR; i += stride) A.mat[i] = KEY_INF;
 }
 
 void ct_init(hipStream_t s, const CtArgs &A, size_t flag_words)
@@ -120,11 +120,12 @@ void ct_init(hipStream_t s, const CtArgs &A, size_t flag_words)
 
 // The rank-th smallest key of a sample of CT_SAMPLES edges (one from each of
 // as many equal stretches of the input, at a mixed place): the threshold of
-// phase 0.  One workgroup, samples in registers, eight bits per step.
+// phase 0.  One workgroup, samples in registers, eight bits per step until
+// the bin holds one sample (the second or third step, unless weights repeat).
 __global__ __launch_bounds__(CE_NT) void k_ct_threshold(CtArgs A, uint32_t rank)
 {
     __shared__ uint32_t s_hist[256];
-    __shared__ uint32_t s_bin, s_rank;
+    __shared__ uint32_t s_bin, s_rank, s_num;
     constexpr int PER = CT_SAMPLES / CE_NT;
     uint64_t key[PER];
     const uint64_t m = (uint64_t)A.m;
@@ -136,13 +137,13 @@ __global__ __launch_bounds__(CE_NT) void k_ct_threshold(CtArgs A, uint32_t rank)
         x ^= x >> 15;
         x *= 0x2C1B3C6Du;
         x ^= x >> 12;
-        uint64_t e = lo + (hi > lo ? x % (hi - lo) : 0);
+        uint64_t e = lo + (((hi - lo) * (uint64_t)x) >> 32);
         if (e >= m) e = m - 1;
         key[q] = ((uint64_t)ct_wkey(A.w[e], A.wt) << 32) | e;
     }
     uint64_t pre = 0;
     uint32_t want = rank;
-    for (int sh = 56; sh >= 0; sh -= 8) {
+    for (int sh = 56;; sh -= 8) {
         if (threadIdx.x < 256) s_hist[threadIdx.x] = 0;
         __syncthreads();
 #pragma unroll
@@ -160,6 +161,7 @@ __global__ __launch_bounds__(CE_NT) void k_ct_threshold(CtArgs A, uint32_t rank)
                 if (want >= ex && want < ex + c[q]) {
                     s_bin = threadIdx.x * 4 + q;
                     s_rank = want - ex;
+                    s_num = c[q];
                 }
                 ex += c[q];
             }
@@ -167,9 +169,14 @@ __global__ __launch_bounds__(CE_NT) void k_ct_threshold(CtArgs A, uint32_t rank)
         __syncthreads();
         pre = (pre << 8) | s_bin;
         want = s_rank;
+        if (s_num == 1 || sh == 0) {
+#pragma unroll
+            for (int q = 0; q < PER; ++q)
+                if ((key[q] >> sh) == pre) A.cnt->ct.T = key[q];
+            return;
+        }
         __syncthreads();
     }
-    if (threadIdx.x == 0) A.cnt->ct.T = pre;
 }
 
 void ct_threshold(hipStream_t s, const CtArgs &A, int64_t light)
@@ -184,6 +191,21 @@ void ct_threshold(hipStream_t s, const CtArgs &A, int64_t light)
 // Every edge read once and checked; those up to the threshold (no loops) go
 // to the wave's segment.  A wave takes every W-th tile, so the segments are
 // even whatever the order of the input.
+
+// A wave's tile t of the input (indices past the end clamped).
+template <bool WEIGHTS>
+__device__ __forceinline__ void ct_load(const CtArgs &A, int64_t t, int lane, int2 (&uv)[4],
+                                        uint32_t (&wb)[4])
+{
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        int64_t e = t * CT_TILE + q * 64 + lane;
+        e = e < A.m ? e : A.m - 1;
+        uv[q] = A.edges[e];
+        if (WEIGHTS) wb[q] = A.w[e];
+    }
+}
+
 __global__ __launch_bounds__(CE_NT) void k_ct_select(CtArgs A)
 {
     __shared__ uint32_t s_cnt[CE_WV];
@@ -194,24 +216,28 @@ __global__ __launch_bounds__(CE_NT) void k_ct_select(CtArgs A)
     const uint32_t n = (uint32_t)A.n;
     CtEdge *seg = A.list + (size_t)wv * A.segcap;
     uint32_t out = 0, err = 0;
+    int2 uv[4];
+    uint32_t wb[4];
+    ct_load<true>(A, wv, lane, uv, wb);
     for (int64_t t = wv; t < tiles; t += A.W) {
-        int2 uv[4];
-        uint32_t wb[4];
+        int2 x[4];
+        uint32_t y[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            int64_t e = t * CT_TILE + q * 64 + lane;
-            e = e < A.m ? e : A.m - 1;
-            uv[q] = A.edges[e];
-            wb[q] = A.w[e];
+            x[q] = uv[q];
+            y[q] = wb[q];
         }
+        // the next tile's loads are in flight meanwhile
+        if (t + A.W < tiles) ct_load<true>(A, t + A.W, lane, uv, wb);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int64_t e = t * CT_TILE + q * 64 + lane;
-            const uint32_t a = (uint32_t)uv[q].x, b = (uint32_t)uv[q].y;
-            if (a >= n || b >= n) err |= ERR_ENDPOINT;
-            if (ct_nan(wb[q], A.wt)) err |= ERR_NAN;
-            const uint64_t key = ((uint64_t)ct_wkey(wb[q], A.wt) << 32) | (uint32_t)e;
-            const bool sel = e < A.m && !err && a != b && key <= T;
+            const uint32_t a = (uint32_t)x[q].x, b = (uint32_t)x[q].y;
+            uint32_t bad = a >= n || b >= n ? ERR_ENDPOINT : 0u;
+            if (ct_nan(y[q], A.wt)) bad |= ERR_NAN;
+            err |= bad;
+            const uint64_t key = ((uint64_t)ct_wkey(y[q], A.wt) << 32) | (uint32_t)e;
+            const bool sel = e < A.m && !bad && a != b && key <= T;
             const uint64_t mask = __ballot(sel);
             if (sel) seg[out + __popcll(mask & lanemask_lt())] = CtEdge{a, b, key};
             out += (uint32_t)__popcll(mask);
@@ -226,7 +252,7 @@ __global__ __launch_bounds__(CE_NT) void k_ct_select(CtArgs A)
     if (threadIdx.x == 0) {
         uint32_t t = 0;
         for (int i = 0; i < CE_WV; ++i) t += s_cnt[i];
-        if (t) atomicAdd(&A.cnt->ct.E[0][0], t);
+        if (t) atomicAdd(&A.cnt->ct.E0[0], t);
     }
 }
 
@@ -243,9 +269,11 @@ template <int U>
 __device__ __forceinline__ void ct_ends(const CtArgs &A, const uint64_t (&key)[U], int k, int tl,
                                         uint32_t (&a)[U], uint32_t (&b)[U])
 {
+    // every lane loads, from place 0 without an edge: loads behind a branch
+    // would wait for each other
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-        const int2 uv = key[q] != KEY_INF ? A.edges[(uint32_t)key[q]] : make_int2(0, 0);
+        const int2 uv = A.edges[key[q] != KEY_INF ? (uint32_t)key[q] : 0u];
         a[q] = (uint32_t)uv.x;
         b[q] = (uint32_t)uv.y;
     }
@@ -253,12 +281,16 @@ __device__ __forceinline__ void ct_ends(const CtArgs &A, const uint64_t (&key)[U
     for (int l = A.comp ? -1 : 0; l <= top; ++l) {
         if (l == top && k <= tl) break;
         const uint32_t *map = l < 0 ? A.comp : l < top ? ct_map(A, l) : A.cum;
+        uint32_t x[U], y[U];
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            if (key[q] != KEY_INF) {
-                a[q] = map[a[q]];
-                b[q] = map[b[q]];
-            }
+            x[q] = map[key[q] != KEY_INF ? a[q] : 0u];
+            y[q] = map[key[q] != KEY_INF ? b[q] : 0u];
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            a[q] = x[q];
+            b[q] = y[q];
         }
     }
 }
@@ -273,7 +305,7 @@ __device__ void ct_small_round(const CtArgs &A, int k, uint32_t L, uint32_t *s_h
     const uint64_t *r = A.r[k & 1];
     const uint32_t tl1 = load_relaxed_u32(&c->ct.tl[A.ph]);
     const int tl = tl1 ? (int)tl1 - 1 : k;
-    constexpr int IT = CT_SMALL / CE_NT;
+    constexpr int IT = (CT_SMALL + CE_NT - 1) / CE_NT;
     uint64_t key[IT];
 #pragma unroll
     for (int q = 0; q < IT; ++q) {
@@ -343,22 +375,107 @@ __device__ void ct_small_round(const CtArgs &A, int k, uint32_t L, uint32_t *s_h
     const uint32_t Ln = s_c[0];
     uint32_t *map = ct_map(A, k);
     for (uint32_t i = tid; i < L; i += CE_NT) map[i] = s_nid[s_h[i]];
-    // the first small round's vertices: what they are now
+    // the first small round's vertices: what they are now (a single vertex
+    // left has no edge: it is a finished tree)
     const uint32_t L0 = tl1 ? load_relaxed_u32(&c->ct.L[A.ph][tl]) : L;
     for (uint32_t i = tid; i < L0; i += CE_NT) {
         const uint32_t x = tl1 ? A.cum[i] : i;
-        if (!(x & CT_DEAD)) A.cum[i] = s_nid[s_h[x]];
+        if (x & CT_DEAD) continue;
+        const uint32_t v = s_nid[s_h[x]];
+        A.cum[i] = Ln == 1 && !(v & CT_DEAD) ? CT_DEAD | (dead0 + s_c[1]) : v;
     }
     uint64_t *rn = A.r[(k + 1) & 1];
     for (uint32_t i = tid; i < Ln; i += CE_NT) rn[i] = KEY_INF;
     if (tid == 0) {
         if (!tl1) c->ct.tl[A.ph] = (uint32_t)k + 1;
-        c->ct.L[A.ph][k + 1] = Ln;
-        c->ct.dead[A.ph] = dead0 + s_c[1];
+        c->ct.L[A.ph][k + 1] = Ln == 1 ? 0 : Ln;
+        c->ct.dead[A.ph] = dead0 + s_c[1] + (Ln == 1 ? 1 : 0);
         c->ct.hooks[A.ph][k] = s_c[2];
         c->ct.wl = wl0 + s_c[2];
         c->ct.done[A.ph][k] = 1;
-        if (Ln == 0) c->ct.phdone[A.ph] = 1;
+        if (Ln <= 1) c->ct.phdone[A.ph] = 1;
+    }
+}
+
+// The remaining rounds of a phase with L <= CT_PAIR vertices in one
+// workgroup, on the minimum keys of their pairs (one pair a thread).
+__device__ void ct_pair_rounds(const CtArgs &A, int k, uint32_t L, uint64_t *s_min, uint32_t *s_h,
+                               uint32_t *s_c)
+{
+    static_assert(CT_PAIR * CT_PAIR == CE_NT, "one pair a thread");
+    Counters *c = A.cnt;
+    const uint32_t tid = threadIdx.x, i = tid / CT_PAIR, j = tid % CT_PAIR;
+    uint32_t *s_comp = s_h + CT_PAIR, *s_id = s_comp + CT_PAIR;
+    const uint64_t key = load_relaxed_u64(A.mat + tid);
+    const uint32_t tl1 = load_relaxed_u32(&c->ct.tl[A.ph]);
+    const int tl = tl1 ? (int)tl1 - 1 : k;
+    const uint32_t dead0 = load_relaxed_u32(&c->ct.dead[A.ph]);
+    uint32_t wl = load_relaxed_u32(&c->ct.wl);
+    if (tid < CT_PAIR) s_comp[tid] = tid;
+    int rr = k;
+    for (;; ++rr) {
+        if (tid < CT_PAIR) s_min[tid] = KEY_INF;
+        if (tid == 0) s_c[0] = 0;
+        __syncthreads();
+        const uint32_t a = s_comp[i], b = s_comp[j];
+        const bool live = key != KEY_INF && a != b;
+        if (live) {
+            lower_lds(s_min, a, KEY_INF, key);
+            lower_lds(s_min, b, KEY_INF, key);
+        }
+        __syncthreads();
+        // keys are distinct: one pair has each minimum
+        if (live && s_min[a] == key) s_h[a] = b;
+        if (live && s_min[b] == key) s_h[b] = a;
+        __syncthreads();
+        if (tid < CT_PAIR) {  // lanes of one wave
+            const bool root = s_comp[tid] == tid && s_min[tid] != KEY_INF;
+            const uint32_t t = root ? s_h[tid] : tid;
+            const bool stay = root && tid < t && s_h[t] == tid;
+            const bool hook = root && !stay;
+            const uint64_t mk = __ballot(hook);
+            if (hook) {
+                const uint64_t x = s_min[tid];
+                A.flags[(uint32_t)x] = 1;
+                A.wlist[wl + __popcll(mk & lanemask_lt())] = (uint32_t)(x >> 32);
+            }
+            s_h[tid] = hook ? t : tid;
+            if (tid == 0) s_c[0] = (uint32_t)__popcll(mk);
+        }
+        __syncthreads();
+        const uint32_t hooks = s_c[0];
+        if (tid == 0 && rr < CT_ROUNDS - 1 && (hooks || rr == k)) {
+            c->ct.hooks[A.ph][rr] = hooks;
+            c->ct.done[A.ph][rr] = 1;
+        }
+        if (!hooks) break;
+        wl += hooks;
+        uint32_t x = 0;
+        if (tid < CT_PAIR) {
+            x = s_comp[tid];
+            while (s_h[x] != x) x = s_h[x];
+        }
+        __syncthreads();
+        if (tid < CT_PAIR) s_comp[tid] = x;
+    }
+    // every vertex is in a finished tree now: number them by their roots
+    if (tid < CT_PAIR) {
+        const uint64_t mk = __ballot(tid < L && s_comp[tid] == tid);
+        s_id[tid] = dead0 + (uint32_t)__popcll(mk & lanemask_lt());
+        if (tid == 0) s_c[1] = (uint32_t)__popcll(mk);
+    }
+    __syncthreads();
+    const uint32_t L0 = tl1 ? load_relaxed_u32(&c->ct.L[A.ph][tl]) : L;
+    for (uint32_t q = tid; q < L0; q += CE_NT) {
+        const uint32_t x = tl1 ? A.cum[q] : q;
+        if (!(x & CT_DEAD)) A.cum[q] = CT_DEAD | s_id[s_comp[x]];
+    }
+    if (tid == 0) {
+        if (!tl1) c->ct.tl[A.ph] = (uint32_t)k + 1;
+        c->ct.L[A.ph][k + 1] = 0;
+        c->ct.dead[A.ph] = dead0 + s_c[1];
+        c->ct.wl = wl;
+        c->ct.phdone[A.ph] = 1;
     }
 }
 
@@ -367,20 +484,37 @@ __device__ void ct_small_round(const CtArgs &A, int k, uint32_t L, uint32_t *s_h
 // Hot vertices of an edge pass (a star's centre, the largest tree of phase 0)
 // would take one atomic after another on one address, 3 ns each: the read
 // in front of an atomic sees what its XCD's L2 holds, not the latest value.
-// Each workgroup samples its edges, and the vertices it meets at least
-// CT_HOT_MIN times keep their minimum in LDS until the end of the pass.
-constexpr uint32_t CT_HOT = 512, CT_HOT_MIN = 16;
+// Each workgroup samples its edges, and the vertices with at least one in
+// CT_HOT_SHARE of the live ones (and CT_HOT_MIN of them) keep their minimum in
+// LDS until the end of the pass.
+constexpr uint32_t CT_HOT = 512, CT_HOT_MIN = 4, CT_HOT_SHARE = 64;
+constexpr uint32_t CT_READ = 320;  // edges of a wave above which minima are read first
 
 __device__ __forceinline__ uint32_t ct_hot_slot(uint32_t v) { return (v * 0x9E3779B1u) >> 23; }
 
-enum { CT_MIN_LDS, CT_MIN_HOT, CT_MIN_DEV };
+enum { CT_MIN_LDS, CT_MIN_HOT, CT_MIN_DEV, CT_MIN_PAIR };
+// Ends as they are (a phase's first round); through the last round's map,
+// the edges between different vertices kept in place; through the cumulative
+// map since the first small round, in LDS, the list left as it is (few edges
+// become internal from there on, and a pass then only reads).
+enum { CT_ENDS, CT_MAP, CT_CUM };
 
-// One wave over its segment: map the ends, lower the minima, keep the edges
-// between different vertices in place.  Returns how many it kept.
-template <bool FIRST, int MODE>
+// m <- min(m, the m of the lane CTRL names) where that lane has the same a.
+template <int CTRL>
+__device__ __forceinline__ void run_min(uint32_t a, uint64_t &m)
+{
+    const uint32_t oa = dpp_u32<CTRL>(a, ~a);
+    const uint64_t om = dpp_u64<CTRL>(m, KEY_INF);
+    if (oa == a && om < m) m = om;
+}
+
+// One wave over a segment: map the ends and lower the minima (read: behind a
+// read of them).  Returns the live edges.
+template <int ENDS, int MODE>
 __device__ __forceinline__ uint32_t ct_sweep(CtEdge *seg, uint32_t cnt,
-                                             const uint32_t *__restrict__ map, uint64_t *r,
-                                             uint64_t *s_r, const uint32_t *s_tag)
+                                             const uint32_t *__restrict__ map,
+                                             const uint16_t *s_cum, uint64_t *r, uint64_t *s_r,
+                                             const uint32_t *s_tag, bool read)
 {
     constexpr int U = 4;
     const int lane = __lane_id();
@@ -392,18 +526,27 @@ __device__ __forceinline__ uint32_t ct_sweep(CtEdge *seg, uint32_t cnt,
             const uint32_t j = j0 + q * 64 + lane;
             x[q] = seg[j < cnt ? j : cnt - 1];
         }
-        if (!FIRST) {
 #pragma unroll
-            for (int q = 0; q < U; ++q) {
+        for (int q = 0; q < U; ++q) {
+            if (ENDS == CT_MAP) {
                 x[q].a = map[x[q].a];
                 x[q].b = map[x[q].b];
+            } else if (ENDS == CT_CUM) {
+                x[q].a = s_cum[x[q].a];
+                x[q].b = s_cum[x[q].b];
             }
         }
         uint64_t ra[U], rb[U];
         uint32_t ha[U], hb[U];
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            if (MODE == CT_MIN_LDS) {
+            if (MODE == CT_MIN_PAIR) {
+                ha[q] = x[q].a != x[q].b ? min(x[q].a, x[q].b) * CT_PAIR + max(x[q].a, x[q].b) : 0u;
+                ra[q] = s_r[ha[q]];
+            } else if (ENDS == CT_CUM && x[q].a == x[q].b) {
+                ra[q] = rb[q] = 0;  // internal (a finished tree's number is no index)
+                ha[q] = hb[q] = CT_HOT;
+            } else if (MODE == CT_MIN_LDS) {
                 ra[q] = s_r[x[q].a];
                 rb[q] = s_r[x[q].b];
             } else {
@@ -413,14 +556,39 @@ __device__ __forceinline__ uint32_t ct_sweep(CtEdge *seg, uint32_t cnt,
                     if (s_tag[sa] == x[q].a) ha[q] = sa;
                     if (s_tag[sb] == x[q].b) hb[q] = sb;
                 }
-                ra[q] = ha[q] < CT_HOT ? s_r[ha[q]] : load_relaxed_u64(r + x[q].a);
-                rb[q] = hb[q] < CT_HOT ? s_r[hb[q]] : load_relaxed_u64(r + x[q].b);
+                ra[q] = ha[q] < CT_HOT ? s_r[ha[q]]
+                                       : read ? load_relaxed_u64(r + x[q].a) : KEY_INF;
+                rb[q] = hb[q] < CT_HOT ? s_r[hb[q]]
+                                       : read ? load_relaxed_u64(r + x[q].b) : KEY_INF;
             }
         }
 #pragma unroll
         for (int q = 0; q < U; ++q) {
             const bool live = j0 + q * 64 + lane < cnt && x[q].a != x[q].b;
-            if (live) {
+            if (ENDS == CT_ENDS && MODE != CT_MIN_LDS && MODE != CT_MIN_PAIR) {
+                // the list is in the input's order, where edges often come in
+                // runs of one first end: a run's minimum (within 16 lanes)
+                // leaves from its last lane alone (grid 256^3, 31M light
+                // edges: 361 us, 520 us with one atomic per end; 1.1M random
+                // edges on 10^6 vertices: 90 us either way)
+                const uint32_t a = live ? x[q].a : NONE32;
+                uint64_t m = live ? x[q].key : KEY_INF;
+                run_min<DPP_ROW_SHR1>(a, m);
+                run_min<DPP_ROW_SHR2>(a, m);
+                run_min<DPP_ROW_SHR4>(a, m);
+                run_min<DPP_ROW_SHR8>(a, m);
+                const bool last = dpp_u32<DPP_ROW_SHL1>(a, ~a) != a;
+                if (live) {
+                    if (last) {
+                        if (ha[q] < CT_HOT) lower_lds(s_r, ha[q], ra[q], m);
+                        else lower_dev(r, x[q].a, ra[q], m);
+                    }
+                    if (hb[q] < CT_HOT) lower_lds(s_r, hb[q], rb[q], x[q].key);
+                    else lower_dev(r, x[q].b, rb[q], x[q].key);
+                }
+            } else if (live && MODE == CT_MIN_PAIR) {
+                lower_lds(s_r, ha[q], ra[q], x[q].key);
+            } else if (live) {
                 if (MODE == CT_MIN_LDS) lower_lds(s_r, x[q].a, ra[q], x[q].key);
                 else if (ha[q] < CT_HOT) lower_lds(s_r, ha[q], ra[q], x[q].key);
                 else lower_dev(r, x[q].a, ra[q], x[q].key);
@@ -428,118 +596,186 @@ __device__ __forceinline__ uint32_t ct_sweep(CtEdge *seg, uint32_t cnt,
                 else if (hb[q] < CT_HOT) lower_lds(s_r, hb[q], rb[q], x[q].key);
                 else lower_dev(r, x[q].b, rb[q], x[q].key);
             }
-            if (!FIRST) {
-                const uint64_t mask = __ballot(live);
-                if (live) seg[out + __popcll(mask & lanemask_lt())] = x[q];
-                out += (uint32_t)__popcll(mask);
-            }
+            const uint64_t mask = __ballot(live);
+            if (ENDS == CT_MAP && live) seg[out + __popcll(mask & lanemask_lt())] = x[q];
+            out += (uint32_t)__popcll(mask);
         }
     }
     return out;
 }
 
-template <bool FIRST>
-__global__ __launch_bounds__(CE_NT) void k_ct_edges(CtArgs A, int k, int big)
+// The pass of one workgroup: minima into LDS where the round's vertices (or
+// their pairs) fit, lowering r (or the matrix) at the end; else into r
+// directly, hot vertices in LDS.
+template <int ENDS>
+__device__ __forceinline__ uint32_t ct_pass(const CtArgs &A, int k, uint32_t L,
+                                            const uint32_t *map, const uint16_t *s_cum,
+                                            uint64_t *r, uint64_t *s_r, uint32_t *s_tag,
+                                            uint32_t *s_num, uint32_t *s_c)
 {
-    __shared__ __align__(16) uint64_t s_r[CT_LDSR];  // also the targets of a small round
-    __shared__ uint32_t s_nid[CT_SMALL];             // also the hot vertices' tags and counts
+    const uint32_t tid = threadIdx.x, wv = blockIdx.x * CE_WV + (tid >> 6);
+    const int lane = __lane_id();
+    uint32_t live = 0;
+    // every wave over its segments, one sweep each
+#define CT_SEGMENTS(MODE, READ)                                                               \
+    for (uint32_t sg = wv; sg < A.W; sg += gridDim.x * CE_WV) {                               \
+        const uint32_t cnt = A.cw[sg];                                                        \
+        const uint32_t out = ct_sweep<ENDS, MODE>(A.list + (size_t)sg * A.segcap, cnt, map,   \
+                                                  s_cum, r, s_r, s_tag, READ);                \
+        if (ENDS == CT_MAP && lane == 0) A.cw[sg] = out;                                      \
+        live += out;                                                                          \
+    }
+    if (L <= CT_SMALL) {
+        const bool pair = L <= CT_PAIR;
+        const uint32_t cells = pair ? CT_PAIR * CT_PAIR : L;
+        uint64_t *dst = pair ? A.mat : r;
+        for (uint32_t i = tid; i < cells; i += CE_NT) s_r[i] = KEY_INF;
+        __syncthreads();
+        if (pair) {
+            CT_SEGMENTS(CT_MIN_PAIR, true)
+        } else {
+            CT_SEGMENTS(CT_MIN_LDS, true)
+        }
+        __syncthreads();
+        // behind a read only where every workgroup has most cells to lower
+        if (tid == 0) s_c[0] = 0;
+        __syncthreads();
+        if (lane == 0) atomicAdd(&s_c[0], live);
+        __syncthreads();
+        const bool read = s_c[0] > cells;
+        for (uint32_t i = tid; i < cells; i += CE_NT) {
+            const uint64_t v = s_r[i];
+            if (v != KEY_INF) lower_dev(dst, i, read ? load_relaxed_u64(dst + i) : KEY_INF, v);
+        }
+        __syncthreads();
+        return live;
+    }
+    for (uint32_t i = tid; i < CT_HOT; i += CE_NT) {
+        s_tag[i] = NONE32;
+        s_num[i] = 0;
+        s_r[i] = KEY_INF;
+    }
+    if (tid < 2) s_c[tid] = 0;
+    __syncthreads();
+    // the first edges of every wave are the sample
+    const uint32_t cnt0 = A.cw[wv];
+    uint32_t va = NONE32, vb = NONE32;
+    if ((uint32_t)lane < cnt0) {
+        const CtEdge *seg = A.list + (size_t)wv * A.segcap;
+        va = seg[lane].a;
+        vb = seg[lane].b;
+        if (ENDS == CT_MAP) {
+            va = map[va];
+            vb = map[vb];
+        } else if (ENDS == CT_CUM) {
+            va = s_cum[va];
+            vb = s_cum[vb];
+        }
+        if (va != vb) {
+            atomicAdd(&s_num[ct_hot_slot(va)], 1u);
+            atomicAdd(&s_num[ct_hot_slot(vb)], 1u);
+        }
+    }
+    const uint64_t lv = __ballot(va != vb);
+    if (lane == 0 && lv) atomicAdd(&s_c[1], (uint32_t)__popcll(lv));
+    __syncthreads();
+    const uint32_t hot = max(CT_HOT_MIN, s_c[1] / CT_HOT_SHARE);
+    if (va != vb) {
+        if (s_num[ct_hot_slot(va)] >= hot) {
+            s_tag[ct_hot_slot(va)] = va;
+            s_c[0] = 1;
+        }
+        if (s_num[ct_hot_slot(vb)] >= hot) {
+            s_tag[ct_hot_slot(vb)] = vb;
+            s_c[0] = 1;
+        }
+    }
+    __syncthreads();
+    // Whether minima are read before an atomic.  A wave with few edges sends
+    // them all at once, before any read could show a minimum, and reading
+    // lines that atomics change is slow (passes over 271 / 113 / 70 / 60 edges
+    // a wave, 10^6 edges on 10^6 vertices and less: 81 / 82 / 51 / 56 us with
+    // the read, 62 / 48 / 26 / 26 us without; over 472 edges a wave, phase 1
+    // of R-MAT s22: 150 us with it, 336 us without).
+    const bool read = cnt0 > CT_READ;
+    if (s_c[0]) {
+        CT_SEGMENTS(CT_MIN_HOT, read)
+        __syncthreads();
+        for (uint32_t i = tid; i < CT_HOT; i += CE_NT) {
+            const uint64_t v = s_r[i];
+            if (v != KEY_INF) lower_dev(r, s_tag[i], load_relaxed_u64(r + s_tag[i]), v);
+        }
+    } else {
+        CT_SEGMENTS(CT_MIN_DEV, read)
+    }
+#undef CT_SEGMENTS
+    return live;
+}
+
+// (two workgroups on a compute unit: at most 64 registers)
+template <bool FIRST>
+__global__ __launch_bounds__(CE_NT, 8) void k_ct_edges(CtArgs A, int k, int big)
+{
+    // minima of a small round; then its targets and numbers
+    __shared__ __align__(16) uint64_t s_r[CT_SMALL];
+    // the cumulative map of a small round, or a larger one's hot vertices
+    __shared__ __align__(16) uint16_t s_cum[CT_SMALL];
     __shared__ uint32_t s_cnt[CE_WV];
     __shared__ uint32_t s_c[4];
-    static_assert(sizeof(uint64_t) * CT_LDSR >= sizeof(uint32_t) * CT_SMALL, "targets alias minima");
+    static_assert(2 * (sizeof s_r + sizeof s_cum + 256) <= 160 << 10, "two workgroups a CU");
+    static_assert(sizeof s_cum >= 8 * CT_HOT, "tags and counts in the map's place");
     Counters *c = A.cnt;
     const uint32_t L = c->ct.L[A.ph][k];
     if (c->err || L == 0 || (L > CT_SMALL && !big)) return;
     if (k > 0 ? !c->ct.done[A.ph][k - 1] : (A.ph > 0 && !c->ct.phdone[A.ph - 1])) return;
     if (c->ct.done[A.ph][k]) return;
+    const uint32_t tl1 = c->ct.tl[A.ph];
     const int lane = __lane_id();
-    const uint32_t tid = threadIdx.x, wv = blockIdx.x * CE_WV + (tid >> 6);
+    const uint32_t tid = threadIdx.x;
     if (blockIdx.x == 0 && tid == 0) c->ct.ran[A.ph][k] = 1;
     uint64_t *r = A.r[k & 1];
-    const uint32_t *map = FIRST ? nullptr : ct_map(A, k - 1);
-    CtEdge *seg = A.list + (size_t)wv * A.segcap;
-    const uint32_t cnt = A.cw[wv];
-    const bool lds = L <= CT_LDSR;
-    uint32_t out = 0;
-    if (lds) {
-        for (uint32_t i = tid; i < L; i += CE_NT) s_r[i] = KEY_INF;
+    uint32_t *s_tag = reinterpret_cast<uint32_t *>(s_cum), *s_num = s_tag + CT_HOT;
+    uint32_t out;
+    if (FIRST) {
+        out = ct_pass<CT_ENDS>(A, k, L, nullptr, nullptr, r, s_r, s_tag, s_num, s_c);
+    } else if (tl1 && k >= (int)tl1) {
+        const uint32_t L0 = c->ct.L[A.ph][tl1 - 1];
+        for (uint32_t i = tid; i < L0; i += CE_NT) s_cum[i] = (uint16_t)min(A.cum[i], 0xFFFFu);
         __syncthreads();
-        out = ct_sweep<FIRST, CT_MIN_LDS>(seg, cnt, map, r, s_r, nullptr);
-        __syncthreads();
-        for (uint32_t i = tid; i < L; i += CE_NT) {
-            const uint64_t v = s_r[i];
-            if (v != KEY_INF) lower_dev(r, i, load_relaxed_u64(r + i), v);
-        }
+        out = ct_pass<CT_CUM>(A, k, L, nullptr, s_cum, r, s_r, s_tag, s_num, s_c);
     } else {
-        uint32_t *s_tag = s_nid, *s_num = s_nid + CT_HOT;
-        for (uint32_t i = tid; i < CT_HOT; i += CE_NT) {
-            s_tag[i] = NONE32;
-            s_num[i] = 0;
-            s_r[i] = KEY_INF;
-        }
-        if (tid == 0) s_c[0] = 0;
-        __syncthreads();
-        uint32_t va = NONE32, vb = NONE32;
-        if ((uint32_t)lane < cnt) {
-            va = seg[lane].a;
-            vb = seg[lane].b;
-            if (!FIRST) {
-                va = map[va];
-                vb = map[vb];
-            }
-            if (va != vb) {
-                atomicAdd(&s_num[ct_hot_slot(va)], 1u);
-                atomicAdd(&s_num[ct_hot_slot(vb)], 1u);
-            }
-        }
-        __syncthreads();
-        if (va != vb) {
-            if (s_num[ct_hot_slot(va)] >= CT_HOT_MIN) {
-                s_tag[ct_hot_slot(va)] = va;
-                s_c[0] = 1;
-            }
-            if (s_num[ct_hot_slot(vb)] >= CT_HOT_MIN) {
-                s_tag[ct_hot_slot(vb)] = vb;
-                s_c[0] = 1;
-            }
-        }
-        __syncthreads();
-        if (s_c[0]) {
-            out = ct_sweep<FIRST, CT_MIN_HOT>(seg, cnt, map, r, s_r, s_tag);
-            __syncthreads();
-            for (uint32_t i = tid; i < CT_HOT; i += CE_NT) {
-                const uint64_t v = s_r[i];
-                if (v != KEY_INF) lower_dev(r, s_tag[i], load_relaxed_u64(r + s_tag[i]), v);
-            }
-        } else {
-            out = ct_sweep<FIRST, CT_MIN_DEV>(seg, cnt, map, r, s_r, s_tag);
-        }
+        out = ct_pass<CT_MAP>(A, k, L, ct_map(A, k - 1), nullptr, r, s_r, s_tag, s_num, s_c);
     }
-    if (!FIRST) {
-        if (lane == 0) {
-            A.cw[wv] = out;
-            s_cnt[tid >> 6] = out;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            uint32_t t = 0;
-            for (int i = 0; i < CE_WV; ++i) t += s_cnt[i];
-            if (t) atomicAdd(&c->ct.E[A.ph][k], t);
+    if (lane == 0) s_cnt[tid >> 6] = out;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (tid < 64) {
+        const uint32_t t = wave_sum(tid < CE_WV ? s_cnt[tid] : 0u);
+        // live edges and the workgroups through, in one atomic; its answer is
+        // waited for (13 ns each on one address) only where it is needed
+        unsigned long long *tick = (unsigned long long *)&c->ct.tick[A.ph][k];
+        const unsigned long long add = ((unsigned long long)t << 16) | 1u;
+        if (L > CT_SMALL) {
+            if (tid == 0) atomicAdd(tick, add);
+        } else if (tid == 0) {
+            s_c[1] = (uint32_t)(atomicAdd(tick, add) & 0xFFFFu);
         }
     }
     if (L > CT_SMALL) return;
-    // The last workgroup of a small round finishes it.  It reads only r,
-    // which is written by device-scope atomics alone: each wave waits for
-    // its own before the ticket (a release fence would write back the whole
-    // L2 in every workgroup, 70-220 us a pass), and the last one drops what
-    // its L2 holds of r before reading.
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (tid == 0) s_c[1] = atomicAdd(&c->ct.tick[A.ph][k], 1u);
+    // The last workgroup of a small round finishes it.  It reads only r (or
+    // the matrix), which is written by device-scope atomics alone: each wave
+    // waits for its own before the ticket (a release fence would write back
+    // the whole L2 in every workgroup, 70-220 us a pass), and the last one
+    // drops what its L2 holds of r before reading.
     __syncthreads();
     if (s_c[1] != gridDim.x - 1) return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     __syncthreads();
-    ct_small_round(A, k, L, reinterpret_cast<uint32_t *>(s_r), s_nid, s_c);
+    if (L <= CT_PAIR)
+        ct_pair_rounds(A, k, L, s_r, reinterpret_cast<uint32_t *>(s_cum), s_c);
+    else
+        ct_small_round(A, k, L, reinterpret_cast<uint32_t *>(s_r),
+                       reinterpret_cast<uint32_t *>(s_r) + CT_SMALL, s_c);
 }
 
 // ------------------------------------------------ rounds of many vertices --
@@ -551,85 +787,62 @@ __device__ __forceinline__ bool ct_big_round(const CtArgs &A, int k, uint32_t L)
     return L > CT_SMALL && !c->err && c->ct.ran[A.ph][k];
 }
 
-__global__ __launch_bounds__(256) void k_ct_hook(CtArgs A, int k)
-{
-    const uint32_t L = A.cnt->ct.L[A.ph][k];
-    if (!ct_big_round(A, k, L) || A.cnt->ct.done[A.ph][k]) return;
-    const uint64_t *r = A.r[k & 1];
-    constexpr int U = 4;
-    for (uint64_t base = (uint64_t)blockIdx.x * (256 * U); base < L;
-         base += (uint64_t)gridDim.x * (256 * U)) {
-        uint64_t key[U];
-        uint32_t a[U], b[U];
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const uint64_t i = base + q * 256 + threadIdx.x;
-            key[q] = i < L ? r[i] : KEY_INF;
-        }
-        ct_ends<U>(A, key, k, k, a, b);
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const uint64_t i = base + q * 256 + threadIdx.x;
-            if (i < L) A.h[i] = key[q] == KEY_INF ? (uint32_t)i : (a[q] == (uint32_t)i ? b[q] : a[q]);
-        }
-    }
-}
-
-// Tie break, forest flags, weights, and the numbers of the vertices that
-// stay (dense from 0) and of the finished trees.  A tile is IT x 512
-// consecutive vertices; the numbers keep the vertices' order inside it
-// (item-major, then wave, then lane) and each tile takes its range with one
-// atomic, so neighbours stay neighbours.
+// Hook, tie break, forest flags, weights, and the numbers of the vertices
+// that stay (dense from 0) and of the finished trees.  Two vertices hooked
+// onto each other exactly when they have the same minimum (keys are
+// distinct), so the tie break reads the target's minimum instead of waiting
+// for its hook.  A tile is IT x 512 consecutive vertices; the numbers keep
+// the vertices' order inside it (item-major, then wave, then lane) and each
+// tile takes its range with one atomic, so neighbours stay neighbours.
 constexpr int TIE_NT = 512;
 
 template <int IT, int WT>
-__global__ __launch_bounds__(TIE_NT) void k_ct_tie(CtArgs A, int k)
+__device__ __forceinline__ uint32_t ct_hook_tiles(const CtArgs &A, int k, uint32_t L,
+                                                  uint32_t (*s_off)[64], uint32_t *s_base,
+                                                  WSum &ws)
 {
     constexpr int NW = TIE_NT / 64;
-    static_assert(IT * NW <= 128 && (IT * NW) % 2 == 0, "two counts a lane");
-    __shared__ uint32_t s_off[2][128];
-    __shared__ uint32_t s_base[2];
-    __shared__ int64_t s_sum[NW * (ACC_DIGITS + 1)];
-    __shared__ int64_t s_tot[WS_WORDS];
-    __shared__ uint32_t s_hk[NW];
+    static_assert(IT * NW <= 64, "one count a lane");
     Counters *c = A.cnt;
-    const uint32_t L = c->ct.L[A.ph][k];
-    if (!ct_big_round(A, k, L) || c->ct.done[A.ph][k]) return;
     const uint64_t *r = A.r[k & 1];
     uint32_t *map = ct_map(A, k);
     const uint32_t w = threadIdx.x >> 6;
     const uint64_t lt = lanemask_lt();
     const uint32_t tiles = (uint32_t)(((uint64_t)L + IT * TIE_NT - 1) / (IT * TIE_NT));
-    WSum ws;
     uint32_t hooks = 0;
     for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
         const uint64_t base = (uint64_t)tile * (IT * TIE_NT) + threadIdx.x;
-        uint32_t t[IT], back[IT];
         uint64_t key[IT];
+        uint32_t a[IT], b[IT];
 #pragma unroll
         for (int q = 0; q < IT; ++q) {
             const uint64_t i = base + q * TIE_NT;
-            t[q] = i < L ? load_relaxed_u32(A.h + i) : NONE32;
             key[q] = i < L ? r[i] : KEY_INF;
         }
+        ct_ends<IT>(A, key, k, k, a, b);
+        uint64_t kt[IT];
 #pragma unroll
-        for (int q = 0; q < IT; ++q)
-            back[q] = key[q] != KEY_INF ? load_relaxed_u32(A.h + t[q]) : NONE32;
+        for (int q = 0; q < IT; ++q) {
+            a[q] = a[q] == (uint32_t)(base + q * TIE_NT) ? b[q] : a[q];  // the target
+            kt[q] = r[key[q] != KEY_INF ? a[q] : 0u];
+        }
         uint32_t stay = 0, dead = 0;
 #pragma unroll
         for (int q = 0; q < IT; ++q) {
             const uint64_t i = base + q * TIE_NT;
             if (i >= L) continue;
+            uint32_t t = (uint32_t)i;
             if (key[q] == KEY_INF) {
                 dead |= 1u << q;
-            } else if (back[q] == (uint32_t)i && (uint32_t)i < t[q]) {
-                store_relaxed_u32(A.h + i, (uint32_t)i);
+            } else if (kt[q] == key[q] && (uint32_t)i < a[q]) {
                 stay |= 1u << q;
             } else {
+                t = a[q];
                 A.flags[(uint32_t)key[q]] = 1;
                 wsum_add<WT>(ws, (uint32_t)(key[q] >> 32));
                 ++hooks;
             }
+            A.h[i] = t;
         }
 #pragma unroll
         for (int q = 0; q < IT; ++q) {
@@ -642,28 +855,45 @@ __global__ __launch_bounds__(TIE_NT) void k_ct_tie(CtArgs A, int k)
         __syncthreads();
         if (w < 2) {
             // exclusive scan of one list's IT x NW counts by one wave
-            const uint32_t l2 = 2 * __lane_id();
-            const uint32_t c0 = l2 < IT * NW ? s_off[w][l2] : 0u;
-            const uint32_t c1 = l2 + 1 < IT * NW ? s_off[w][l2 + 1] : 0u;
-            const uint32_t inc = wave_incl_sum(c0 + c1);
-            if (l2 < IT * NW) {
-                s_off[w][l2] = inc - c0 - c1;
-                s_off[w][l2 + 1] = inc - c1;
-            }
-            if (__lane_id() == 63)
+            const uint32_t l = __lane_id();
+            const uint32_t c0 = l < IT * NW ? s_off[w][l] : 0u;
+            const uint32_t inc = wave_incl_sum(c0);
+            s_off[w][l] = inc - c0;
+            if (l == 63)
                 s_base[w] = inc ? atomicAdd(w ? &c->ct.dead[A.ph] : &c->ct.L[A.ph][k + 1], inc) : 0u;
         }
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < IT; ++q) {
             const uint64_t i = base + q * TIE_NT;
-            const bool a = (stay >> q) & 1u, b = (dead >> q) & 1u;
-            const uint64_t ms = __ballot(a), md = __ballot(b);
-            if (a) map[i] = s_base[0] + s_off[0][q * NW + w] + (uint32_t)__popcll(ms & lt);
-            if (b) map[i] = CT_DEAD | (s_base[1] + s_off[1][q * NW + w] + (uint32_t)__popcll(md & lt));
+            const bool st = (stay >> q) & 1u, de = (dead >> q) & 1u;
+            const uint64_t ms = __ballot(st), md = __ballot(de);
+            if (st) map[i] = s_base[0] + s_off[0][q * NW + w] + (uint32_t)__popcll(ms & lt);
+            if (de) map[i] = CT_DEAD | (s_base[1] + s_off[1][q * NW + w] + (uint32_t)__popcll(md & lt));
         }
         __syncthreads();
     }
+    return hooks;
+}
+
+template <int WT>
+__global__ __launch_bounds__(TIE_NT) void k_ct_hook(CtArgs A, int k)
+{
+    constexpr int NW = TIE_NT / 64;
+    __shared__ uint32_t s_off[2][64];
+    __shared__ uint32_t s_base[2];
+    __shared__ int64_t s_sum[NW * (ACC_DIGITS + 1)];
+    __shared__ int64_t s_tot[WS_WORDS];
+    __shared__ uint32_t s_hk[NW];
+    Counters *c = A.cnt;
+    const uint32_t L = c->ct.L[A.ph][k];
+    if (!ct_big_round(A, k, L) || c->ct.done[A.ph][k]) return;
+    const uint32_t w = threadIdx.x >> 6;
+    WSum ws;
+    // eight vertices a thread while there are many (one atomic, 13 ns on one
+    // address, per 4096), two with fewer, to keep the compute units busy
+    uint32_t hooks = L >= (1u << 20) ? ct_hook_tiles<8, WT>(A, k, L, s_off, s_base, ws)
+                                     : ct_hook_tiles<2, WT>(A, k, L, s_off, s_base, ws);
     // this workgroup's weights into its slot, its hooks into the round's count
     hooks = wave_sum(hooks);
     if (__lane_id() == 0) s_hk[w] = hooks;
@@ -721,22 +951,13 @@ __global__ __launch_bounds__(256) void k_ct_chase(CtArgs A, int k)
 
 void ct_round(hipStream_t s, const CtArgs &A, int k, bool big, uint32_t bound)
 {
-    const unsigned g = A.W / CE_WV;
+    const unsigned g = (A.ph ? A.W : A.pass_waves) / CE_WV;
     if (k == 0) k_ct_edges<true><<<g, CE_NT, 0, s>>>(A, k, big);
     else k_ct_edges<false><<<g, CE_NT, 0, s>>>(A, k, big);
     if (!big || bound <= CT_SMALL) return;
-    k_ct_hook<<<grid_for(bound, 1024, 4096), 256, 0, s>>>(A, k);
-    // 16 vertices a thread while there are many (one atomic per 8192), four
-    // with fewer, to keep the compute units busy
-    if (bound >= (1u << 22)) {
-        const unsigned t = grid_for(bound, 16 * TIE_NT, CT_WSLOTS);
-        if (A.wt == MSF_W_F32) k_ct_tie<16, MSF_W_F32><<<t, TIE_NT, 0, s>>>(A, k);
-        else k_ct_tie<16, MSF_W_U32><<<t, TIE_NT, 0, s>>>(A, k);
-    } else {
-        const unsigned t = grid_for(bound, 4 * TIE_NT, CT_WSLOTS);
-        if (A.wt == MSF_W_F32) k_ct_tie<4, MSF_W_F32><<<t, TIE_NT, 0, s>>>(A, k);
-        else k_ct_tie<4, MSF_W_U32><<<t, TIE_NT, 0, s>>>(A, k);
-    }
+    const unsigned t = grid_for(bound, 2 * TIE_NT, CT_WSLOTS);
+    if (A.wt == MSF_W_F32) k_ct_hook<MSF_W_F32><<<t, TIE_NT, 0, s>>>(A, k);
+    else k_ct_hook<MSF_W_U32><<<t, TIE_NT, 0, s>>>(A, k);
     k_ct_chase<<<grid_for(bound, 256, 8192), 256, 0, s>>>(A, k);
 }
 
@@ -758,17 +979,20 @@ __global__ __launch_bounds__(256) void k_ct_compose(CtArgs A, uint32_t *comp)
         comp[v] = x & ~CT_DEAD;
         A.r[0][v] = KEY_INF;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) c->ct.L[1][0] = c->ct.dead[0];
+    if (blockIdx.x == 0) {
+        for (uint32_t i = threadIdx.x; i < CT_PAIR * CT_PAIR; i += 256) A.mat[i] = KEY_INF;
+        if (threadIdx.x == 0) c->ct.L[1][0] = c->ct.dead[0];
+    }
 }
 
-// The tree that most of 1024 sampled edge ends lie in.
-__global__ __launch_bounds__(CE_NT) void k_ct_giant(CtArgs A, const uint32_t *__restrict__ comp)
+// The tree that most of 256 sampled edge ends lie in.
+__global__ __launch_bounds__(256) void k_ct_giant(CtArgs A, const uint32_t *__restrict__ comp)
 {
-    __shared__ __align__(16) uint32_t s_v[CE_NT];
+    __shared__ __align__(16) uint32_t s_v[256];
     __shared__ unsigned long long s_best;
     Counters *c = A.cnt;
     if (c->err || !c->ct.phdone[0] || c->ct.ran[1][0]) return;
-    const int64_t e = (int64_t)((uint64_t)A.m * threadIdx.x / CE_NT);
+    const int64_t e = (int64_t)((uint64_t)A.m * threadIdx.x / 256);
     const int2 uv = A.edges[e];
     const uint32_t v = comp[(threadIdx.x & 1) ? uv.x : uv.y];
     s_v[threadIdx.x] = v;
@@ -776,8 +1000,8 @@ __global__ __launch_bounds__(CE_NT) void k_ct_giant(CtArgs A, const uint32_t *__
     __syncthreads();
     uint32_t same = 0;
     const uint4 *s_v4 = reinterpret_cast<const uint4 *>(s_v);
-#pragma unroll 8
-    for (int i = 0; i < CE_NT / 4; ++i) {
+#pragma unroll 16
+    for (int i = 0; i < 64; ++i) {
         const uint4 x = s_v4[i];
         same += (x.x == v) + (x.y == v) + (x.z == v) + (x.w == v);
     }
@@ -816,15 +1040,19 @@ __global__ __launch_bounds__(CE_NT) void k_ct_between(CtArgs A, const uint32_t *
     const int64_t tiles = (A.m + CT_TILE - 1) / CT_TILE;
     CtEdge *seg = A.list + (size_t)wv * A.segcap;
     uint32_t out = 0;
+    int2 nx[4];
+    uint32_t none[4];
+    ct_load<false>(A, wv, lane, nx, none);
     for (int64_t t = wv; t < tiles; t += A.W) {
         int2 uv[4];
         bool go[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int64_t e = t * CT_TILE + q * 64 + lane;
-            uv[q] = A.edges[e < A.m ? e : A.m - 1];
-            go[q] = e < A.m;
+            uv[q] = nx[q];
+            go[q] = t * CT_TILE + q * 64 + lane < A.m;
         }
+        // the next tile's loads are in flight meanwhile
+        if (t + A.W < tiles) ct_load<false>(A, t + A.W, lane, nx, none);
         if (BITS) {
             uint32_t ba[4], bb[4];
 #pragma unroll
@@ -866,7 +1094,7 @@ __global__ __launch_bounds__(CE_NT) void k_ct_between(CtArgs A, const uint32_t *
     if (threadIdx.x == 0) {
         uint32_t t = 0;
         for (int i = 0; i < CE_WV; ++i) t += s_cnt[i];
-        if (t) atomicAdd(&c->ct.E[1][0], t);
+        if (t) atomicAdd(&c->ct.E0[1], t);
     }
 }
 
@@ -876,7 +1104,7 @@ void ct_between(hipStream_t s, const CtArgs &A, uint32_t *comp, uint32_t *bits)
     // a table of 2^20 trees (4 MB) still fits an L2: 205 G lookups/s against
     // 76 at 2^22, where the bits give 259 (64M random lookups)
     if (A.n > (1 << 20)) {
-        k_ct_giant<<<1, CE_NT, 0, s>>>(A, comp);
+        k_ct_giant<<<1, 256, 0, s>>>(A, comp);
         k_ct_bits<<<grid_for(((size_t)A.n + 63) / 64, 4, 4096), 256, 0, s>>>(
             A, comp, reinterpret_cast<uint64_t *>(bits));
         k_ct_between<true><<<A.W / CE_WV, CE_NT, 0, s>>>(A, comp, bits);

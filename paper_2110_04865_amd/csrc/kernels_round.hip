@@ -13,6 +13,8 @@
 // (up to m/8192 tiles) are counted, scanned and written in separate passes
 // instead: a long chain of tickets and look-backs costs more there than a
 // second read of the flags.
+#include <algorithm>
+
 #include "exact_sum.hpp"
 #include "msf_internal.hpp"
 #include "wave.hpp"
@@ -614,23 +616,60 @@ __device__ __forceinline__ uint32_t count_flags(const uint32_t (&fw)[OUT_IT / 4]
     return c;
 }
 
-// Pass 1 (tile = workgroup): the tile's forest-edge count.
+// Pass 1: the tiles' forest-edge counts; the last workgroup to finish scans
+// them into the tiles' offsets (a launch of its own for each step of a scan
+// costs more than the steps).  The counts go out as device-scope stores,
+// waited for before the ticket, and the last workgroup drops what its L2
+// holds before reading them.  At most OUT_WG workgroups: tickets on one
+// address cost 13 ns each.
+constexpr unsigned OUT_WG = 512;
+
 __global__ __launch_bounds__(OUT_NT) void k_output_count(const uint8_t *__restrict__ flags,
-                                                        int64_t m,
-                                                        uint32_t *__restrict__ tile_cnt,
-                                                        const uint32_t *go)
+                                                        int64_t m, uint32_t ntiles,
+                                                        uint32_t *tile_cnt,
+                                                        uint32_t *__restrict__ tile_off,
+                                                        Counters *cnt, const uint32_t *go)
 {
     if (go && !*go) return;
-    __shared__ uint64_t s_lds[OUT_NT / 64 + 1];
-    const uint32_t tile = blockIdx.x;
-    const int64_t base = (int64_t)tile * OUT_TILE + (int64_t)threadIdx.x * OUT_IT;
-    uint32_t fw[OUT_IT / 4];
-    load_flags(flags, m, base, fw);
-    const uint64_t tot = block_sum<OUT_NT>((uint64_t)count_flags(fw), s_lds);
-    if (threadIdx.x == 0) tile_cnt[tile] = (uint32_t)tot;
+    __shared__ uint32_t s_lds[OUT_NT / 64 + 1];
+    __shared__ uint32_t s_last;
+    for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        const int64_t base = (int64_t)tile * OUT_TILE + (int64_t)threadIdx.x * OUT_IT;
+        uint32_t fw[OUT_IT / 4];
+        load_flags(flags, m, base, fw);
+        const uint32_t tot = block_sum<OUT_NT>(count_flags(fw), s_lds);
+        if (threadIdx.x == 0) store_relaxed_u32(tile_cnt + tile, tot);
+    }
+    if (threadIdx.x == 0) {
+        __builtin_amdgcn_s_waitcnt(0);
+        s_last = atomicAdd(&cnt->oticket, 1u) == gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    constexpr int IT = 8;
+    uint32_t run = 0;
+    for (uint32_t b0 = 0; b0 < ntiles; b0 += OUT_NT * IT) {
+        const uint32_t i0 = b0 + threadIdx.x * IT;
+        uint32_t v[IT], sum = 0;
+#pragma unroll
+        for (int k = 0; k < IT; ++k) v[k] = i0 + k < ntiles ? load_relaxed_u32(tile_cnt + i0 + k) : 0u;
+#pragma unroll
+        for (int k = 0; k < IT; ++k) sum += v[k];
+        uint32_t all;
+        uint32_t at = run + block_excl_sum<OUT_NT>(sum, s_lds, &all);
+#pragma unroll
+        for (int k = 0; k < IT; ++k) {
+            if (i0 + k < ntiles) tile_off[i0 + k] = at;
+            at += v[k];
+        }
+        run += all;
+    }
+    if (threadIdx.x == 0) cnt->count = run;
 }
 
-// Pass 2: the tile's ids, ascending, from its scanned offset.
+// Pass 2: the tile's ids, ascending, from its offset (through LDS, so that
+// they leave in whole cache lines).
 __global__ __launch_bounds__(OUT_NT) void k_output_ids(const uint8_t *__restrict__ flags,
                                                       int64_t m,
                                                       const uint32_t *__restrict__ tile_off,
@@ -639,19 +678,23 @@ __global__ __launch_bounds__(OUT_NT) void k_output_ids(const uint8_t *__restrict
 {
     if (go && !*go) return;
     __shared__ uint32_t s_lds[OUT_NT / 64 + 1];
+    __shared__ int32_t s_ids[OUT_TILE];
     const uint32_t tile = blockIdx.x;
     const int64_t base = (int64_t)tile * OUT_TILE + (int64_t)threadIdx.x * OUT_IT;
     uint32_t fw[OUT_IT / 4];
     load_flags(flags, m, base, fw);
     const uint32_t c = count_flags(fw);
     uint32_t tot;
-    uint32_t pos = tile_off[tile] + block_excl_sum<OUT_NT>(c, s_lds, &tot);
+    uint32_t pos = block_excl_sum<OUT_NT>(c, s_lds, &tot);
     if (c) {
-        for (int k = 0; k < OUT_IT; ++k) {
-            if (!((fw[k >> 2] >> (8 * (k & 3))) & 0xFFu)) continue;
-            ids[pos++] = (int32_t)(base + k);
-        }
+#pragma unroll
+        for (int q = 0; q < OUT_IT / 4; ++q)
+            for (uint32_t bits = fw[q]; bits; bits &= bits - 1)
+                s_ids[pos++] = (int32_t)(base + 4 * q + (__builtin_ctz(bits) >> 3));
     }
+    __syncthreads();
+    int32_t *out = ids + tile_off[tile];
+    for (uint32_t i = threadIdx.x; i < tot; i += OUT_NT) out[i] = s_ids[i];
 }
 
 // Round the exact forest weight once (one thread).
@@ -682,11 +725,11 @@ msf_status launch_output(Ctx *c, const uint8_t *in_forest, int64_t m, const void
     if (ntiles == 0) return MSF_OK;
     hipStream_t s = c->stream;
     (void)w;
-    // per-tile counts, then their exclusive scan
+    // per-tile counts and their exclusive scan
     uint32_t *tcnt = reinterpret_cast<uint32_t *>(part);
     uint32_t *toff = tcnt + ntiles;
-    k_output_count<<<(unsigned)ntiles, OUT_NT, 0, s>>>(in_forest, m, tcnt, go);
-    MSF_TRY(scan_u32(c, tcnt, toff, ntiles, &c->dcnt->count));
+    k_output_count<<<(unsigned)std::min<int64_t>(ntiles, OUT_WG), OUT_NT, 0, s>>>(
+        in_forest, m, (uint32_t)ntiles, tcnt, toff, c->dcnt, go);
     k_output_ids<<<(unsigned)ntiles, OUT_NT, 0, s>>>(in_forest, m, toff, ids, go);
     if (!go) k_total<<<1, 64, 0, s>>>(c->dcnt, (int)wt);
     MSF_HIP(hipGetLastError());

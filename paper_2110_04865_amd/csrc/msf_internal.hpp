@@ -143,21 +143,23 @@ struct Counters {
     uint32_t grounds;
     uint32_t gpad;
     uint32_t ghist[64];
+    uint32_t oticket;       // output: workgroups through the count
+    uint32_t opad;
     uint64_t long_entries;  // stored entries in rows of at least WAVE_ROW entries
     // rounds over a contracted edge list (kernels_contract.hip), per phase
     struct {
+        uint64_t tick[2][CT_ROUNDS];   // live edges << 16 | workgroups through the edge pass
         uint32_t L[2][CT_ROUNDS];      // vertices at the start of a round
-        uint32_t E[2][CT_ROUNDS];      // live edges of a round
         uint32_t hooks[2][CT_ROUNDS];  // kept hooks
         uint32_t ran[2][CT_ROUNDS];    // the edge pass ran
         uint32_t done[2][CT_ROUNDS];   // the round is complete
-        uint32_t tick[2][CT_ROUNDS];   // workgroups through the edge pass
         uint32_t dead[2];              // finished trees
         uint32_t tl[2];                // 1 + first round finished by one workgroup
         uint32_t phdone[2];            // the phase is complete
         uint32_t wl;                   // weight keys listed by those rounds
         uint32_t giant;                // the tree most sampled edges lie in
         uint32_t fin;                  // every phase complete, total known
+        uint32_t E0[2];                // edges on a phase's list
         uint32_t pad;
         uint64_t T;                    // phase 0 takes keys up to this one
     } ct;
@@ -249,6 +251,7 @@ struct SolveState {
     bool two_phase = false;   // contracted edge list: light edges first
     size_t ct_words = 0;      // its buffers: words of the flags
     uint32_t ct_W = 0;        // its list segments
+    uint32_t ct_pass = 0;     // waves of its edge passes
     int ri = 0, ai = 0, rounds = 0;
     int sweep_events = 0;     // rounds whose sweep start/end events were recorded
     double live_frac = 1.0;

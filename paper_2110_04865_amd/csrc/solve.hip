@@ -168,13 +168,16 @@ static bool contract_eligible(const Ctx *c, int32_t n, int64_t m)
     return defaults && c->small_m > 0 && !small_eligible(c, n, m);
 }
 
-// Edges of phase 0: n ln(4 m / n) / 2 of the lightest.  With f n random
+// Edges of phase 0: 0.4 n ln(4 m / n) of the lightest.  With f n random
 // edges a fraction of about 2 exp(-2 f) of the rest still joins different
-// trees (Erdos-Renyi), so this balances the edges of the two phases; on
-// R-MAT and grids the two are within a factor of two of each other there.
+// trees (Erdos-Renyi), so n ln(4 m / n) / 2 balances the edges of the two
+// phases; a fifth fewer is best, since an edge costs more in phase 0, where
+// its ends are the graph's vertices (factor 0.3 / 0.4 / 0.5 / 0.6: R-MAT s22
+// 2.16 / 2.23 / 2.27 / 2.29 ms, grid 256^3 5.13 / 3.68 / 3.82 / 4.27 ms: a
+// grid's light edges stop forming one large tree below about 0.9 n).
 static int64_t contract_light(int32_t n, int64_t m)
 {
-    const double f = 0.5 * std::log(std::max(1.0, 4.0 * (double)m / (double)n));
+    const double f = 0.4 * std::log(std::max(1.0, 4.0 * (double)m / (double)n));
     return std::max<int64_t>(1, (int64_t)(f * (double)n));
 }
 
@@ -191,7 +194,7 @@ static msf_status contract_args(Ctx *c, CtArgs *A)
         {WS_KEY, sizeof(CtEdge) * cap},  {WS_WLIVE, 4 * (size_t)S.ct_W},
         {WS_R, 8 * nn},                  {WS_HEDGE, 8 * (nn / 2 + 64)},
         {WS_H, 4 * nn},                  {WS_RL, 4 * nn},
-        {WS_RL2, 4 * ct_maps_words(S.n)}, {WS_HWK, 4 * 3 * CT_SMALL},
+        {WS_RL2, 4 * ct_maps_words(S.n)}, {WS_HWK, 4 * 3 * CT_SMALL + 8 * CT_PAIR * CT_PAIR},
         {WS_FLAGS, 4 * S.ct_words},      {WS_PART, ct_wpart_bytes() + output_part_bytes(S.m)},
         {WS_P, 4 * nn},                  {WS_STATUS, 8 * ((nn + 63) / 64)},
     };
@@ -204,6 +207,7 @@ static msf_status contract_args(Ctx *c, CtArgs *A)
     A->list = (CtEdge *)v[0];
     A->cw = (uint32_t *)v[1];
     A->W = S.ct_W;
+    A->pass_waves = S.ct_pass;
     A->segcap = (uint32_t)ct_segcap(S.m, S.ct_W);
     A->r[0] = (uint64_t *)v[2];
     A->r[1] = (uint64_t *)v[3];
@@ -212,6 +216,7 @@ static msf_status contract_args(Ctx *c, CtArgs *A)
     A->maps = (uint32_t *)v[6];
     A->cum = (uint32_t *)v[7];
     A->wlist = A->cum + CT_SMALL;
+    A->mat = (uint64_t *)(A->wlist + 2 * CT_SMALL);
     A->flags = (uint8_t *)v[8];
     A->wpart = (int64_t *)v[9];
     A->cnt = c->dcnt;
@@ -219,13 +224,16 @@ static msf_status contract_args(Ctx *c, CtArgs *A)
 }
 
 // Enqueue a phase's rounds from round k0 on (bound: the most vertices that
-// round can have, expect: those it is likely to have).  A round keeps about
-// a quarter of its vertices, at most half; seven more take CT_SMALL to one.
+// round can have, expect: those it is likely to have).  A round of the light
+// edges keeps about a quarter of its vertices, at most half, and five more
+// take CT_SMALL to one; in phase 1 most vertices hook onto the largest tree
+// and few are left after a round.  A launch with nothing to do takes 5 us; a
+// phase that needs more rounds goes on after a host step (25 us).
 static msf_status contract_rounds(Ctx *c, const CtArgs &A, int k0, uint32_t bound, double expect)
 {
     const int end = CT_ROUNDS - 2;
-    int small = 7;
-    for (int k = k0; k < end && small > 0; ++k, expect /= 4.0) {
+    int small = A.ph ? 3 : 5;
+    for (int k = k0; k < end && small > 0; ++k, expect /= A.ph ? 8.0 : 4.0) {
         const bool big = expect > CT_SMALL;
         if (!big) --small;
         ct_round(c->stream, A, k, big, bound >> (k - k0));
@@ -249,7 +257,7 @@ static msf_status contract_enqueue(Ctx *c, int ph, int k0, uint32_t bound)
         if (p == 1 && ph == 0) ct_between(c->stream, A, (uint32_t *)vcomp, (uint32_t *)vbits);
         const bool mid = p == ph && (k0 > 0 || ph > 0);
         MSF_TRY(contract_rounds(c, A, mid ? k0 : 0, mid ? bound : (uint32_t)S.n,
-                                mid ? (double)bound : (double)S.n / (p ? 2.0 : 1.0)));
+                                mid ? (double)bound : (double)S.n / (p ? 4.0 : 1.0)));
     }
     ct_total(c->stream, A, S.two_phase ? 1 : 0);
     MSF_TRY(launch_output(c, S.b.flags, S.m, S.w, S.wt, S.ids,
@@ -262,10 +270,17 @@ static msf_status contract_start(Ctx *c)
 {
     SolveState &S = c->ss;
     const int64_t tiles = (S.m + CT_TILE - 1) / CT_TILE;
-    S.ct_W = (uint32_t)std::min<int64_t>(CT_MAX_WAVES, (tiles + 15) / 16 * 16);
-    S.ct_words = ((size_t)S.m + 3) / 4;
     const int64_t light = contract_light(S.n, S.m);
-    S.two_phase = light * 10 <= S.m * 6;
+    S.two_phase = light * 2 <= S.m;
+    // the passes over the input want two workgroups of 16 waves on each
+    // compute unit, those over the list one, up to 2^23 edges (4096 / 8192
+    // waves: R-MAT s22 2.15 / 2.21 ms, grid 256^3 3.81 / 3.67 ms)
+    const int64_t list = S.two_phase ? light : S.m;
+    const int64_t waves = S.m > ((int64_t)1 << 23) ? CT_MAX_WAVES : CT_MAX_WAVES / 2;
+    S.ct_W = (uint32_t)std::min<int64_t>(waves, (tiles + 15) / 16 * 16);
+    S.ct_pass = list > ((int64_t)1 << 23) ? S.ct_W
+                                          : std::min<uint32_t>(S.ct_W, CT_MAX_WAVES / 2);
+    S.ct_words = ((size_t)S.m + 3) / 4;
     CtArgs A;
     MSF_TRY(contract_args(c, &A));
     S.b.flags = A.flags;
@@ -304,7 +319,7 @@ static msf_status contract_advance(Ctx *c)
         for (int k = 0; k < CT_ROUNDS && h->ct.done[ph][k]; ++k, ++rounds) {
             if (rounds >= 64) continue;
             S.st.hooks[rounds] = h->ct.hooks[ph][k];
-            S.st.active_nnz[rounds] = 2 * (int64_t)h->ct.E[ph][k];
+            S.st.active_nnz[rounds] = 2 * (int64_t)(h->ct.tick[ph][k] >> 16);
             if (h->ct.hooks[ph][k]) ++S.st.hook_rounds;
         }
     S.rounds = rounds;

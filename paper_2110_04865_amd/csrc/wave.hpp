@@ -14,12 +14,12 @@ __device__ __forceinline__ int lane_id() { return __lane_id(); }
 __device__ __forceinline__ uint64_t lanemask_lt() { return (1ull << __lane_id()) - 1ull; }
 
 // ---- DPP lane moves (GFX9 encodings; no LDS traffic) -----------------------
-// row_shr:n = 0x110 + n (within rows of 16 lanes), row_bcast:15 = 0x142 (lane
+// row_shr:n = 0x110 + n, row_shl:n = 0x100 + n (within rows of 16 lanes), row_bcast:15 = 0x142 (lane
 // 15 of a row to the next row), row_bcast:31 = 0x143 (lane 31 to rows 2-3),
 // wave_shl:1 = 0x130 (lane l reads l+1), wave_shr:1 = 0x138 (lane l reads
 // l-1).  Lanes without a source, or in rows outside ROW_MASK, read `old`.
 constexpr int DPP_ROW_SHR1 = 0x111, DPP_ROW_SHR2 = 0x112, DPP_ROW_SHR4 = 0x114,
-              DPP_ROW_SHR8 = 0x118, DPP_ROW_BCAST15 = 0x142, DPP_ROW_BCAST31 = 0x143,
+              DPP_ROW_SHR8 = 0x118, DPP_ROW_SHL1 = 0x101, DPP_ROW_BCAST15 = 0x142, DPP_ROW_BCAST31 = 0x143,
               DPP_WAVE_SHL1 = 0x130, DPP_WAVE_SHR1 = 0x138;
 
 template <int CTRL, int ROW_MASK = 0xF>
