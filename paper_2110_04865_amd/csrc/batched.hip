@@ -12,6 +12,7 @@
 #include <vector>
 #include <cstring>
 
+#include "contract.hpp"
 #include "exact_sum.hpp"
 #include "msf_internal.hpp"
 #include "persist.hpp"
@@ -252,7 +253,9 @@ msf_status batched_persistent(Ctx *c, int32_t G, const int64_t *vtx_off, const i
 bool small_eligible(const Ctx *c, int32_t n, int64_t m)
 {
     return c->small_m > 0 && m > 0 && m <= c->small_m && (uint32_t)n <= PERSIST_MAX_N &&
-           persist_state_bytes((uint32_t)n, (uint32_t)m) <= SMALL_LDS &&
+           (contract_settings(c)
+                ? m + 2 * (int64_t)n <= SMALL_WORK
+                : persist_state_bytes((uint32_t)n, (uint32_t)m) <= SMALL_LDS) &&
            persist_cfg_fits(c->device, PersistCfg{1024, 4, SMALL_LDS});
 }
 

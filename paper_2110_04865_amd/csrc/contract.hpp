@@ -55,6 +55,9 @@ struct CtArgs {
     Counters *cnt = nullptr;
 };
 
+// Whether the context's settings leave msf_solve to these rounds.
+bool contract_settings(const Ctx *c);
+
 // Words of the maps of rounds 1, 2, ... (round k has at most n >> k
 // vertices: every vertex with an edge hooks).
 size_t ct_maps_words(int32_t n);

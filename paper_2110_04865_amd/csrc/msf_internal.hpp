@@ -295,8 +295,9 @@ struct Ctx {
     // larger ones solved one by one), 0 the disjoint union through the
     // round loop
     int batch_mode = 1;
-    // msf_solve of graphs with at most this many edges (and state that fits
-    // LDS) by one workgroup of the persistent kernel; 0 turns it off
+    // msf_solve of graphs with at most this many edges (and within the sizes
+    // of small_eligible) by one workgroup of the persistent kernel; 0 turns
+    // it off
     int64_t small_m = (int64_t)1 << 17;
     // kept graphs (msf_graph_create) store their vertices by decreasing
     // degree class (1) or in the caller's order (0)

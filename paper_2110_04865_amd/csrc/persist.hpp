@@ -58,8 +58,9 @@ constexpr uint32_t PERSIST_MAX_M = 1u << 22;
 // Dynamic LDS of the one-workgroup solve of a small graph (msf_solve).
 constexpr uint32_t SMALL_LDS = 150u << 10;
 
-// The size by which msf_solve and the server choose the one-workgroup path
-// (up to SMALL_LDS), and the part of a slot beside 32 bytes per edge.
+// The size by which the server, and msf_solve with other than the default
+// settings, choose the one-workgroup path (up to SMALL_LDS), and the part of
+// a slot beside 32 bytes per edge.
 __host__ __device__ inline size_t persist_state_bytes(uint32_t n, uint32_t m)
 {
     return 20 * (size_t)n + 4 * (((size_t)m + 31) / 32);
@@ -82,8 +83,18 @@ hipError_t launch_persist(hipStream_t s, const PersistArgs &A, const PersistCfg 
 void launch_small_setup(hipStream_t s, int64_t *vo, int64_t *eo, uint32_t *order, int64_t n,
                         int64_t m);
 
+// The one-workgroup path's share where the contracted rounds are the other
+// choice: edges + 2 * vertices.  One workgroup takes about 1.5-2 us per 1000
+// of them, the contracted rounds 140-230 us at these sizes, mostly launches.
+// One workgroup / contracted rounds, us a solve by vertices and edges: 8000,
+// 16000: 112 / 179; 8000, 48000: 154 / 164; 16000, 32000: 166 / 201; 12000,
+// 48000: 176 / 178; 3000, 64000: 152 / 136; 8000, 64000: 181 / 164; 24000,
+// 48000: 243 / 231; 5000, 96000: 206 / 158; 1000, 128000: 188 / 124.
+constexpr int64_t SMALL_WORK = 68000;
+
 // Whether msf_solve takes the one-workgroup path for this graph: at most
-// c->small_m edges and state that fits the largest LDS allocation.
+// c->small_m edges, and SMALL_WORK or, where the rounds over an adjacency
+// matrix are the other choice, state that fits the largest LDS allocation.
 bool small_eligible(const Ctx *c, int32_t n, int64_t m);
 
 // msf_solve of a small graph by one workgroup of the persistent kernel

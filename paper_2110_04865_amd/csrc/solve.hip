@@ -158,14 +158,17 @@ static int edge_bits(int64_t m);
 
 // ------------------------------------- rounds over a contracted edge list --
 
+bool contract_settings(const Ctx *c)
+{
+    if (c->contract != 1) return c->contract == 2;
+    return c->heads == 1 && c->filter_mode == 1 && !c->check_rounds && c->first_round == 2 &&
+           c->bucketed_build == 1 && c->slices == 0 && c->graph_rounds == 2 && c->small_m > 0;
+}
+
 static bool contract_eligible(const Ctx *c, int32_t n, int64_t m)
 {
-    if (n < 2 || m < 1 || c->contract == 0) return false;
-    if (c->contract == 2) return true;
-    const bool defaults = c->heads == 1 && c->filter_mode == 1 && !c->check_rounds &&
-                          c->first_round == 2 && c->bucketed_build == 1 && c->slices == 0 &&
-                          c->graph_rounds == 2;
-    return defaults && c->small_m > 0 && !small_eligible(c, n, m);
+    return n >= 2 && m >= 1 && contract_settings(c) &&
+           (c->contract == 2 || !small_eligible(c, n, m));
 }
 
 // Edges of phase 0: 0.4 n ln(4 m / n) of the lightest.  With f n random

@@ -174,6 +174,19 @@ def test_default_route_and_bad_input(pkg):
     c.close()
 
 
+@pytest.mark.parametrize("n,m,path", [(1000, 66000, 1), (1000, 66001, 4), (22000, 24000, 1),
+                                      (22000, 24001, 4), (33999, 2, 1), (34000, 1, 4)])
+def test_one_workgroup_line(pkg, n, m, path):
+    """A default context solves up to 68000 = edges + 2 * vertices in one
+    workgroup, and one more by the contracted rounds."""
+    c = pkg.Context(0)
+    rng = np.random.default_rng(n + m)
+    e = rng.integers(0, n, size=(m, 2)).astype(np.int32)
+    check(c, n, e, rng.integers(0, 50, size=m).astype(np.uint32), U32, "line, ties", path=path)
+    check(c, n, e, rng.standard_normal(m).astype(np.float32), F32, "line, f32", path=path)
+    c.close()
+
+
 def test_refused_allocations(pkg):
     """Every workspace allocation of the path refused in turn: MSF_ENOMEM,
     the output untouched, and the next solve right."""
