@@ -71,9 +71,28 @@ msf_status ws_get(Ctx *c, Slot s, size_t bytes, void **out)
 
 msf_status read_counters(Ctx *c)
 {
-    MSF_HIP(hipMemcpyAsync(c->hcnt, c->dcnt, offsetof(Counters, ct), hipMemcpyDeviceToHost,
-                           c->stream));
+    launch_publish(c, offsetof(Counters, ct));
+    MSF_HIP(hipGetLastError());
     MSF_HIP(hipStreamSynchronize(c->stream));
+    return MSF_OK;
+}
+
+msf_status pin_get(Ctx *c, size_t bytes, void **out)
+{
+    if (c->hpin_cap < bytes) {
+        if (c->hpin) (void)hipHostFree(c->hpin);
+        c->hpin = nullptr;
+        c->hpin_cap = 0;
+        const size_t cap = (bytes + 65535) & ~(size_t)65535;
+        if (hipHostMalloc(&c->hpin, cap, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            c->hpin = nullptr;
+            set_error("host allocation of %zu bytes failed", cap);
+            return MSF_ENOMEM;
+        }
+        c->hpin_cap = cap;
+    }
+    *out = c->hpin;
     return MSF_OK;
 }
 
@@ -136,11 +155,16 @@ msf_status ctx_init(Ctx *c, int device, hipStream_t stream, bool async_alloc)
     c->async_alloc = async_alloc;
     MSF_TRY(noalloc_init(device));
     if (hipMalloc(&c->dcnt, sizeof(Counters)) != hipSuccess ||
-        hipHostMalloc(&c->hcnt, sizeof(Counters), hipHostMallocDefault) != hipSuccess) {
+        hipHostMalloc((void **)&c->hcnt, sizeof(Counters) + sizeof(SmallOut),
+                      hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         set_error("counter allocation failed");
         return MSF_ENOMEM;
     }
+    c->hsmall = reinterpret_cast<SmallOut *>(c->hcnt + 1);
+    int khz = 0;
+    MSF_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device));
+    if (khz > 0) c->clock_khz = khz;
     for (auto &ev : c->sev)
         if (hipEventCreate(&ev) != hipSuccess) {
             set_error("event creation failed");
@@ -201,6 +225,7 @@ void ctx_release(Ctx *c)
         if (ev) (void)hipEventDestroy(ev), ev = nullptr;
     if (c->dcnt) (void)hipFree(c->dcnt), c->dcnt = nullptr;
     if (c->hcnt) (void)hipHostFree(c->hcnt), c->hcnt = nullptr;
+    if (c->hpin) (void)hipHostFree(c->hpin), c->hpin = nullptr;
 }
 
 }  // namespace msf

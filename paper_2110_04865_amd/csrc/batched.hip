@@ -101,18 +101,54 @@ __global__ __launch_bounds__(256) void k_split(const int32_t *__restrict__ gids,
 }
 
 
+// out[0..count) = ids, unless a graph of the batch failed.
+__global__ __launch_bounds__(256) void k_batch_ids(const int32_t *__restrict__ ids,
+                                                   int32_t *__restrict__ out, int64_t count,
+                                                   const uint32_t *__restrict__ err)
+{
+    if (*err) return;
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += stride)
+        out[i] = ids[i];
+}
+
+// The small arrays of a batch, each once on the device and once in pinned
+// host memory: the offsets, the order, the queue and error words (copied to
+// the device in one piece), then the counts and totals (copied back in one
+// piece with the two words).
+struct BatchBlock {
+    int64_t *voff, *eoff;
+    uint32_t *order;
+    uint32_t *ctl;  // queue, error word
+    int64_t *counts;
+    uint64_t *tu;
+    double *tf;
+    BatchBlock(void *p, size_t G)
+    {
+        voff = (int64_t *)p;
+        eoff = voff + (G + 1);
+        order = (uint32_t *)(eoff + (G + 1));
+        ctl = order + ((G + 1) & ~(size_t)1);
+        counts = (int64_t *)(ctl + 2);
+        tu = (uint64_t *)(counts + G);
+        tf = (double *)(tu + G);
+    }
+    size_t up_bytes() const { return (size_t)((uint8_t *)counts - (uint8_t *)voff); }
+    static size_t bytes(size_t G) { return 16 * (G + 1) + 4 * (G + 1) + 8 + 24 * G; }
+};
+
 // Batched solve by the persistent kernel (kernels_persist.hip) for every
 // graph it takes, and one msf_solve-equivalent per graph for the rest.
 // Writes each graph's ids into d_stage (device, at vtx_off[g]) and its
-// count and totals into hres (host: counts, then u64 totals, then f64
-// totals as bits); on any error nothing outside the workspace is written.
-msf_status batched_persistent(Ctx *c, int32_t G, const int64_t *vtx_off, const int64_t *edge_off,
-                              const int64_t *d_voff, const int64_t *d_eoff,
+// count and totals into the host block, whose offsets are set; the ids then
+// go to d_out (device, if given).  On any error nothing outside the
+// workspace is written.
+msf_status batched_persistent(Ctx *c, int32_t G, const BatchBlock &D, const BatchBlock &H,
                               const int32_t *d_edges, const void *d_w, msf_wtype wt,
-                              int32_t *d_stage, int64_t *d_counts, uint64_t *d_tu,
-                              double *d_tf, int64_t *hres)
+                              int32_t *d_stage, int32_t *d_out)
 {
     hipStream_t s = c->stream;
+    const int64_t *vtx_off = H.voff, *edge_off = H.eoff;
     std::vector<uint32_t> order, large;
     uint32_t n_cap = 1, m_cap = 1;
     double sum_n = 0.0, sum_m = 0.0;
@@ -162,36 +198,39 @@ msf_status batched_persistent(Ctx *c, int32_t G, const int64_t *vtx_off, const i
         // two live-edge lists of the largest graph: 32 bytes per edge)
         slots = std::min({slots, Gs, (uint32_t)std::max(1, 4 * cus)});
         const size_t slot_bytes = persist_slot_bytes(n_cap, m_cap);
-        void *vord, *vctl, *vscr;
-        if ((rc = ws_get(c, WS_PORDER, 4 * ((size_t)Gs + sample.size()), &vord))) return rc;
+        void *vsample, *vctl, *vscr;
+        if ((rc = ws_get(c, WS_PORDER, 4 * sample.size(), &vsample))) return rc;
         if ((rc = ws_get(c, WS_PCTL, 256, &vctl))) return rc;
         if ((rc = ws_get(c, WS_PSCRATCH, slot_bytes * slots, &vscr))) return rc;
-        uint32_t *d_order = (uint32_t *)vord, *d_sample = d_order + Gs;
-        uint32_t *d_ctl = (uint32_t *)vctl;
-        MSF_HIP(hipMemcpyAsync(d_order, order.data(), 4 * (size_t)Gs, hipMemcpyHostToDevice, s));
-        MSF_HIP(hipMemcpyAsync(d_sample, sample.data(), 4 * sample.size(), hipMemcpyHostToDevice,
-                               s));
+        std::memcpy(H.order, order.data(), 4 * (size_t)Gs);
+        H.ctl[0] = H.ctl[1] = 0;
+        MSF_HIP(hipMemcpyAsync(D.voff, H.voff, D.up_bytes(), hipMemcpyHostToDevice, s));
         PersistArgs A;
-        A.queue = d_ctl;
-        A.err = d_ctl + 1;
-        A.vtx_off = d_voff;
-        A.edge_off = d_eoff;
+        A.vtx_off = D.voff;
+        A.edge_off = D.eoff;
         A.edges = d_edges;
         A.w = (const uint32_t *)d_w;
         A.out = d_stage;
-        A.counts = d_counts;
-        A.tot_u64 = d_tu;
-        A.tot_f64 = d_tf;
+        A.counts = D.counts;
+        A.tot_u64 = D.tu;
+        A.tot_f64 = D.tf;
         A.scratch = (uint8_t *)vscr;
         A.slot_bytes = slot_bytes;
         auto grid_of = [&](int i, uint32_t graphs) {
             return (unsigned)std::max<uint32_t>(
                 1, std::min<uint32_t>({graphs, slots, (uint32_t)std::max(1, cus * bpc[i])}));
         };
+        bool sampled = false;
         auto run = [&](int i, float *ms) -> msf_status {
+            if (!sampled)
+                MSF_HIP(hipMemcpyAsync(vsample, sample.data(), 4 * sample.size(),
+                                       hipMemcpyHostToDevice, s));
+            sampled = true;
             PersistArgs T = A;
             T.G = (int32_t)sample.size();
-            T.order = d_sample;
+            T.order = (const uint32_t *)vsample;
+            T.queue = (uint32_t *)vctl;
+            T.err = (uint32_t *)vctl + 1;
             T.lds_bytes = cand[i].lds;
             if (ms) MSF_HIP(hipEventRecord(c->ev[0], s));
             MSF_HIP(launch_persist(s, T, cand[i], (int)wt, grid_of(i, T.G)));
@@ -208,29 +247,36 @@ msf_status batched_persistent(Ctx *c, int32_t G, const int64_t *vtx_off, const i
         int ci = 0;
         if ((rc = persist_pick(c, shape, (int)wt, run, &ci))) return rc;
         A.G = (int32_t)Gs;
-        A.order = d_order;
+        A.order = D.order;
+        A.queue = D.ctl;
+        A.err = D.ctl + 1;
         A.lds_bytes = cand[ci].lds;
         const unsigned grid = grid_of(ci, Gs);
         MSF_HIP(hipEventRecord(c->ev[0], s));
-        MSF_HIP(launch_persist(s, A, cand[ci], (int)wt, grid));
+        MSF_HIP(launch_persist(s, A, cand[ci], (int)wt, grid, false));
         MSF_HIP(hipEventRecord(c->ev[1], s));
         c->stats.batch_config = ci;
         c->stats.batch_grid = (int32_t)grid;
     }
-    MSF_HIP(hipMemcpyAsync(hres, d_counts, 24 * (size_t)G, hipMemcpyDeviceToHost, s));
-    uint32_t herr = 0;
+    // the ids to the caller's array and the results to the host, in one wait
+    const int64_t N = vtx_off[G];
+    auto ids_out = [&]() -> msf_status {
+        if (!d_out || N == 0) return MSF_OK;
+        const size_t blocks = ((size_t)N + 1023) / 1024;
+        k_batch_ids<<<(unsigned)std::min<size_t>(blocks, 4096), 256, 0, s>>>(d_stage, d_out, N,
+                                                                            D.ctl + 1);
+        MSF_HIP(hipGetLastError());
+        return MSF_OK;
+    };
     if (Gs > 0) {
-        void *vctl;
-        if ((rc = ws_get(c, WS_PCTL, 256, &vctl))) return rc;
-        MSF_HIP(hipMemcpyAsync(&herr, (uint32_t *)vctl + 1, 4, hipMemcpyDeviceToHost, s));
-    }
-    MSF_HIP(hipStreamSynchronize(s));
-    if (Gs > 0) {
+        if (large.empty() && (rc = ids_out())) return rc;
+        MSF_HIP(hipMemcpyAsync(H.ctl, D.ctl, 8 + 24 * (size_t)G, hipMemcpyDeviceToHost, s));
+        MSF_HIP(hipStreamSynchronize(s));
         float ms = 0.f;
         (void)hipEventElapsedTime(&ms, c->ev[0], c->ev[1]);
         c->stats.batch_ms = ms;
+        if ((rc = decode_err(H.ctl[1]))) return rc;
     }
-    if ((rc = decode_err(herr))) return rc;
     // graphs too large for one workgroup: one solve each, into the staging
     for (uint32_t g : large) {
         const int64_t v0 = vtx_off[g], e0 = edge_off[g];
@@ -242,11 +288,11 @@ msf_status batched_persistent(Ctx *c, int32_t G, const int64_t *vtx_off, const i
                           &tot);
         c->stats = keep;
         if (rc) return rc;
-        hres[g] = cnt;
-        hres[G + g] = (int64_t)tot.u64;
-        std::memcpy(&hres[2 * (size_t)G + g], &tot.f64, sizeof(double));
+        H.counts[g] = cnt;
+        H.tu[g] = tot.u64;
+        H.tf[g] = tot.f64;
     }
-    return MSF_OK;
+    return large.empty() ? MSF_OK : ids_out();
 }
 
 
@@ -269,53 +315,36 @@ msf_status solve_small(Ctx *c, int32_t n, int64_t m, const int32_t *d_edges, con
     if ((rc = ws_get(c, WS_PCTL, 512, &vctl))) return rc;
     if ((rc = ws_get(c, WS_PSCRATCH, persist_slot_bytes((uint32_t)n, (uint32_t)m), &vscr)))
         return rc;
-    // control block: queue, error word; at byte 64 the offsets, then the
-    // count, totals, the order and the per-round hooks
-    uint8_t *ctl = (uint8_t *)vctl;
     PersistArgs A;
     A.G = 1;
-    A.queue = (uint32_t *)ctl;
-    A.err = (uint32_t *)ctl + 1;
-    A.vtx_off = (int64_t *)(ctl + 64);
-    A.edge_off = (int64_t *)(ctl + 80);
-    A.counts = (int64_t *)(ctl + 96);
-    A.tot_u64 = (uint64_t *)(ctl + 104);
-    A.tot_f64 = (double *)(ctl + 112);
-    A.order = (uint32_t *)(ctl + 120);
-    A.round_hooks = (uint32_t *)(ctl + 128);
+    A.one_n = n;
+    A.one_m = m;
+    A.one_out = c->hsmall;
+    A.round_hooks = (uint32_t *)vctl;
     A.edges = d_edges;
     A.w = (const uint32_t *)d_w;
     A.out = d_ids;
     A.scratch = (uint8_t *)vscr;
     A.slot_bytes = persist_slot_bytes((uint32_t)n, (uint32_t)m);
     A.lds_bytes = SMALL_LDS;
-    launch_small_setup(s, (int64_t *)A.vtx_off, (int64_t *)A.edge_off, (uint32_t *)A.order, n, m);
-    MSF_HIP(hipEventRecord(c->ev[0], s));
-    MSF_HIP(launch_persist(s, A, PersistCfg{1024, 4, SMALL_LDS}, (int)wt, 1));
-    MSF_HIP(hipEventRecord(c->ev[1], s));
-    alignas(8) uint8_t h[512];
-    MSF_HIP(hipMemcpyAsync(h, ctl, 512, hipMemcpyDeviceToHost, s));
+    MSF_HIP(launch_persist(s, A, PersistCfg{1024, 4, SMALL_LDS}, (int)wt, 1, false));
     MSF_HIP(hipStreamSynchronize(s));
-    uint32_t err;
-    std::memcpy(&err, h + 4, 4);
-    if ((rc = decode_err(err))) return rc;
-    const uint32_t *hooks = (const uint32_t *)(h + 128);
+    const SmallOut *h = c->hsmall;
+    if ((rc = decode_err(h->err))) return rc;
     msf_stats st{};
     st.batch_config = -1;
     st.path = 1;
-    st.rounds = (int32_t)hooks[64];
+    st.rounds = (int32_t)h->hooks[64];
     for (int k = 0; k < st.rounds && k < 64; ++k) {
-        st.hooks[k] = hooks[k];
-        st.hook_rounds += hooks[k] != 0;
+        st.hooks[k] = h->hooks[k];
+        st.hook_rounds += h->hooks[k] != 0;
     }
-    float ms = 0.f;
-    (void)hipEventElapsedTime(&ms, c->ev[0], c->ev[1]);
-    st.rounds_ms = ms;
+    st.rounds_ms = (double)h->clk / c->clock_khz;
     c->stats = st;
-    std::memcpy(count, h + 96, 8);
+    *count = h->count;
     if (total) {
-        std::memcpy(&total->u64, h + 104, 8);
-        std::memcpy(&total->f64, h + 112, 8);
+        total->u64 = h->tot_u64;
+        total->f64 = h->tot_f64;
     }
     return MSF_OK;
 }
@@ -369,14 +398,14 @@ extern "C" msf_status msf_solve_batched(msf_ctx *ctx, int32_t G, const int64_t *
     MSF_HIP(hipSetDevice(c->device));
     hipStream_t s = c->stream;
     const size_t mm = (size_t)std::max<int64_t>(M, 1), nn = (size_t)std::max<int64_t>(N, 1);
-    void *voff, *vge = nullptr, *vgid, *vout = nullptr, *vw = nullptr, *vin = nullptr, *vres;
+    void *vblock, *hblock, *vge = nullptr, *vgid, *vout = nullptr, *vw = nullptr, *vin = nullptr;
     msf_status rc;
-    if ((rc = ws_get(c, WS_BATCH0, 8 * 2 * (size_t)(G + 1), &voff))) return rc;
+    if ((rc = ws_get(c, WS_BATCH0, BatchBlock::bytes(G), &vblock))) return rc;
     if ((rc = ws_get(c, WS_BATCH2, 4 * nn, &vgid))) return rc;
-    if ((rc = ws_get(c, WS_BATCH3, (8 + 8 + 8) * (size_t)G, &vres))) return rc;
-    int64_t *d_voff = (int64_t *)voff, *d_eoff = d_voff + (G + 1);
-    MSF_HIP(hipMemcpyAsync(d_voff, vtx_off, 8 * (size_t)(G + 1), hipMemcpyHostToDevice, s));
-    MSF_HIP(hipMemcpyAsync(d_eoff, edge_off, 8 * (size_t)(G + 1), hipMemcpyHostToDevice, s));
+    if ((rc = pin_get(c, BatchBlock::bytes(G), &hblock))) return rc;
+    const BatchBlock D(vblock, G), H(hblock, G);
+    std::memcpy(H.voff, vtx_off, 8 * (size_t)(G + 1));
+    std::memcpy(H.eoff, edge_off, 8 * (size_t)(G + 1));
     const int32_t *d_edges = edges;
     const void *d_w = weights;
     int32_t *d_out = forest_ids;
@@ -392,18 +421,15 @@ extern "C" msf_status msf_solve_batched(msf_ctx *ctx, int32_t G, const int64_t *
         d_w = vw;
         d_out = (int32_t *)vout;
     }
-    int64_t *d_counts = (int64_t *)vres;
-    uint64_t *d_tu = (uint64_t *)(d_counts + G);
-    double *d_tf = (double *)(d_tu + G);
-    std::vector<int64_t> hres(3 * (size_t)G);
     if (c->batch_mode == 0) {
         // the disjoint union through the round loop of msf_solve
         if ((rc = ws_get(c, WS_BATCH1, 8 * mm, &vge))) return rc;
+        MSF_HIP(hipMemcpyAsync(D.voff, H.voff, 16 * (size_t)(G + 1), hipMemcpyHostToDevice, s));
         launch_fill_u32(s, &c->dcnt->err, 0u, 1);
         if (M > 0) {
             size_t g = (size_t)(M + 255) / 256;
             k_globalize<<<(unsigned)std::min<size_t>(g, 16384), 256, 0, s>>>(
-                d_edges, M, d_voff, d_eoff, G, (int32_t *)vge, c->dcnt);
+                d_edges, M, D.voff, D.eoff, G, (int32_t *)vge, c->dcnt);
         }
         MSF_HIP(hipGetLastError());
         if ((rc = read_counters(c))) return rc;
@@ -417,35 +443,35 @@ extern "C" msf_status msf_solve_batched(msf_ctx *ctx, int32_t G, const int64_t *
                           &tot);
         if (rc) return rc;
         if (wt == MSF_W_F32)
-            k_split<MSF_W_F32><<<G, 256, 0, s>>>((const int32_t *)vgid, cnt, d_voff, d_eoff, d_w,
-                                                 d_out, d_counts, d_tu, d_tf);
+            k_split<MSF_W_F32><<<G, 256, 0, s>>>((const int32_t *)vgid, cnt, D.voff, D.eoff, d_w,
+                                                 d_out, D.counts, D.tu, D.tf);
         else
-            k_split<MSF_W_U32><<<G, 256, 0, s>>>((const int32_t *)vgid, cnt, d_voff, d_eoff, d_w,
-                                                 d_out, d_counts, d_tu, d_tf);
+            k_split<MSF_W_U32><<<G, 256, 0, s>>>((const int32_t *)vgid, cnt, D.voff, D.eoff, d_w,
+                                                 d_out, D.counts, D.tu, D.tf);
         MSF_HIP(hipGetLastError());
-        MSF_HIP(hipMemcpyAsync(hres.data(), vres, 24 * (size_t)G, hipMemcpyDeviceToHost, s));
+        MSF_HIP(hipMemcpyAsync(H.counts, D.counts, 24 * (size_t)G, hipMemcpyDeviceToHost, s));
         c->stats = msf_stats{};
         c->stats.batch_config = -1;
     } else {
         // persistent launch into the staging buffer (vgid); the caller's
         // forest ids are written only once every graph has succeeded
-        rc = batched_persistent(c, G, vtx_off, edge_off, d_voff, d_eoff, d_edges, d_w, wt,
-                                (int32_t *)vgid, d_counts, d_tu, d_tf, hres.data());
-        if (rc) return rc;
+        rc = batched_persistent(c, G, D, H, d_edges, d_w, wt, (int32_t *)vgid,
+                                mem == MSF_MEM_HOST ? nullptr : d_out);
+        if (rc) {
+            // (nothing enqueued may still read the pinned block)
+            (void)hipStreamSynchronize(s);
+            return rc;
+        }
         if (mem == MSF_MEM_HOST) d_out = (int32_t *)vgid;  // downloaded from there below
-        else if (N > 0)
-            MSF_HIP(hipMemcpyAsync(d_out, vgid, 4 * (size_t)N, hipMemcpyDeviceToDevice, s));
     }
     if (mem == MSF_MEM_HOST && N > 0)
         MSF_HIP(hipMemcpyAsync(forest_ids, d_out, 4 * (size_t)N, hipMemcpyDeviceToHost, s));
     MSF_HIP(hipStreamSynchronize(s));
     for (int32_t g = 0; g < G; ++g) {
-        counts[g] = hres[g];
+        counts[g] = H.counts[g];
         if (totals) {
-            totals[g].u64 = (uint64_t)hres[G + g];
-            double f;
-            std::memcpy(&f, &hres[2 * (size_t)G + g], sizeof f);
-            totals[g].f64 = f;
+            totals[g].u64 = H.tu[g];
+            totals[g].f64 = H.tf[g];
         }
     }
     return MSF_OK;

@@ -59,6 +59,24 @@ void launch_fill_u32(hipStream_t s, uint32_t *p, uint32_t v, size_t n)
 {
     if (n) k_fill_u32<<<grid_for(n), 256, 0, s>>>(p, v, n);
 }
+
+__global__ __launch_bounds__(256) void k_publish(const uint64_t *__restrict__ src,
+                                                 uint64_t *__restrict__ dst, uint32_t words,
+                                                 uint32_t end_clk)
+{
+    for (uint32_t i = threadIdx.x; i < words; i += 256)
+        dst[i] = i == end_clk ? (uint64_t)wall_clock64() : src[i];
+}
+
+void launch_publish(Ctx *c, size_t bytes)
+{
+    static_assert(sizeof(Counters) % 8 == 0 && offsetof(Counters, ct) % 8 == 0, "whole words");
+    const uint32_t end = (uint32_t)(offsetof(Counters, ct.clk) / 8) + 3;
+    k_publish<<<1, 256, 0, c->stream>>>(reinterpret_cast<const uint64_t *>(c->dcnt),
+                                        reinterpret_cast<uint64_t *>(c->hcnt),
+                                        (uint32_t)(bytes / 8), end);
+}
+
 void launch_zero_lookback(hipStream_t s, uint64_t *status, uint32_t tiles, uint32_t *z1,
                           uint32_t n1, uint32_t *z2, uint32_t n2)
 {

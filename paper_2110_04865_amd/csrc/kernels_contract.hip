@@ -103,6 +103,7 @@ __global__ __launch_bounds__(256) void k_ct_init(CtArgs A, size_t flag_words)
         if (threadIdx.x == 0) {
             A.cnt->ct.L[0][0] = (uint32_t)A.n;
             A.cnt->ct.T = KEY_INF;
+            A.cnt->ct.clk[0] = wall_clock64();
         }
     }
     uint32_t *fl = reinterpret_cast<uint32_t *>(A.flags);
@@ -725,6 +726,8 @@ __global__ __launch_bounds__(CE_NT, 8) void k_ct_edges(CtArgs A, int k, int big)
     static_assert(2 * (sizeof s_r + sizeof s_cum + 256) <= 160 << 10, "two workgroups a CU");
     static_assert(sizeof s_cum >= 8 * CT_HOT, "tags and counts in the map's place");
     Counters *c = A.cnt;
+    if (A.ph == 0 && k <= 1 && blockIdx.x == 0 && threadIdx.x == 0 && !c->ct.clk[1 + k])
+        c->ct.clk[1 + k] = wall_clock64();
     const uint32_t L = c->ct.L[A.ph][k];
     if (c->err || L == 0 || (L > CT_SMALL && !big)) return;
     if (k > 0 ? !c->ct.done[A.ph][k - 1] : (A.ph > 0 && !c->ct.phdone[A.ph - 1])) return;

@@ -536,10 +536,11 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
                                                  uint8_t *slot, PCtl<NT> &pc, int64_t *s_sum, int64_t *s_tot, uint32_t *s_scan)
 {
     const uint32_t tid = threadIdx.x;
-    const int64_t v0 = A.vtx_off[g];
-    const uint32_t n = (uint32_t)(A.vtx_off[g + 1] - v0);
-    const int64_t e0 = A.edge_off[g];
-    const uint32_t m = (uint32_t)(A.edge_off[g + 1] - e0);
+    const bool one = A.one_out != nullptr;
+    const int64_t v0 = one ? 0 : A.vtx_off[g];
+    const uint32_t n = (uint32_t)(one ? A.one_n : A.vtx_off[g + 1] - v0);
+    const int64_t e0 = one ? 0 : A.edge_off[g];
+    const uint32_t m = (uint32_t)(one ? A.one_m : A.edge_off[g + 1] - e0);
     const int2 *E = reinterpret_cast<const int2 *>(A.edges) + e0;
     const uint32_t *W = A.w + e0;
     const size_t S = A.lds_bytes;
@@ -889,11 +890,20 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
     wsum_block<NT, WT>(ws, s_sum, s_tot, 1);
     if (err) atomicOr(&pc.err, err);
     if (tid == 0) {
-        A.counts[g] = failed ? -(int64_t)pc.gerr : (int64_t)pos;
-        A.tot_u64[(size_t)g * A.tot_stride] = WT == MSF_W_U32 ? (uint64_t)s_tot[0] : 0;
-        A.tot_f64[(size_t)g * A.tot_stride] = exact_total_f64((uint64_t)s_tot[0], s_tot + 1,
-                                       (uint32_t)s_tot[1 + ACC_DIGITS],
-                                       (uint32_t)s_tot[2 + ACC_DIGITS], WT);
+        const int64_t count = failed ? -(int64_t)pc.gerr : (int64_t)pos;
+        const uint64_t tu = WT == MSF_W_U32 ? (uint64_t)s_tot[0] : 0;
+        const double tf = exact_total_f64((uint64_t)s_tot[0], s_tot + 1,
+                                          (uint32_t)s_tot[1 + ACC_DIGITS],
+                                          (uint32_t)s_tot[2 + ACC_DIGITS], WT);
+        if (one) {
+            A.one_out->count = count;
+            A.one_out->tot_u64 = tu;
+            A.one_out->tot_f64 = tf;
+        } else {
+            A.counts[g] = count;
+            A.tot_u64[(size_t)g * A.tot_stride] = tu;
+            A.tot_f64[(size_t)g * A.tot_stride] = tf;
+        }
     }
     __syncthreads();
 }
@@ -909,22 +919,33 @@ __global__ __launch_bounds__(NT) void k_persist(PersistArgs A)
     __shared__ int64_t s_tot[WS_WORDS];
     __shared__ uint32_t s_scan[NT / 64 + 1];
     uint8_t *slot = A.scratch + (size_t)blockIdx.x * A.slot_bytes;
+    const uint64_t t0 = wall_clock64();
+    const bool one = A.one_out != nullptr;
     if (threadIdx.x == 0) pc.err = 0;
-    for (;;) {
+    for (bool first = true;; first = false) {
         if (threadIdx.x == 0) {
-            const uint32_t k = atomicAdd(A.queue, 1u);
-            pc.g = k < (uint32_t)A.G ? (A.order ? A.order[k] : k) : NONE32;
+            const uint32_t k = one ? (first ? 0u : 1u) : atomicAdd(A.queue, 1u);
+            pc.g = k < (uint32_t)A.G ? (!one && A.order ? A.order[k] : k) : NONE32;
         }
         __syncthreads();
         const uint32_t g = uniform(pc.g);
         if (g == NONE32) break;
         // vertex numbers of at most 16 bits: both ends of an edge in one word
-        if (A.vtx_off[g + 1] - A.vtx_off[g] <= 65536)
+        if ((one ? A.one_n : A.vtx_off[g + 1] - A.vtx_off[g]) <= 65536)
             solve_contracted<NT, EPT, WT, true>(A, g, smem, slot, pc, s_sum, s_tot, s_scan);
         else
             solve_contracted<NT, EPT, WT, false>(A, g, smem, slot, pc, s_sum, s_tot, s_scan);
     }
-    if (threadIdx.x == 0 && pc.err) atomicOr(A.err, pc.err);
+    if (one) {
+        // (round_hooks was written before the last barriers)
+        if (threadIdx.x < 65) A.one_out->hooks[threadIdx.x] = A.round_hooks[threadIdx.x];
+        if (threadIdx.x == 0) {
+            A.one_out->err = pc.err;
+            A.one_out->clk = wall_clock64() - t0;
+        }
+    } else if (threadIdx.x == 0 && pc.err) {
+        atomicOr(A.err, pc.err);
+    }
 }
 
 // Queue counter and error word to zero (a kernel, not a memset, so the
@@ -935,24 +956,6 @@ __global__ void k_persist_reset(uint32_t *queue, uint32_t *err)
         *queue = 0;
         *err = 0;
     }
-}
-
-// Offsets and order of a one-graph launch: vertices [0, n), edges [0, m).
-__global__ void k_small_setup(int64_t *vo, int64_t *eo, uint32_t *order, int64_t n, int64_t m)
-{
-    if (threadIdx.x == 0) {
-        vo[0] = 0;
-        vo[1] = n;
-        eo[0] = 0;
-        eo[1] = m;
-        order[0] = 0;
-    }
-}
-
-void launch_small_setup(hipStream_t s, int64_t *vo, int64_t *eo, uint32_t *order, int64_t n,
-                        int64_t m)
-{
-    k_small_setup<<<1, 64, 0, s>>>(vo, eo, order, n, m);
 }
 
 namespace {
@@ -1027,9 +1030,9 @@ const PersistCfg *persist_candidates(int *count)
 }
 
 hipError_t launch_persist(hipStream_t s, const PersistArgs &A, const PersistCfg &cfg, int wt,
-                          unsigned grid)
+                          unsigned grid, bool reset)
 {
-    k_persist_reset<<<1, 64, 0, s>>>(A.queue, A.err);
+    if (reset) k_persist_reset<<<1, 64, 0, s>>>(A.queue, A.err);
     if (cfg.nt == 256 && cfg.ept == 4) return launch_cfg<256, 4>(s, A, wt, grid);
     if (cfg.nt == 512 && cfg.ept == 2) return launch_cfg<512, 2>(s, A, wt, grid);
     if (cfg.nt == 512 && cfg.ept == 4) return launch_cfg<512, 4>(s, A, wt, grid);

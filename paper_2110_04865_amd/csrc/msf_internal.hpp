@@ -162,7 +162,18 @@ struct Counters {
         uint32_t E0[2];                // edges on a phase's list
         uint32_t pad;
         uint64_t T;                    // phase 0 takes keys up to this one
+        uint64_t clk[4];               // device clock: start, list made, first round done, end
     } ct;
+};
+
+// What the one-workgroup solve of one graph writes to pinned host memory.
+struct SmallOut {
+    uint32_t err, pad;
+    int64_t count;
+    uint64_t tot_u64;
+    double tot_f64;
+    uint64_t clk;        // device clock ticks of the kernel
+    uint32_t hooks[65];  // kept hooks of rounds 0..63; at [64] the rounds run
 };
 
 // Key-sorted runs for the head sweep: every 64-entry chunk of the
@@ -265,6 +276,11 @@ struct Ctx {
     DevBuf ws[WS_COUNT];
     Counters *dcnt = nullptr;   // device
     Counters *hcnt = nullptr;   // pinned host mirror
+    SmallOut *hsmall = nullptr;  // behind hcnt
+    // pinned staging of the batched solve's small arrays
+    void *hpin = nullptr;
+    size_t hpin_cap = 0;
+    double clock_khz = 1e5;  // of the device clock
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     hipEvent_t sev[2 * 64] = {};  // sweep start/end events, per round
     // one-launch passes (placement, run sort, level-2 and level-1
@@ -349,6 +365,15 @@ msf_status hip_fail(hipError_t e, const char *what);
 
 // Workspace: returns a device buffer of at least `bytes` for slot s.
 msf_status ws_get(Ctx *c, Slot s, size_t bytes, void **out);
+
+// Pinned host memory of the context, at least `bytes` of it (what it held
+// before is lost; the stream must be past its last use of it).
+msf_status pin_get(Ctx *c, size_t bytes, void **out);
+
+// Copy the counters' first `bytes` to the pinned host mirror by a kernel (a
+// stream copy of them is a kernel too, behind two queue handoffs: 10 us more
+// a step); contracted rounds: with the device clock as their end.
+void launch_publish(Ctx *c, size_t bytes);
 
 // Sync the context stream and copy the counters to the host mirror.
 msf_status read_counters(Ctx *c);

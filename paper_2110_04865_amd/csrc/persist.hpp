@@ -34,9 +34,13 @@ struct PersistArgs {
     size_t slot_bytes = 0;
     uint32_t lds_bytes = 0;
     uint32_t *err = nullptr;
-    // nullable: kept hooks of rounds 0..63 and, at [64], the rounds run
-    // (for a launch that solves one graph)
+    // one graph of one_n vertices and one_m edges and no queue, order,
+    // offsets, counts and totals: everything that the host reads goes to
+    // *one_out (pinned host memory, written once at the end).  round_hooks
+    // (device): kept hooks of rounds 0..63 and, at [64], the rounds run
+    SmallOut *one_out = nullptr;
     uint32_t *round_hooks = nullptr;
+    int64_t one_n = 0, one_m = 0;
     // graph g's totals go to tot_u64[g * tot_stride], tot_f64[g * tot_stride]
     // (2 when they are the fields of an msf_total array)
     uint32_t tot_stride = 1;
@@ -75,13 +79,9 @@ __host__ inline size_t persist_slot_bytes(uint32_t n_cap, uint32_t m_cap)
 // The candidate configurations the tuner times (count in *count).
 const PersistCfg *persist_candidates(int *count);
 
-// Zero the queue and error word, then launch `grid` workgroups.
+// Zero the queue and error word if reset, then launch `grid` workgroups.
 hipError_t launch_persist(hipStream_t s, const PersistArgs &A, const PersistCfg &cfg, int wt,
-                          unsigned grid);
-
-// Offsets {0, n}, {0, m} and order {0} of a one-graph launch (a kernel).
-void launch_small_setup(hipStream_t s, int64_t *vo, int64_t *eo, uint32_t *order, int64_t n,
-                        int64_t m);
+                          unsigned grid, bool reset = true);
 
 // The one-workgroup path's share where the contracted rounds are the other
 // choice: edges + 2 * vertices.  One workgroup takes about 1.5-2 us per 1000

@@ -144,10 +144,9 @@ constexpr int64_t HEADS_MIN_DEG = 16;
 // End a step: counters to pinned host memory, then the step event.
 static msf_status end_step(Ctx *c, int next_phase)
 {
-    MSF_HIP(hipGetLastError());
     // the contracted rounds' counters only for their own phase
-    const size_t bytes = next_phase == 8 ? sizeof(Counters) : offsetof(Counters, ct);
-    MSF_HIP(hipMemcpyAsync(c->hcnt, c->dcnt, bytes, hipMemcpyDeviceToHost, c->stream));
+    launch_publish(c, next_phase == 8 ? sizeof(Counters) : offsetof(Counters, ct));
+    MSF_HIP(hipGetLastError());
     MSF_HIP(hipEventRecord(c->ev[3], c->stream));
     c->ss.phase = next_phase;
     return MSF_OK;
@@ -240,8 +239,6 @@ static msf_status contract_rounds(Ctx *c, const CtArgs &A, int k0, uint32_t boun
         const bool big = expect > CT_SMALL;
         if (!big) --small;
         ct_round(c->stream, A, k, big, bound >> (k - k0));
-        // the first round of a solve ends its build interval
-        if (A.ph == 0 && k == 0) MSF_HIP(hipEventRecord(c->ev[1], c->stream));
     }
     return MSF_OK;
 }
@@ -265,7 +262,6 @@ static msf_status contract_enqueue(Ctx *c, int ph, int k0, uint32_t bound)
     ct_total(c->stream, A, S.two_phase ? 1 : 0);
     MSF_TRY(launch_output(c, S.b.flags, S.m, S.w, S.wt, S.ids,
                           (uint8_t *)c->ws[WS_PART].ptr + ct_wpart_bytes(), &c->dcnt->ct.fin));
-    MSF_HIP(hipEventRecord(c->ev[2], c->stream));
     return end_step(c, 8);
 }
 
@@ -287,13 +283,9 @@ static msf_status contract_start(Ctx *c)
     CtArgs A;
     MSF_TRY(contract_args(c, &A));
     S.b.flags = A.flags;
-    MSF_HIP(hipEventRecord(c->ev[0], c->stream));
     ct_init(c->stream, A, S.ct_words);
     if (S.two_phase) ct_threshold(c->stream, A, light);
     ct_select(c->stream, A);
-    // the light edges' list stands in for the adjacency matrix; the build
-    // interval also holds the set-up of the rounds
-    MSF_HIP(hipEventRecord(c->kev[1], c->stream));
     return contract_enqueue(c, 0, 0, (uint32_t)S.n);
 }
 
@@ -328,13 +320,12 @@ static msf_status contract_advance(Ctx *c)
     S.rounds = rounds;
     S.st.rounds = rounds;
     S.st.path = 4;
-    float ms = 0.f;
-    (void)hipEventElapsedTime(&ms, c->ev[0], c->kev[1]);
-    S.st.adjacency_ms = ms;
-    (void)hipEventElapsedTime(&ms, c->ev[0], c->ev[1]);
-    S.st.build_ms = ms;
-    (void)hipEventElapsedTime(&ms, c->ev[1], c->ev[2]);
-    S.st.rounds_ms = ms;
+    // the light edges' list stands in for the adjacency matrix; the build
+    // interval ends with the first round
+    const uint64_t *clk = h->ct.clk;
+    S.st.adjacency_ms = (double)(clk[1] - clk[0]) / c->clock_khz;
+    S.st.build_ms = (double)(clk[2] - clk[0]) / c->clock_khz;
+    S.st.rounds_ms = (double)(clk[3] - clk[2]) / c->clock_khz;
     c->stats = S.st;
     S.phase = 5;
     return MSF_OK;
