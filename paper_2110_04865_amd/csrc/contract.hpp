@@ -19,6 +19,7 @@ constexpr uint32_t CT_MAX_WAVES = 8192;  // list segments
 constexpr uint32_t CT_TILE = 256;        // input edges a wave takes at a time
 constexpr uint32_t CT_WSLOTS = 2048;     // partial weight sums
 constexpr uint32_t CT_SMALL = 7680;      // vertices whose minima fit LDS (two workgroups a CU)
+constexpr uint32_t CT_FINISH = 2048;     // vertices whose round one workgroup finishes best
 constexpr uint32_t CT_PAIR = 32;         // vertices finished on their pairs' minima
 
 // Edges per list segment when the input's tiles are dealt to W waves.

@@ -66,6 +66,11 @@ __device__ __forceinline__ uint32_t *ct_map(const CtArgs &A, int k)
     return k == 0 ? A.map0 : A.maps + ct_map_at(A.n, k);
 }
 
+__device__ __forceinline__ uint32_t ct_uniform(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+
 // r[i] <- min(r[i], x), where a read of r[i] gave cur (r only falls, so a
 // stale read can cost an atomic, never lose one).
 __device__ __forceinline__ void lower_dev(uint64_t *r, uint32_t i, uint64_t cur, uint64_t x)
@@ -296,15 +301,24 @@ __device__ __forceinline__ void ct_ends(const CtArgs &A, const uint64_t (&key)[U
     }
 }
 
+// What a small round's last workgroup needs from the counters, read before
+// the pass (only that workgroup changes them).
+struct CtSmall {
+    uint32_t tl1;   // 1 + the phase's first small round, if there was one
+    uint32_t L0;    // that round's vertices (else this one's)
+    uint32_t dead;  // finished trees
+    uint32_t wl;    // weight keys listed
+};
+
 // The rest of round k in one workgroup (at most CT_SMALL vertices): hook,
 // tie break, shortcut and the next round's numbers, with the targets in LDS.
-__device__ void ct_small_round(const CtArgs &A, int k, uint32_t L, uint32_t *s_h, uint32_t *s_nid,
-                               uint32_t *s_c)
+__device__ void ct_small_round(const CtArgs &A, int k, uint32_t L, const CtSmall &z,
+                               uint32_t *s_h, uint32_t *s_nid, uint32_t *s_c)
 {
     Counters *c = A.cnt;
     const uint32_t tid = threadIdx.x;
     const uint64_t *r = A.r[k & 1];
-    const uint32_t tl1 = load_relaxed_u32(&c->ct.tl[A.ph]);
+    const uint32_t tl1 = z.tl1, dead0 = z.dead, wl0 = z.wl;
     const int tl = tl1 ? (int)tl1 - 1 : k;
     constexpr int IT = (CT_SMALL + CE_NT - 1) / CE_NT;
     uint64_t key[IT];
@@ -331,10 +345,9 @@ __device__ void ct_small_round(const CtArgs &A, int k, uint32_t L, uint32_t *s_h
         if (i < t && s_h[t] == i) s_h[i] = i;
     }
     __syncthreads();
-    const uint32_t dead0 = load_relaxed_u32(&c->ct.dead[A.ph]);
-    const uint32_t wl0 = load_relaxed_u32(&c->ct.wl);
 #pragma unroll
     for (int q = 0; q < IT; ++q) {
+        if (q * CE_NT >= L) break;
         const uint32_t i = q * CE_NT + tid;
         const bool in = i < L, live = in && key[q] != KEY_INF;
         const bool stay = live && s_h[i] == i, dead = in && !live, hook = live && !stay;
@@ -378,8 +391,7 @@ __device__ void ct_small_round(const CtArgs &A, int k, uint32_t L, uint32_t *s_h
     for (uint32_t i = tid; i < L; i += CE_NT) map[i] = s_nid[s_h[i]];
     // the first small round's vertices: what they are now (a single vertex
     // left has no edge: it is a finished tree)
-    const uint32_t L0 = tl1 ? load_relaxed_u32(&c->ct.L[A.ph][tl]) : L;
-    for (uint32_t i = tid; i < L0; i += CE_NT) {
+    for (uint32_t i = tid; i < z.L0; i += CE_NT) {
         const uint32_t x = tl1 ? A.cum[i] : i;
         if (x & CT_DEAD) continue;
         const uint32_t v = s_nid[s_h[x]];
@@ -400,18 +412,16 @@ __device__ void ct_small_round(const CtArgs &A, int k, uint32_t L, uint32_t *s_h
 
 // The remaining rounds of a phase with L <= CT_PAIR vertices in one
 // workgroup, on the minimum keys of their pairs (one pair a thread).
-__device__ void ct_pair_rounds(const CtArgs &A, int k, uint32_t L, uint64_t *s_min, uint32_t *s_h,
-                               uint32_t *s_c)
+__device__ void ct_pair_rounds(const CtArgs &A, int k, uint32_t L, const CtSmall &z,
+                               uint64_t *s_min, uint32_t *s_h, uint32_t *s_c)
 {
     static_assert(CT_PAIR * CT_PAIR == CE_NT, "one pair a thread");
     Counters *c = A.cnt;
     const uint32_t tid = threadIdx.x, i = tid / CT_PAIR, j = tid % CT_PAIR;
     uint32_t *s_comp = s_h + CT_PAIR, *s_id = s_comp + CT_PAIR;
     const uint64_t key = load_relaxed_u64(A.mat + tid);
-    const uint32_t tl1 = load_relaxed_u32(&c->ct.tl[A.ph]);
-    const int tl = tl1 ? (int)tl1 - 1 : k;
-    const uint32_t dead0 = load_relaxed_u32(&c->ct.dead[A.ph]);
-    uint32_t wl = load_relaxed_u32(&c->ct.wl);
+    const uint32_t tl1 = z.tl1, dead0 = z.dead;
+    uint32_t wl = z.wl;
     if (tid < CT_PAIR) s_comp[tid] = tid;
     int rr = k;
     for (;; ++rr) {
@@ -466,8 +476,7 @@ __device__ void ct_pair_rounds(const CtArgs &A, int k, uint32_t L, uint64_t *s_m
         if (tid == 0) s_c[1] = (uint32_t)__popcll(mk);
     }
     __syncthreads();
-    const uint32_t L0 = tl1 ? load_relaxed_u32(&c->ct.L[A.ph][tl]) : L;
-    for (uint32_t q = tid; q < L0; q += CE_NT) {
+    for (uint32_t q = tid; q < z.L0; q += CE_NT) {
         const uint32_t x = tl1 ? A.cum[q] : q;
         if (!(x & CT_DEAD)) A.cum[q] = CT_DEAD | s_id[s_comp[x]];
     }
@@ -713,6 +722,17 @@ __device__ __forceinline__ uint32_t ct_pass(const CtArgs &A, int k, uint32_t L,
     return live;
 }
 
+// Whether the edge pass's last workgroup finishes a round of L vertices: from
+// CT_SMALL down, as one compute unit's scattered reads (eight or so a vertex,
+// one a cycle) are slower than two more launches above CT_FINISH, only if
+// those launches follow (3000 vertices, grid 60^3: 26 us alone, 14 us by hook
+// and chase; 1000: 11 us alone).  From a phase's first such round on all are
+// (the maps since are composed into one).
+__device__ __forceinline__ bool ct_one_finishes(uint32_t L, uint32_t tl1, bool big)
+{
+    return L <= (big && !tl1 ? CT_FINISH : CT_SMALL);
+}
+
 // (two workgroups on a compute unit: at most 64 registers)
 template <bool FIRST>
 __global__ __launch_bounds__(CE_NT, 8) void k_ct_edges(CtArgs A, int k, int big)
@@ -732,7 +752,11 @@ __global__ __launch_bounds__(CE_NT, 8) void k_ct_edges(CtArgs A, int k, int big)
     if (c->err || L == 0 || (L > CT_SMALL && !big)) return;
     if (k > 0 ? !c->ct.done[A.ph][k - 1] : (A.ph > 0 && !c->ct.phdone[A.ph - 1])) return;
     if (c->ct.done[A.ph][k]) return;
-    const uint32_t tl1 = c->ct.tl[A.ph];
+    const uint32_t tl1 = ct_uniform(c->ct.tl[A.ph]);
+    // (in scalar registers)
+    const CtSmall z{tl1, ct_uniform(tl1 ? c->ct.L[A.ph][tl1 - 1] : L),
+                    ct_uniform(c->ct.dead[A.ph]), ct_uniform(c->ct.wl)};
+    const bool finish = ct_one_finishes(L, tl1, big);
     const int lane = __lane_id();
     const uint32_t tid = threadIdx.x;
     if (blockIdx.x == 0 && tid == 0) c->ct.ran[A.ph][k] = 1;
@@ -742,8 +766,7 @@ __global__ __launch_bounds__(CE_NT, 8) void k_ct_edges(CtArgs A, int k, int big)
     if (FIRST) {
         out = ct_pass<CT_ENDS>(A, k, L, nullptr, nullptr, r, s_r, s_tag, s_num, s_c);
     } else if (tl1 && k >= (int)tl1) {
-        const uint32_t L0 = c->ct.L[A.ph][tl1 - 1];
-        for (uint32_t i = tid; i < L0; i += CE_NT) s_cum[i] = (uint16_t)min(A.cum[i], 0xFFFFu);
+        for (uint32_t i = tid; i < z.L0; i += CE_NT) s_cum[i] = (uint16_t)min(A.cum[i], 0xFFFFu);
         __syncthreads();
         out = ct_pass<CT_CUM>(A, k, L, nullptr, s_cum, r, s_r, s_tag, s_num, s_c);
     } else {
@@ -758,13 +781,13 @@ __global__ __launch_bounds__(CE_NT, 8) void k_ct_edges(CtArgs A, int k, int big)
         // waited for (13 ns each on one address) only where it is needed
         unsigned long long *tick = (unsigned long long *)&c->ct.tick[A.ph][k];
         const unsigned long long add = ((unsigned long long)t << 16) | 1u;
-        if (L > CT_SMALL) {
+        if (!finish) {
             if (tid == 0) atomicAdd(tick, add);
         } else if (tid == 0) {
             s_c[1] = (uint32_t)(atomicAdd(tick, add) & 0xFFFFu);
         }
     }
-    if (L > CT_SMALL) return;
+    if (!finish) return;
     // The last workgroup of a small round finishes it.  It reads only r (or
     // the matrix), which is written by device-scope atomics alone: each wave
     // waits for its own before the ticket (a release fence would write back
@@ -775,9 +798,9 @@ __global__ __launch_bounds__(CE_NT, 8) void k_ct_edges(CtArgs A, int k, int big)
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     __syncthreads();
     if (L <= CT_PAIR)
-        ct_pair_rounds(A, k, L, s_r, reinterpret_cast<uint32_t *>(s_cum), s_c);
+        ct_pair_rounds(A, k, L, z, s_r, reinterpret_cast<uint32_t *>(s_cum), s_c);
     else
-        ct_small_round(A, k, L, reinterpret_cast<uint32_t *>(s_r),
+        ct_small_round(A, k, L, z, reinterpret_cast<uint32_t *>(s_r),
                        reinterpret_cast<uint32_t *>(s_r) + CT_SMALL, s_c);
 }
 
@@ -787,7 +810,7 @@ __global__ __launch_bounds__(CE_NT, 8) void k_ct_edges(CtArgs A, int k, int big)
 __device__ __forceinline__ bool ct_big_round(const CtArgs &A, int k, uint32_t L)
 {
     const Counters *c = A.cnt;
-    return L > CT_SMALL && !c->err && c->ct.ran[A.ph][k];
+    return !ct_one_finishes(L, c->ct.tl[A.ph], true) && !c->err && c->ct.ran[A.ph][k];
 }
 
 // Hook, tie break, forest flags, weights, and the numbers of the vertices
@@ -957,7 +980,7 @@ void ct_round(hipStream_t s, const CtArgs &A, int k, bool big, uint32_t bound)
     const unsigned g = (A.ph ? A.W : A.pass_waves) / CE_WV;
     if (k == 0) k_ct_edges<true><<<g, CE_NT, 0, s>>>(A, k, big);
     else k_ct_edges<false><<<g, CE_NT, 0, s>>>(A, k, big);
-    if (!big || bound <= CT_SMALL) return;
+    if (!big || bound <= CT_FINISH) return;
     const unsigned t = grid_for(bound, 2 * TIE_NT, CT_WSLOTS);
     if (A.wt == MSF_W_F32) k_ct_hook<MSF_W_F32><<<t, TIE_NT, 0, s>>>(A, k);
     else k_ct_hook<MSF_W_U32><<<t, TIE_NT, 0, s>>>(A, k);

@@ -85,11 +85,11 @@ hipError_t launch_persist(hipStream_t s, const PersistArgs &A, const PersistCfg 
 
 // The one-workgroup path's share where the contracted rounds are the other
 // choice: edges + 2 * vertices.  One workgroup takes about 1.5-2 us per 1000
-// of them, the contracted rounds 140-230 us at these sizes, mostly launches.
-// One workgroup / contracted rounds, us a solve by vertices and edges: 8000,
-// 16000: 112 / 179; 8000, 48000: 154 / 164; 16000, 32000: 166 / 201; 12000,
-// 48000: 176 / 178; 3000, 64000: 152 / 136; 8000, 64000: 181 / 164; 24000,
-// 48000: 243 / 231; 5000, 96000: 206 / 158; 1000, 128000: 188 / 124.
+// of them, the contracted rounds 100-140 us at these sizes, mostly launches
+// and dependent steps.  One workgroup / contracted rounds, us a solve by
+// vertices and edges: 8000, 16000: 90 / 126; grid 20^3, 22K: 110 / 120; 24000,
+// 20000: 143 / 160; 8000, 48000: 130 / 129; 16000, 32000: 143 / 141; 12000,
+// 40000: 142 / 137; 1000, 64000: 101 / 92; R-MAT s12, 58K: 134 / 100.
 constexpr int64_t SMALL_WORK = 68000;
 
 // Whether msf_solve takes the one-workgroup path for this graph: at most

@@ -227,16 +227,16 @@ static msf_status contract_args(Ctx *c, CtArgs *A)
 
 // Enqueue a phase's rounds from round k0 on (bound: the most vertices that
 // round can have, expect: those it is likely to have).  A round of the light
-// edges keeps about a quarter of its vertices, at most half, and five more
-// take CT_SMALL to one; in phase 1 most vertices hook onto the largest tree
-// and few are left after a round.  A launch with nothing to do takes 5 us; a
-// phase that needs more rounds goes on after a host step (25 us).
+// edges keeps about a quarter of its vertices, at most half, and four more
+// take CT_FINISH to one; in phase 1 most vertices hook onto the largest tree
+// and few are left after a round.  A launch with nothing to do takes 2-5 us;
+// a phase that needs more rounds goes on after a host step (25 us).
 static msf_status contract_rounds(Ctx *c, const CtArgs &A, int k0, uint32_t bound, double expect)
 {
     const int end = CT_ROUNDS - 2;
-    int small = A.ph ? 3 : 5;
+    int small = A.ph ? 3 : 4;
     for (int k = k0; k < end && small > 0; ++k, expect /= A.ph ? 8.0 : 4.0) {
-        const bool big = expect > CT_SMALL;
+        const bool big = expect > CT_FINISH;
         if (!big) --small;
         ct_round(c->stream, A, k, big, bound >> (k - k0));
     }
@@ -265,12 +265,20 @@ static msf_status contract_enqueue(Ctx *c, int ph, int k0, uint32_t bound)
     return end_step(c, 8);
 }
 
+// Edges up to which one phase takes them all: a second phase costs some ten
+// launches and dependent steps, about 35 us, which the shorter passes only
+// give back above this (two phases / one, us a solve by vertices and edges:
+// R-MAT s14, 244K 158 / 130; 64000, 200K 210 / 176; 30000, 300K 181 / 167;
+// R-MAT s16, 488K 188 / 173; 10^5, 500K 236 / 239; 20000, 600K 184 / 195;
+// grid 60^3, 605K 283 / 240; 200K, 800K 302 / 380; R-MAT s16, 975K 204 / 218).
+constexpr int64_t CT_ONE_PHASE = (int64_t)1 << 19;
+
 static msf_status contract_start(Ctx *c)
 {
     SolveState &S = c->ss;
     const int64_t tiles = (S.m + CT_TILE - 1) / CT_TILE;
     const int64_t light = contract_light(S.n, S.m);
-    S.two_phase = light * 2 <= S.m;
+    S.two_phase = S.m > CT_ONE_PHASE && light * 2 <= S.m;
     // the passes over the input want two workgroups of 16 waves on each
     // compute unit, those over the list one, up to 2^23 edges (4096 / 8192
     // waves: R-MAT s22 2.15 / 2.21 ms, grid 256^3 3.81 / 3.67 ms)

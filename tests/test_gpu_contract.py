@@ -174,6 +174,33 @@ def test_default_route_and_bad_input(pkg):
     c.close()
 
 
+@pytest.mark.parametrize("n,m", [(9000, 1 << 19), (9000, (1 << 19) + 1), (200, (1 << 19) + 1),
+                                 (240000, (1 << 19) + 1), (7680, 600000), (7681, 600000),
+                                 (2048, 600000), (2049, 600000)])
+def test_one_or_two_phases(ctx, n, m):
+    """One phase up to 2^19 edges, light edges first above (with more than
+    two edges a light one); vertices around the sizes where one workgroup
+    finishes a round."""
+    rng = np.random.default_rng(n + m)
+    e = rng.integers(0, n, size=(m, 2)).astype(np.int32)
+    check(ctx, n, e, rng.integers(0, 1 << 32, size=m, dtype=np.uint64).astype(np.uint32), U32,
+          "phases, u32")
+    check(ctx, n, e, rng.integers(0, 3, size=m).astype(np.uint32), U32, "phases, three weights")
+
+
+def test_more_rounds_than_enqueued_two_phases(ctx):
+    """The ruler path above the line: in the first phase, and left to the
+    second one by lighter loops."""
+    n, e, w = ruler(1 << 17)
+    e6 = np.concatenate([e] * 6)
+    w6 = np.concatenate([w] + [w + 40 + 10 * k for k in range(5)]).astype(np.uint32)
+    check(ctx, n, e6, w6, U32, "ruler path with five parallel edges each")
+    loops = np.stack([np.arange(n), np.arange(n)], 1).astype(np.int32)
+    e7 = np.concatenate([loops] * 5 + [e])
+    w7 = np.concatenate([np.zeros(5 * n), w + 100]).astype(np.uint32)
+    check(ctx, n, e7, w7, U32, "ruler path among many light loops")
+
+
 @pytest.mark.parametrize("n,m,path", [(1000, 66000, 1), (1000, 66001, 4), (22000, 24000, 1),
                                       (22000, 24001, 4), (33999, 2, 1), (34000, 1, 4)])
 def test_one_workgroup_line(pkg, n, m, path):
