@@ -326,8 +326,13 @@ msf_status solve_small(Ctx *c, int32_t n, int64_t m, const int32_t *d_edges, con
     A.out = d_ids;
     A.scratch = (uint8_t *)vscr;
     A.slot_bytes = persist_slot_bytes((uint32_t)n, (uint32_t)m);
-    A.lds_bytes = SMALL_LDS;
-    MSF_HIP(launch_persist(s, A, PersistCfg{1024, 4, SMALL_LDS}, (int)wt, 1, false));
+    // the fewest threads whose registers hold the edges (a barrier of four
+    // waves is cheaper than one of sixteen), else the most
+    PersistCfg cfg{1024, 4, SMALL_LDS};
+    for (const PersistCfg &f : {PersistCfg{256, 4, 32u << 10}, PersistCfg{512, 4, 64u << 10}})
+        if (cfg.nt == 1024 && persist_in_registers((uint32_t)n, (uint32_t)m, f.nt, f.lds)) cfg = f;
+    A.lds_bytes = cfg.lds;
+    MSF_HIP(launch_persist(s, A, cfg, (int)wt, 1, false));
     MSF_HIP(hipStreamSynchronize(s));
     const SmallOut *h = c->hsmall;
     if ((rc = decode_err(h->err))) return rc;

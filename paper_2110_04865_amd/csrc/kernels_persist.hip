@@ -18,11 +18,13 @@
 //   shortcut  complete shortcutting (section 4.2), then new numbers for the
 //             roots that can still hook;
 //   stop      when no live edge is left.
-// Once 128 or fewer vertices are left, one pass takes the minimum key of
-// every pair of them into a matrix in LDS and the remaining rounds run on
-// that.  From PERSIST_TWO_PHASE_M edges on the lightest edges go first (see
-// kernels_contract.hip): their forest is built, one pass over the graph
-// drops every edge inside one of its trees, and a second phase finishes.
+// Once few edges are left (persist_rq a thread) they move to registers and the
+// remaining rounds touch LDS alone; with 128 or fewer vertices and more edges,
+// one pass first takes the minimum key of every pair of vertices into a matrix
+// in LDS.  A graph that has so few edges from the start never leaves the chip
+// (solve_registers).  From PERSIST_TWO_PHASE_M edges on the lightest edges go
+// first (see kernels_contract.hip): their forest is built, one pass over the
+// graph drops every edge inside one of its trees, and a second phase finishes.
 //
 // A round's minima, hook records and map take 10 bytes of LDS per vertex of
 // the round; where that does not fit (the first round of a graph of more
@@ -34,10 +36,15 @@
 // in ascending order from out + vtx_off[g], count and exact totals.
 //
 // Measured on 10^4 Erdos-Renyi graphs (64 to 65536 vertices, 382M edges):
-// 42.3 -> 7.6 ms against the earlier form, which swept the edge list with a
-// parent vector in LDS and the minima in global memory (10.7 cycles an edge
-// visit there, and 23 visits per vertex instead of 9).  It moves 37 GB (27
-// read, 10 written) in that time, 4.8 TB/s: bound by memory.
+// 42.3 ms by an earlier form, which swept the edge list with a parent vector
+// in LDS and the minima in global memory; 7.6 ms by the list; 7.1 ms with the
+// loops over vertices batched (PC_B) and the ids written through LDS.  It
+// moves 22 GB (13 read, 9 written).  The passes over the input run at 4.8
+// TB/s, memory's rate; between them a graph's one workgroup on its compute
+// unit waits for device memory 70% of the time.
+// Smaller graphs, registers against the list before: 10^4 of 1000 vertices
+// and 4000 edges 658 / 576 us, 10^4 of 50 to 2000 vertices and six edges each
+// 698 / 467 us; one graph of 100 vertices and 400 edges 31 / 28 us a solve.
 #include <algorithm>
 #include <map>
 #include <mutex>
@@ -126,6 +133,7 @@ struct PList {
 };
 
 constexpr uint32_t PC_MARK = 0xFFFFFFFFu;
+constexpr uint32_t PC_TREE = 0x80000000u;  // with a tree's number
 constexpr int PC_LEVELS = 40;
 
 // Shared control words of the contracted solve.
@@ -140,9 +148,9 @@ struct PCtl {
     uint32_t err;   // ERR_* seen by this workgroup
     uint32_t gerr;  // the current graph failed validation
     uint32_t off[PC_LEVELS];
-    // rounds on a pair matrix: minima, component and target per vertex
-    uint64_t mr[PC_MAT];
-    uint32_t mc[PC_MAT], mh[PC_MAT];
+    // rounds in registers: hooks and edges of even and odd rounds, flags of
+    // the pointer jumping
+    uint32_t rc[4], rj[3];
 };
 
 // A value that every lane of every wave reads alike, in a scalar register
@@ -151,6 +159,10 @@ struct PCtl {
 __device__ __forceinline__ uint32_t uniform(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+__device__ __forceinline__ int64_t uniform(int64_t v)
+{
+    return (int64_t)(((uint64_t)uniform((uint32_t)(v >> 32)) << 32) | uniform((uint32_t)v));
 }
 
 // Items of a tile: wave w takes the 64 U consecutive ones from 64 U w on,
@@ -177,11 +189,17 @@ __device__ __forceinline__ uint32_t wave_place(uint32_t c, PCtl<NT> &pc, int par
 // A thread's first item (item q is 64 q further).  Opaque, so that each pass
 // computes its own offsets: shared by all the passes inlined into the kernel
 // they cost some 40 registers everywhere.
-template <int U>
-__device__ __forceinline__ uint32_t tile_item0()
+__device__ __forceinline__ uint32_t opaque_tid()
 {
     uint32_t t = threadIdx.x;
     asm volatile("" : "+v"(t));
+    return t;
+}
+
+template <int U>
+__device__ __forceinline__ uint32_t tile_item0()
+{
+    const uint32_t t = opaque_tid();
     return (t >> 6) * (64u * U) + (t & 63u);
 }
 
@@ -367,84 +385,200 @@ __device__ __forceinline__ void hook_records(const PList<P16> list, uint32_t E, 
     __syncthreads();
 }
 
-// The remaining rounds of a graph with L <= 128 vertices on the matrix of
-// its pairs' minimum keys (rows of 1 << sh entries, upper triangle).  Every
-// vertex ends in a finished tree; with did, did[i] = its number.
-template <int NT>
-__device__ __forceinline__ void matrix_rounds(const uint64_t *mat, uint32_t L, int sh,
-                                              uint8_t *flags, uint32_t *did, PCtl<NT> &pc,
-                                              uint32_t *round_hooks, uint32_t &nrounds)
+// The matrix of the pairs' minimum keys (rows of 1 << sh entries, upper
+// triangle) of L vertices as the list: one edge a pair.  Returns the edges.
+template <int NT, bool P16>
+__device__ __forceinline__ uint32_t matrix_list(const uint64_t *mat, uint32_t L, uint32_t sh,
+                                                const PList<P16> list, PCtl<NT> &pc)
 {
-    const uint32_t tid = threadIdx.x, cells = L << sh, colm = (1u << sh) - 1u;
-    if (tid < L) pc.mc[tid] = tid;
-    for (;;) {
-        if (tid < L) pc.mr[tid] = KEY_INF;
-        if (tid == 0) pc.hooks = 0;
-        __syncthreads();
-        for (uint32_t x = tid; x < cells; x += NT) {
-            const uint32_t i = x >> sh, j = x & colm;
-            if (j <= i || j >= L) continue;
-            const uint64_t key = mat[x];
-            const uint32_t a = pc.mc[i], b = pc.mc[j];
-            if (key == KEY_INF || a == b) continue;
-            lower(pc.mr, a, pc.mr[a], key);
-            lower(pc.mr, b, pc.mr[b], key);
+    if (threadIdx.x == 0) pc.hooks = 0;
+    __syncthreads();
+    const uint32_t cells = L << sh, colm = (1u << sh) - 1u;
+    for (uint32_t x0 = threadIdx.x & ~63u; x0 < cells; x0 += NT) {
+        const uint32_t x = x0 + __lane_id();
+        const uint64_t key = x < cells ? mat[x] : KEY_INF;  // (only i < j were lowered)
+        const uint64_t mk = __ballot(key != KEY_INF);
+        if (!mk) continue;
+        uint32_t at = 0;
+        if (__lane_id() == 0) at = atomicAdd(&pc.hooks, (uint32_t)__popcll(mk));
+        at = __shfl(at, 0, 64);
+        if (key != KEY_INF)
+            list.put(at + __popcll(mk & lanemask_lt()),
+                     PEdge{x >> sh, x & colm, (uint32_t)(key >> 32), (uint32_t)key});
+    }
+    __syncthreads();
+    return uniform(pc.hooks);
+}
+
+// All remaining rounds of a graph with at most persist_rq(NT) * NT edges: edges in
+// registers (key, ends in ab; key KEY_INF: none; qa of them a thread), minima
+// and parents of its L vertices in LDS (10 bytes each, from smem on; what is
+// left of its S bytes serves to deal edges out).  The edge that is a root's minimum hooks it (of two roots with the
+// same one the larger), then pointer jumping; an edge whose ends meet is
+// dropped, and the rest are dealt out again when a register fewer a thread
+// holds them.  forest(key) is called for every forest edge; with did, did[v]
+// = the number of v's tree.  A round takes 1-2 us; through the list it takes
+// a pass to lower the minima, one to write the hook records and a dozen
+// barriers.
+template <int NT, typename F>
+__device__ __forceinline__ void register_rounds(uint64_t (&key)[persist_rq(NT)], uint32_t (&ab)[persist_rq(NT)],
+                                                int qa, uint32_t L, uint8_t *smem, size_t S,
+                                                F forest, uint32_t *did, PCtl<NT> &pc,
+                                                uint32_t *round_hooks, uint32_t &nrounds)
+{
+    constexpr int Q = persist_rq(NT);
+    const uint32_t lane = __lane_id();
+    uint64_t *r = reinterpret_cast<uint64_t *>(smem);
+    uint16_t *par = reinterpret_cast<uint16_t *>(smem + 8 * (size_t)L);
+    const size_t used = (10 * (size_t)L + 15) & ~(size_t)15;
+    uint64_t *s_key = reinterpret_cast<uint64_t *>(smem + used);
+    const uint32_t stage = (uint32_t)((S - used) / 12);  // edges there is room to deal out
+    for (uint32_t v = opaque_tid(); v < L; v += NT) {
+        par[v] = (uint16_t)v;
+        r[v] = KEY_INF;
+    }
+    if (threadIdx.x < 4) pc.rc[threadIdx.x] = 0;
+    if (threadIdx.x < 3) pc.rj[threadIdx.x] = 0;
+    __syncthreads();
+    uint32_t jump = 0;
+    for (uint32_t p = 0;; p ^= 1) {  // rc[p]: this round's hooks, rc[2 + p]: its edges
+        uint32_t mine = 0, at = 0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (q >= qa) continue;
+            if (key[q] != KEY_INF) {
+                const uint32_t a = par[ab[q] & 0xFFFFu], b = par[ab[q] >> 16];
+                if (a == b) key[q] = KEY_INF;
+                ab[q] = a | (b << 16);
+            }
+            mine += (uint32_t)__popcll(__ballot(key[q] != KEY_INF));
         }
+        if (lane == 0 && mine) at = atomicAdd(&pc.rc[2 + p], mine);
         __syncthreads();
-        // keys are distinct: exactly one pair has each minimum
-        for (uint32_t x = tid; x < cells; x += NT) {
-            const uint32_t i = x >> sh, j = x & colm;
-            if (j <= i || j >= L) continue;
-            const uint64_t key = mat[x];
-            const uint32_t a = pc.mc[i], b = pc.mc[j];
-            if (key == KEY_INF || a == b) continue;
-            if (pc.mr[a] == key) pc.mh[a] = b;
-            if (pc.mr[b] == key) pc.mh[b] = a;
-        }
-        __syncthreads();
-        bool hook = false;
-        if (tid < L && pc.mc[tid] == tid) {
-            const uint64_t key = pc.mr[tid];
-            if (key == KEY_INF) {
-                pc.mh[tid] = tid;
-            } else {
-                const uint32_t t = pc.mh[tid];
-                // (the larger of a mutual pair never reverts)
-                if (tid < t && pc.mh[t] == tid) {
-                    pc.mh[tid] = tid;
-                } else {
-                    flags[(uint32_t)key] = 1;
-                    hook = true;
+        const uint32_t live = uniform(pc.rc[2 + p]);
+        const int qn = (int)((live + NT - 1) / NT);
+        if (qn < qa && live <= stage) {
+            uint32_t *s_ab = reinterpret_cast<uint32_t *>(s_key + stage);
+            at = __shfl(at, 0, 64);
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const uint64_t mk = __ballot(key[q] != KEY_INF);
+                if (key[q] != KEY_INF) {
+                    const uint32_t i = at + __popcll(mk & lanemask_lt());
+                    s_key[i] = key[q];
+                    s_ab[i] = ab[q];
+                }
+                at += (uint32_t)__popcll(mk);
+            }
+            __syncthreads();
+            qa = qn;
+            const uint32_t i0 = opaque_tid();
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const uint32_t i = q * NT + i0;
+                key[q] = KEY_INF;
+                if (q < qa && i < live) {
+                    key[q] = s_key[i];
+                    ab[q] = s_ab[i];
                 }
             }
         }
-        const uint64_t mk = __ballot(hook);
-        if (__lane_id() == 0 && mk) atomicAdd(&pc.hooks, (uint32_t)__popcll(mk));
-        __syncthreads();
-        const uint32_t hooks = uniform(pc.hooks);
-        if (!hooks) break;
-        if (round_hooks && tid == 0 && nrounds < 64) round_hooks[nrounds] = hooks;
-        ++nrounds;
-        uint32_t x = 0;
-        if (tid < L) {
-            x = pc.mc[tid];
-            while (pc.mh[x] != x) x = pc.mh[x];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (q >= qa || key[q] == KEY_INF) continue;
+            const uint32_t a = ab[q] & 0xFFFFu, b = ab[q] >> 16;
+            const uint64_t ra = r[a], rb = r[b];
+            lower(r, a, ra, key[q]);
+            lower(r, b, rb, key[q]);
         }
         __syncthreads();
-        if (tid < L) pc.mc[tid] = x;
+        // keys are distinct: one edge has each minimum
+        uint32_t hooks = 0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (q >= qa) continue;
+            bool wa = false, wb = false;
+            if (key[q] != KEY_INF) {
+                const uint32_t a = ab[q] & 0xFFFFu, b = ab[q] >> 16;
+                wa = r[a] == key[q];
+                wb = r[b] == key[q];
+                if (wa && (!wb || a > b)) par[a] = (uint16_t)b;
+                else if (wb) par[b] = (uint16_t)a;
+                if (wa || wb) forest(key[q]);
+            }
+            hooks += (uint32_t)__popcll(__ballot(wa || wb));
+        }
+        if (lane == 0 && hooks) atomicAdd(&pc.rc[p], hooks);
+        __syncthreads();
+        hooks = uniform(pc.rc[p]);
+        if (!hooks) break;
+        if (threadIdx.x == 0) {
+            pc.rc[1 - p] = pc.rc[3 - p] = 0;
+            if (round_hooks && nrounds < 64) round_hooks[nrounds] = hooks;
+        }
+        ++nrounds;
+        // pointer jumping in place (a value read is always an ancestor)
+        for (bool first = true;; first = false) {
+            bool any = false;
+            for (uint32_t v = opaque_tid(); v < L; v += NT) {
+                const uint32_t x = par[v], z = par[par[x]];
+                if (z != x) {
+                    par[v] = (uint16_t)z;
+                    any = true;
+                }
+                if (first) r[v] = KEY_INF;
+            }
+            if (any) pc.rj[jump] = 1;
+            const uint32_t next = jump == 2 ? 0 : jump + 1;
+            if (threadIdx.x == 0) pc.rj[next] = 0;
+            __syncthreads();
+            const uint32_t more = uniform(pc.rj[jump]);
+            jump = next;
+            if (!more) break;
+        }
     }
     if (did) {
         // numbers of the trees, by their roots
-        const bool root = tid < L && pc.mc[tid] == tid;
-        const uint64_t mk = __ballot(root);
-        uint32_t at = 0;
-        if (__lane_id() == 0 && mk) at = atomicAdd(&pc.dead, (uint32_t)__popcll(mk));
-        at = __shfl(at, 0, 64);
-        if (root) pc.mh[tid] = at + __popcll(mk & lanemask_lt());
+        uint32_t *s_id = reinterpret_cast<uint32_t *>(smem);
+        for (uint32_t v0 = opaque_tid() & ~63u; v0 < L; v0 += NT) {
+            const uint32_t v = v0 + lane;
+            const bool root = v < L && par[v] == v;
+            const uint64_t mk = __ballot(root);
+            uint32_t at = 0;
+            if (lane == 0 && mk) at = atomicAdd(&pc.dead, (uint32_t)__popcll(mk));
+            at = __shfl(at, 0, 64);
+            if (root) s_id[v] = at + __popcll(mk & lanemask_lt());
+        }
         __syncthreads();
-        if (tid < L) did[tid] = pc.mh[pc.mc[tid]];
+        for (uint32_t v = opaque_tid(); v < L; v += NT) did[v] = s_id[par[v]];
     }
     __syncthreads();
+}
+
+// The same for the edges on the list, with the forest flags in the slot.
+template <int NT, bool P16>
+__device__ __forceinline__ void list_rounds(const PList<P16> list, uint32_t E, uint32_t L,
+                                            uint8_t *smem, size_t S, uint8_t *flags,
+                                            uint32_t *did, PCtl<NT> &pc, uint32_t *round_hooks,
+                                            uint32_t &nrounds)
+{
+    const uint32_t tid = opaque_tid();
+    uint64_t key[persist_rq(NT)];
+    uint32_t ab[persist_rq(NT)];
+    const int qa = (int)uniform((E + NT - 1) / NT);
+#pragma unroll
+    for (int q = 0; q < persist_rq(NT); ++q) {
+        key[q] = KEY_INF;
+        ab[q] = 0;
+        if (q >= qa) continue;
+        const uint32_t j = q * NT + tid;
+        const PEdge x = list.get(min(j, E - 1));
+        ab[q] = x.a | (x.b << 16);
+        if (j < E) key[q] = ((uint64_t)x.w << 32) | x.e;
+    }
+    register_rounds<NT>(key, ab, qa, L, smem, S,
+                        [=](uint64_t k) { flags[(uint32_t)k] = 1; }, did, pc, round_hooks,
+                        nrounds);
 }
 
 // Targets of a round's vertices: 16-bit in LDS, or the x words of the hook
@@ -472,6 +606,11 @@ struct HRec {
     }
 };
 
+// Loops over a graph's vertices in device memory: items of a thread whose
+// loads are issued together.  One at a time, such a loop takes a load's
+// latency, 1-2 us, per NT vertices (40000 vertices, 1024 threads: 60 us).
+constexpr int PC_B = 4;
+
 // Tie break and shortcut over the targets h of a round's L vertices and the
 // hooked edges in rec[i].y (PC_MARK: no edge).  Afterwards h[i] is i's root,
 // and rec[root].y the root's number in the next round; a vertex without an
@@ -483,16 +622,23 @@ __device__ __forceinline__ void tie_and_chase(const H h, uint2 *rec, uint32_t L,
     if (threadIdx.x == 0) pc.live = pc.hooks = 0;
     __syncthreads();
     uint32_t kept = 0;
-    for (uint32_t i = threadIdx.x; i < L; i += NT) {
-        const uint32_t e = rec[i].y;
-        if (e == PC_MARK) continue;
-        const uint32_t t = h.get(i);
-        // the larger of a mutual pair never reverts, whatever it reads
-        if (i < t && h.get(t) == i) {
-            h.set(i, i);
-        } else {
-            flags[e] = 1;
-            ++kept;
+    for (uint32_t i0 = opaque_tid(); i0 < L; i0 += PC_B * NT) {
+        uint32_t e[PC_B], t[PC_B];
+#pragma unroll
+        for (int q = 0; q < PC_B; ++q) e[q] = rec[min(i0 + q * NT, L - 1)].y;
+#pragma unroll
+        for (int q = 0; q < PC_B; ++q) t[q] = h.get(min(i0 + q * NT, L - 1));
+#pragma unroll
+        for (int q = 0; q < PC_B; ++q) {
+            const uint32_t i = i0 + q * NT;
+            if (i >= L || e[q] == PC_MARK) continue;
+            // the larger of a mutual pair never reverts, whatever it reads
+            if (i < t[q] && h.get(t[q]) == i) {
+                h.set(i, i);
+            } else {
+                flags[e[q]] = 1;
+                ++kept;
+            }
         }
     }
     kept = wave_sum(kept);
@@ -511,20 +657,67 @@ __device__ __forceinline__ void tie_and_chase(const H h, uint2 *rec, uint32_t L,
     }
     __syncthreads();
     // numbers: roots with an edge from 0, finished trees from pc.dead
-    for (uint32_t base = 0; base < L; base += NT) {
-        const uint32_t i = base + threadIdx.x;
-        const bool root = i < L && h.get(i) == i;
-        const bool dead = root && rec[i].y == PC_MARK, stay = root && !dead;
-        const uint64_t ms = __ballot(stay), md = __ballot(dead);
-        uint32_t as = 0, ad = 0;
+    for (uint32_t base = 0; base < L; base += PC_B * NT) {
+        const uint32_t i0 = base + opaque_tid();
+        bool root[PC_B];
+        uint32_t y[PC_B];
+#pragma unroll
+        for (int q = 0; q < PC_B; ++q) {
+            const uint32_t i = i0 + q * NT;
+            root[q] = i < L && h.get(i) == i;
+            y[q] = PC_MARK;
+            if (root[q]) y[q] = rec[i].y;
+        }
+        uint64_t ms[PC_B], md[PC_B];
+        uint32_t cs = 0, cd = 0, as = 0, ad = 0;
+#pragma unroll
+        for (int q = 0; q < PC_B; ++q) {
+            ms[q] = __ballot(root[q] && y[q] != PC_MARK);
+            md[q] = __ballot(root[q] && y[q] == PC_MARK);
+            cs += (uint32_t)__popcll(ms[q]);
+            cd += (uint32_t)__popcll(md[q]);
+        }
         if (__lane_id() == 0) {
-            if (ms) as = atomicAdd(&pc.live, (uint32_t)__popcll(ms));
-            if (md && did) ad = atomicAdd(&pc.dead, (uint32_t)__popcll(md));
+            if (cs) as = atomicAdd(&pc.live, cs);
+            if (cd && did) ad = atomicAdd(&pc.dead, cd);
         }
         as = __shfl(as, 0, 64);
         ad = __shfl(ad, 0, 64);
-        if (stay) rec[i].y = as + __popcll(ms & lanemask_lt());
-        if (dead && did) did[i] = ad + __popcll(md & lanemask_lt());
+#pragma unroll
+        for (int q = 0; q < PC_B; ++q) {
+            const uint32_t i = i0 + q * NT;
+            if (root[q] && y[q] != PC_MARK) rec[i].y = as + __popcll(ms[q] & lanemask_lt());
+            if (root[q] && y[q] == PC_MARK && did) did[i] = ad + __popcll(md[q] & lanemask_lt());
+            as += (uint32_t)__popcll(ms[q]);
+            ad += (uint32_t)__popcll(md[q]);
+        }
+    }
+    __syncthreads();
+}
+
+// A graph's count (minus its error flags if it failed validation) and totals.
+template <int NT, int WT>
+__device__ __forceinline__ void graph_results(const PersistArgs &A, uint32_t g, WSum &ws,
+                                              bool failed, uint32_t err, uint32_t pos,
+                                              PCtl<NT> &pc, int64_t *s_sum, int64_t *s_tot)
+{
+    wsum_block<NT, WT>(ws, s_sum, s_tot, 1);
+    if (err) atomicOr(&pc.err, err);
+    if (threadIdx.x == 0) {
+        const int64_t count = failed ? -(int64_t)pc.gerr : (int64_t)pos;
+        const uint64_t tu = WT == MSF_W_U32 ? (uint64_t)s_tot[0] : 0;
+        const double tf = exact_total_f64((uint64_t)s_tot[0], s_tot + 1,
+                                          (uint32_t)s_tot[1 + ACC_DIGITS],
+                                          (uint32_t)s_tot[2 + ACC_DIGITS], WT);
+        if (A.one_out) {
+            A.one_out->count = count;
+            A.one_out->tot_u64 = tu;
+            A.one_out->tot_f64 = tf;
+        } else {
+            A.counts[g] = count;
+            A.tot_u64[(size_t)g * A.tot_stride] = tu;
+            A.tot_f64[(size_t)g * A.tot_stride] = tf;
+        }
     }
     __syncthreads();
 }
@@ -537,10 +730,10 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
 {
     const uint32_t tid = threadIdx.x;
     const bool one = A.one_out != nullptr;
-    const int64_t v0 = one ? 0 : A.vtx_off[g];
-    const uint32_t n = (uint32_t)(one ? A.one_n : A.vtx_off[g + 1] - v0);
-    const int64_t e0 = one ? 0 : A.edge_off[g];
-    const uint32_t m = (uint32_t)(one ? A.one_m : A.edge_off[g + 1] - e0);
+    const int64_t v0 = one ? 0 : uniform(A.vtx_off[g]);
+    const uint32_t n = uniform((uint32_t)(one ? A.one_n : A.vtx_off[g + 1] - v0));
+    const int64_t e0 = one ? 0 : uniform(A.edge_off[g]);
+    const uint32_t m = uniform((uint32_t)(one ? A.one_m : A.edge_off[g + 1] - e0));
     const int2 *E = reinterpret_cast<const int2 *>(A.edges) + e0;
     const uint32_t *W = A.w + e0;
     const size_t S = A.lds_bytes;
@@ -601,7 +794,7 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
     // the first round's minima in the same pass where they fit LDS
     uint64_t *r = reinterpret_cast<uint64_t *>(smem);
     uint32_t Ec = 0, err = 0;
-    bool ready = 10 * (size_t)n + 16 <= S;
+    bool ready = 10 * (size_t)n + 16 <= S && m > persist_rq(NT) * NT;
     if (ready)
         for (uint32_t i = tid; i < n; i += NT) r[i] = KEY_INF;
     __syncthreads();
@@ -666,22 +859,67 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
         uint32_t L = n, off = 0;
         int lev = 0;
         if (ph == 1) {
-            // a tree number per vertex: from the last level's vertices down
-            for (int k = (int)uniform(pc.bin) - 2; k >= 0; --k) {
+            // a tree number per vertex (at the top of LDS where they fit): the
+            // later levels' maps and tree numbers in LDS, as many as there is
+            // room for, where a chain is followed without a barrier; the levels
+            // before them one by one, each from the level after it (a level by
+            // itself takes two dependent reads and a barrier, 3 us: a third of
+            // the time of a graph of 1000 vertices)
+            const bool lds = 2 * ((size_t)n + 8) <= S && n <= 65536u;
+            uint16_t *c16 = reinterpret_cast<uint16_t *>(smem + S) - ((n + 7) & ~7u);
+            uint32_t *lm = reinterpret_cast<uint32_t *>(smem);
+            const int nl = (int)uniform(pc.bin);
+            const uint32_t room = (uint32_t)((lds ? S - 2 * ((size_t)n + 8) : S) / 4);
+            int k1 = 1;
+            while (uniform(pc.off[nl]) - uniform(pc.off[k1]) > room) ++k1;
+            const uint32_t base1 = uniform(pc.off[k1]);
+            for (int k = k1; k < nl; ++k) {
+                const uint32_t ok = uniform(pc.off[k]), o1 = uniform(pc.off[k + 1]);
+                for (uint32_t i0 = ok + opaque_tid(); i0 < o1; i0 += PC_B * NT) {
+                    uint32_t x[PC_B], d[PC_B];
+#pragma unroll
+                    for (int q = 0; q < PC_B; ++q) {
+                        x[q] = mapg[min(i0 + q * NT, o1 - 1)];
+                        d[q] = didg[min(i0 + q * NT, o1 - 1)];
+                    }
+#pragma unroll
+                    for (int q = 0; q < PC_B; ++q)
+                        if (i0 + q * NT < o1)
+                            lm[i0 + q * NT - base1] =
+                                x[q] == PC_MARK ? PC_TREE | d[q] : o1 - base1 + x[q];
+                }
+            }
+            __syncthreads();
+            for (int k = k1 - 1; k >= 0; --k) {
                 const uint32_t ok = uniform(pc.off[k]), o1 = uniform(pc.off[k + 1]), Lk = o1 - ok;
-                for (uint32_t i = tid; i < Lk; i += NT) {
-                    const uint32_t x = mapg[ok + i];
-                    if (x != PC_MARK) didg[ok + i] = didg[o1 + x];
+                for (uint32_t i0 = opaque_tid(); i0 < Lk; i0 += PC_B * NT) {
+                    uint32_t x[PC_B], d[PC_B];
+#pragma unroll
+                    for (int q = 0; q < PC_B; ++q) x[q] = mapg[ok + min(i0 + q * NT, Lk - 1)];
+#pragma unroll
+                    for (int q = 0; q < PC_B; ++q) {
+                        const uint32_t i = min(i0 + q * NT, Lk - 1);
+                        d[q] = x[q];
+                        if (x[q] == PC_MARK || k < k1 - 1)
+                            d[q] = didg[x[q] != PC_MARK ? o1 + x[q] : ok + i];
+                    }
+#pragma unroll
+                    for (int q = 0; q < PC_B; ++q) {
+                        const uint32_t i = i0 + q * NT;
+                        if (i >= Lk) continue;
+                        if (x[q] != PC_MARK && k == k1 - 1) {
+                            uint32_t v = lm[x[q]];
+                            while (!(v & PC_TREE)) v = lm[v];
+                            d[q] = v & ~PC_TREE;
+                        }
+                        if (lds && k == 0) c16[i] = (uint16_t)d[q];
+                        else if (x[q] != PC_MARK) didg[ok + i] = d[q];
+                    }
                 }
                 __syncthreads();
             }
             L = uniform(pc.dead);
             // the edges between different trees, again in edge-id order
-            // (tree numbers at the top of LDS, minima below where both fit)
-            const bool lds = 2 * ((size_t)n + 8) <= S && n <= 65536u;
-            uint16_t *c16 = reinterpret_cast<uint16_t *>(smem + S) - ((n + 7) & ~7u);
-            if (lds)
-                for (uint32_t i = tid; i < n; i += NT) c16[i] = (uint16_t)didg[i];
             ready = lds && 8 * (size_t)L + 2 * ((size_t)n + 8) <= S;
             if (ready)
                 for (uint32_t i = tid; i < L; i += NT) r[i] = KEY_INF;
@@ -751,6 +989,16 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
                 err |= ERR_CYCLE;
                 break;
             }
+            if (Ec <= persist_rq(NT) * NT && 10 * (size_t)L + 16 <= S) {
+                if (tid == 0) pc.off[lev] = off;
+                if (trees)
+                    for (uint32_t i = tid; i < L; i += NT) mapg[off + i] = PC_MARK;
+                list_rounds<NT>(list, Ec, L, smem, S, flags, trees ? didg + off : nullptr, pc,
+                                A.round_hooks, nrounds);
+                if (trees) off += L;
+                ++lev;
+                break;
+            }
             if (10 * (size_t)L + 16 <= S) {
                 // minima, targets, numbers and the map (2 L at the top) in LDS
                 if (!ready) {
@@ -788,13 +1036,27 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
                 }
                 if (2 * ((size_t)L + 8) <= S && L <= 65536u) {
                     uint16_t *map = reinterpret_cast<uint16_t *>(smem + S) - ((L + 7) & ~7u);
-                    for (uint32_t i = tid; i < L; i += NT) map[i] = (uint16_t)rec[i].x;
+                    for (uint32_t i0 = opaque_tid(); i0 < L; i0 += PC_B * NT) {
+                        uint32_t v[PC_B];
+#pragma unroll
+                        for (int q = 0; q < PC_B; ++q) v[q] = rec[min(i0 + q * NT, L - 1)].x;
+#pragma unroll
+                        for (int q = 0; q < PC_B; ++q)
+                            if (i0 + q * NT < L) map[i0 + q * NT] = (uint16_t)v[q];
+                    }
                     __syncthreads();
                     tie_and_chase<NT>(H16{map}, rec, L, flags, trees ? didg + off : nullptr, pc);
-                    for (uint32_t i = tid; i < L; i += NT) {
-                        const uint32_t v = rec[map[i]].y;
-                        map[i] = (uint16_t)v;  // only its own thread reads it now
-                        if (trees) mapg[off + i] = v;
+                    for (uint32_t i0 = opaque_tid(); i0 < L; i0 += PC_B * NT) {
+                        uint32_t v[PC_B];
+#pragma unroll
+                        for (int q = 0; q < PC_B; ++q) v[q] = rec[map[min(i0 + q * NT, L - 1)]].y;
+#pragma unroll
+                        for (int q = 0; q < PC_B; ++q) {
+                            const uint32_t i = i0 + q * NT;
+                            if (i >= L) continue;
+                            map[i] = (uint16_t)v[q];  // only its own thread reads it now
+                            if (trees) mapg[off + i] = v[q];
+                        }
                     }
                 } else {
                     tie_and_chase<NT>(HRec{rec}, rec, L, flags, trees ? didg + off : nullptr, pc);
@@ -812,7 +1074,7 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
             const bool m16 = 2 * ((size_t)L + 8) <= S && L <= 65536u;
             const uint16_t *map = reinterpret_cast<uint16_t *>(smem + S) - ((L + 7) & ~7u);
             const uint32_t sh = Ln <= 32 ? 5u : Ln <= 64 ? 6u : 7u;
-            const bool mat = m16 && Ln > 0 && Ln <= PC_MAT &&
+            const bool mat = m16 && Ln > 0 && Ln <= PC_MAT && Ln * (Ln - 1) <= 2 * persist_rq(NT) * NT &&
                              (8ull * Ln << sh) + 2 * ((size_t)L + 8) <= S;
             ready = m16 && 8 * (size_t)Ln + 2 * ((size_t)L + 8) <= S;
             __syncthreads();
@@ -828,8 +1090,9 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
                     if (tid == 0) pc.off[lev] = off;
                     for (uint32_t i = tid; i < Ln; i += NT) mapg[off + i] = PC_MARK;
                 }
-                matrix_rounds<NT>(r, Ln, (int)sh, flags, trees ? didg + off : nullptr, pc,
-                                  A.round_hooks, nrounds);
+                Ec = matrix_list<NT>(r, Ln, sh, list, pc);
+                list_rounds<NT>(list, Ec, Ln, smem, S, flags, trees ? didg + off : nullptr, pc,
+                                A.round_hooks, nrounds);
                 if (trees) off += Ln;
                 ++lev;
                 break;
@@ -870,48 +1133,140 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
     WSum ws;
     uint32_t pos = 0;
     int32_t *out = A.out + v0;
+    // through LDS, so that the ids leave in whole lines and their weights'
+    // loads go out together (each thread reading the weights of its 16 edges'
+    // one after the other: 91 us for 1024 graphs of 40000 vertices and four
+    // edges each, of 886 us in all)
+    uint16_t *s_id = reinterpret_cast<uint16_t *>(smem);
+    static_assert(16 * NT <= 65536, "places of a tile in 16 bits");
+    uint4 f4 = make_uint4(0u, 0u, 0u, 0u);
+    if (tid < nw && !failed) f4 = fw[tid];
     for (uint32_t base = 0; base < nw && !failed; base += NT) {
-        const uint32_t k = base + tid;
-        const uint4 f4 = k < nw ? fw[k] : make_uint4(0u, 0u, 0u, 0u);
         const uint32_t f[4] = {f4.x, f4.y, f4.z, f4.w};
+        f4 = make_uint4(0u, 0u, 0u, 0u);
+        if (base + NT + tid < nw) f4 = fw[base + NT + tid];  // the next tile's, meanwhile
         const uint32_t c = __popc(f[0]) + __popc(f[1]) + __popc(f[2]) + __popc(f[3]);
         uint32_t total;
-        uint32_t at = pos + block_excl_sum<NT>(c, s_scan, &total);
+        uint32_t at = block_excl_sum<NT>(c, s_scan, &total);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            for (uint32_t bits = f[q]; bits; bits &= bits - 1) {
-                const uint32_t e = 16 * k + 4 * q + (__builtin_ctz(bits) >> 3);
-                out[at++] = (int32_t)e;
-                wsum_add<WT>(ws, weight_key(W[e], WT));
+        for (int q = 0; q < 4; ++q)
+            for (uint32_t bits = f[q]; bits; bits &= bits - 1)
+                s_id[at++] = (uint16_t)(16 * tid + 4 * q + (__builtin_ctz(bits) >> 3));
+        __syncthreads();
+        for (uint32_t i0 = opaque_tid(); i0 < total; i0 += PC_B * NT) {
+            uint32_t e[PC_B], w[PC_B];
+#pragma unroll
+            for (int q = 0; q < PC_B; ++q) e[q] = 16 * base + s_id[min(i0 + q * NT, total - 1)];
+#pragma unroll
+            for (int q = 0; q < PC_B; ++q) w[q] = W[e[q]];
+#pragma unroll
+            for (int q = 0; q < PC_B; ++q) {
+                if (i0 + q * NT >= total) continue;
+                out[pos + i0 + q * NT] = (int32_t)e[q];
+                wsum_add<WT>(ws, weight_key(w[q], WT));
             }
         }
         pos += total;
+        __syncthreads();
     }
-    wsum_block<NT, WT>(ws, s_sum, s_tot, 1);
-    if (err) atomicOr(&pc.err, err);
-    if (tid == 0) {
-        const int64_t count = failed ? -(int64_t)pc.gerr : (int64_t)pos;
-        const uint64_t tu = WT == MSF_W_U32 ? (uint64_t)s_tot[0] : 0;
-        const double tf = exact_total_f64((uint64_t)s_tot[0], s_tot + 1,
-                                          (uint32_t)s_tot[1 + ACC_DIGITS],
-                                          (uint32_t)s_tot[2 + ACC_DIGITS], WT);
-        if (one) {
-            A.one_out->count = count;
-            A.one_out->tot_u64 = tu;
-            A.one_out->tot_f64 = tf;
-        } else {
-            A.counts[g] = count;
-            A.tot_u64[(size_t)g * A.tot_stride] = tu;
-            A.tot_f64[(size_t)g * A.tot_stride] = tf;
-        }
+    graph_results<NT, WT>(A, g, ws, failed, err, pos, pc, s_sum, s_tot);
+}
+
+// The forest of a graph whose edges fit the registers of the workgroup: all
+// rounds on chip, the forest as bits in LDS.  (Through the list and the flags in the slot, a graph of a few
+// hundred edges waits for a dozen dependent device accesses, 1 us each.)
+template <int NT, int WT>
+__device__ __forceinline__ void solve_registers(const PersistArgs &A, uint32_t g, uint8_t *smem,
+                                                PCtl<NT> &pc, int64_t *s_sum, int64_t *s_tot,
+                                                uint32_t *s_scan)
+{
+    const uint32_t tid = opaque_tid();
+    const bool one = A.one_out != nullptr;
+    const int64_t v0 = one ? 0 : uniform(A.vtx_off[g]);
+    const uint32_t n = uniform((uint32_t)(one ? A.one_n : A.vtx_off[g + 1] - v0));
+    const int64_t e0 = one ? 0 : uniform(A.edge_off[g]);
+    const uint32_t m = uniform((uint32_t)(one ? A.one_m : A.edge_off[g + 1] - e0));
+    const int2 *E = reinterpret_cast<const int2 *>(A.edges) + e0;
+    const uint32_t *W = A.w + e0;
+    const int qa = (int)uniform((m + NT - 1) / NT);
+    int2 uv[persist_rq(NT)];
+    uint32_t wb[persist_rq(NT)], ab[persist_rq(NT)];
+    uint64_t key[persist_rq(NT)];
+#pragma unroll
+    for (int q = 0; q < persist_rq(NT); ++q) {
+        if (q >= qa) continue;
+        const uint32_t j = min(q * NT + tid, m - 1);
+        uv[q] = E[j];
+        wb[q] = W[j];
+    }
+    uint32_t *bits = reinterpret_cast<uint32_t *>(smem);
+    constexpr uint32_t BYTES = persist_rq(NT) * NT / 8;
+    for (uint32_t i = opaque_tid(); i < BYTES / 4; i += NT) bits[i] = 0;
+    if (threadIdx.x == 0) {
+        pc.gerr = 0;
+        pc.dead = 0;
     }
     __syncthreads();
+    uint32_t err = 0;
+#pragma unroll
+    for (int q = 0; q < persist_rq(NT); ++q) {
+        key[q] = KEY_INF;
+        ab[q] = 0;
+        if (q >= qa) continue;
+        const uint32_t j = q * NT + tid, a = (uint32_t)uv[q].x, b = (uint32_t)uv[q].y;
+        uint32_t bad = a >= n || b >= n ? ERR_ENDPOINT : 0u;
+        if (WT == MSF_W_F32 && (wb[q] & 0x7FFFFFFFu) > 0x7F800000u) bad |= ERR_NAN;
+        err |= bad;
+        if (j < m && !bad && a != b) {
+            key[q] = ((uint64_t)weight_key(wb[q], WT) << 32) | j;
+            ab[q] = a | (b << 16);
+        }
+    }
+    if (err) {
+        atomicOr(&pc.gerr, err);
+        atomicOr(&pc.err, err);
+    }
+    __syncthreads();
+    const bool failed = uniform(pc.gerr) != 0;
+    uint32_t pos = 0, nrounds = 0;
+    if (!failed)
+        register_rounds<NT>(
+            key, ab, qa, n, smem + BYTES, A.lds_bytes - BYTES,
+            [&](uint64_t k) {
+                const uint32_t e = (uint32_t)k;
+                atomicOr(&bits[e >> 5], 1u << (e & 31));
+            },
+            nullptr, pc, A.round_hooks, nrounds);
+    WSum ws;
+    if (!failed) {
+        // as many edges a thread (their weights once more, from the caches:
+        // sums held through the rounds would not leave enough registers)
+        const uint32_t j0 = persist_rq(NT) * opaque_tid();
+        const uint32_t f = (bits[j0 >> 5] >> (j0 & 31)) & ((1u << persist_rq(NT)) - 1u);
+        uint32_t w[persist_rq(NT)];
+#pragma unroll
+        for (int q = 0; q < persist_rq(NT); ++q) w[q] = (f >> q) & 1 ? W[j0 + q] : 0u;
+        uint32_t at = block_excl_sum<NT>(__popc(f), s_scan, &pos);
+        int32_t *out = A.out + v0;
+#pragma unroll
+        for (int q = 0; q < persist_rq(NT); ++q) {
+            if (!((f >> q) & 1)) continue;
+            out[at++] = (int32_t)(j0 + q);
+            wsum_add<WT>(ws, weight_key(w[q], WT));
+        }
+    }
+    if (A.round_hooks && threadIdx.x == 0) {
+        // the round that finds no edge left
+        if (nrounds < 64) A.round_hooks[nrounds] = 0;
+        A.round_hooks[64] = nrounds + 1;
+    }
+    graph_results<NT, WT>(A, g, ws, failed, 0, pos, pc, s_sum, s_tot);
 }
 
 }  // namespace
 
 template <int NT, int EPT, int WT>
-__global__ __launch_bounds__(NT) void k_persist(PersistArgs A)
+__global__ __launch_bounds__(NT, 4) void k_persist(PersistArgs A)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ PCtl<NT> pc;
@@ -930,8 +1285,12 @@ __global__ __launch_bounds__(NT) void k_persist(PersistArgs A)
         __syncthreads();
         const uint32_t g = uniform(pc.g);
         if (g == NONE32) break;
+        const uint32_t n = (uint32_t)(one ? A.one_n : A.vtx_off[g + 1] - A.vtx_off[g]);
+        const uint32_t m = (uint32_t)(one ? A.one_m : A.edge_off[g + 1] - A.edge_off[g]);
         // vertex numbers of at most 16 bits: both ends of an edge in one word
-        if ((one ? A.one_n : A.vtx_off[g + 1] - A.vtx_off[g]) <= 65536)
+        if (uniform((uint32_t)persist_in_registers(n, m, NT, A.lds_bytes)))
+            solve_registers<NT, WT>(A, g, smem, pc, s_sum, s_tot, s_scan);
+        else if (n <= 65536)
             solve_contracted<NT, EPT, WT, true>(A, g, smem, slot, pc, s_sum, s_tot, s_scan);
         else
             solve_contracted<NT, EPT, WT, false>(A, g, smem, slot, pc, s_sum, s_tot, s_scan);

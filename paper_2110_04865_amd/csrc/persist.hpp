@@ -56,6 +56,17 @@ struct PersistCfg {
     uint32_t lds;
 };
 
+// Edges a thread of the persistent kernel can keep in registers (1024 threads
+// have 128 each: eight edges spill), and whether a graph's edges fit them and
+// its state (10 bytes a vertex, a bit an edge) LDS: such a graph is solved
+// without a list in device memory.
+__host__ __device__ constexpr int persist_rq(int nt) { return nt == 1024 ? 4 : 8; }
+__host__ __device__ inline bool persist_in_registers(uint32_t n, uint32_t m, int nt, size_t lds)
+{
+    const uint32_t cap = (uint32_t)(persist_rq(nt) * nt);
+    return m <= cap && 10 * (size_t)n + 32 + cap / 8 <= lds;
+}
+
 // Graphs above these sizes are not solved by the persistent kernel.
 constexpr uint32_t PERSIST_MAX_N = 1u << 20;
 constexpr uint32_t PERSIST_MAX_M = 1u << 22;

@@ -201,6 +201,34 @@ def test_more_rounds_than_enqueued_two_phases(ctx):
     check(ctx, n, e7, w7, U32, "ruler path among many light loops")
 
 
+@pytest.mark.parametrize("n,m", [(2, 1), (40, 2048), (40, 2049), (3248, 2048), (3249, 2048),
+                                 (500, 4096), (500, 4097), (6499, 4096), (6500, 4096),
+                                 (900, 8193), (130, 20000), (129, 60000)])
+def test_edges_in_registers(pkg, n, m):
+    """One-workgroup solves and batches around the sizes whose edges and
+    state fit the registers and LDS of 256, 512 and 1024 threads."""
+    c = pkg.Context(0)
+    rng = np.random.default_rng(n * 7 + m)
+    e = rng.integers(0, n, size=(m, 2)).astype(np.int32)
+    wu = rng.integers(0, 5, size=m).astype(np.uint32)
+    wf = rng.standard_normal(m).astype(np.float32)
+    wf[::9] = -0.0
+    check(c, n, e, wu, U32, "registers, ties", path=1)
+    check(c, n, e, wf, F32, "registers, f32", path=1)
+    # the same graph between a smaller one and one without edges
+    vo, eo = np.array([0, 2, 2 + n, 5 + n]), np.array([0, 1, 1 + m, 1 + m])
+    eb = np.concatenate([np.array([[0, 1]], np.int32), e])
+    for w, wt in ((wu, U32), (wf, F32)):
+        want, cnt, tot = oracle.msf(n, e, w, wt)
+        wb = np.concatenate([w[:1], w])
+        ids, counts, totals = c.solve_batched(vo, eo, dev(eb), dev(wb), wtype=wt)
+        torch.cuda.synchronize()
+        assert list(counts) == [1, cnt, 0]
+        assert np.array_equal(ids.cpu().numpy()[2:2 + cnt].astype(np.int64), want)
+        assert totals[1][1] == tot[1]
+    c.close()
+
+
 @pytest.mark.parametrize("n,m,path", [(1000, 66000, 1), (1000, 66001, 4), (22000, 24000, 1),
                                       (22000, 24001, 4), (33999, 2, 1), (34000, 1, 4)])
 def test_one_workgroup_line(pkg, n, m, path):
