@@ -216,7 +216,7 @@ __global__ __launch_bounds__(CE_NT) void k_ct_select(CtArgs A)
 {
     __shared__ uint32_t s_cnt[CE_WV];
     const int lane = __lane_id();
-    const uint32_t wv = blockIdx.x * CE_WV + (threadIdx.x >> 6);
+    const uint32_t wv = ct_uniform(blockIdx.x * CE_WV + (threadIdx.x >> 6));
     const uint64_t T = A.cnt->ct.T;
     const int64_t tiles = (A.m + CT_TILE - 1) / CT_TILE;
     const uint32_t n = (uint32_t)A.n;
@@ -547,40 +547,38 @@ __device__ __forceinline__ uint32_t ct_sweep(CtEdge *seg, uint32_t cnt,
             }
         }
         uint64_t ra[U], rb[U];
-        uint32_t ha[U], hb[U];
+        uint32_t pr[U];
+        bool ha[U], hb[U];  // the end is a hot vertex
 #pragma unroll
         for (int q = 0; q < U; ++q) {
             if (MODE == CT_MIN_PAIR) {
-                ha[q] = x[q].a != x[q].b ? min(x[q].a, x[q].b) * CT_PAIR + max(x[q].a, x[q].b) : 0u;
-                ra[q] = s_r[ha[q]];
+                pr[q] = x[q].a != x[q].b ? min(x[q].a, x[q].b) * CT_PAIR + max(x[q].a, x[q].b) : 0u;
+                ra[q] = s_r[pr[q]];
             } else if (ENDS == CT_CUM && x[q].a == x[q].b) {
                 ra[q] = rb[q] = 0;  // internal (a finished tree's number is no index)
-                ha[q] = hb[q] = CT_HOT;
+                ha[q] = hb[q] = false;
             } else if (MODE == CT_MIN_LDS) {
                 ra[q] = s_r[x[q].a];
                 rb[q] = s_r[x[q].b];
             } else {
-                ha[q] = hb[q] = CT_HOT;
-                if (MODE == CT_MIN_HOT) {
-                    const uint32_t sa = ct_hot_slot(x[q].a), sb = ct_hot_slot(x[q].b);
-                    if (s_tag[sa] == x[q].a) ha[q] = sa;
-                    if (s_tag[sb] == x[q].b) hb[q] = sb;
-                }
-                ra[q] = ha[q] < CT_HOT ? s_r[ha[q]]
-                                       : read ? load_relaxed_u64(r + x[q].a) : KEY_INF;
-                rb[q] = hb[q] < CT_HOT ? s_r[hb[q]]
-                                       : read ? load_relaxed_u64(r + x[q].b) : KEY_INF;
+                const uint32_t sa = ct_hot_slot(x[q].a), sb = ct_hot_slot(x[q].b);
+                ha[q] = MODE == CT_MIN_HOT && s_tag[sa] == x[q].a;
+                hb[q] = MODE == CT_MIN_HOT && s_tag[sb] == x[q].b;
+                ra[q] = ha[q] ? s_r[sa] : read ? load_relaxed_u64(r + x[q].a) : KEY_INF;
+                rb[q] = hb[q] ? s_r[sb] : read ? load_relaxed_u64(r + x[q].b) : KEY_INF;
             }
         }
 #pragma unroll
         for (int q = 0; q < U; ++q) {
             const bool live = j0 + q * 64 + lane < cnt && x[q].a != x[q].b;
-            if (ENDS == CT_ENDS && MODE != CT_MIN_LDS && MODE != CT_MIN_PAIR) {
+            if (ENDS != CT_CUM && MODE != CT_MIN_LDS && MODE != CT_MIN_PAIR) {
                 // the list is in the input's order, where edges often come in
                 // runs of one first end: a run's minimum (within 16 lanes)
-                // leaves from its last lane alone (grid 256^3, 31M light
+                // leaves from its last lane alone (first round of grid 256^3, 31M light
                 // edges: 361 us, 520 us with one atomic per end; 1.1M random
-                // edges on 10^6 vertices: 90 us either way)
+                // edges on 10^6 vertices: 90 us either way), and the runs of
+                // the input stay runs while the ends are mapped (R-MAT s19, 4M
+                // edges, a solve: 454 us with the first round only, 421 us)
                 const uint32_t a = live ? x[q].a : NONE32;
                 uint64_t m = live ? x[q].key : KEY_INF;
                 run_min<DPP_ROW_SHR1>(a, m);
@@ -590,20 +588,20 @@ __device__ __forceinline__ uint32_t ct_sweep(CtEdge *seg, uint32_t cnt,
                 const bool last = dpp_u32<DPP_ROW_SHL1>(a, ~a) != a;
                 if (live) {
                     if (last) {
-                        if (ha[q] < CT_HOT) lower_lds(s_r, ha[q], ra[q], m);
+                        if (ha[q]) lower_lds(s_r, ct_hot_slot(x[q].a), ra[q], m);
                         else lower_dev(r, x[q].a, ra[q], m);
                     }
-                    if (hb[q] < CT_HOT) lower_lds(s_r, hb[q], rb[q], x[q].key);
+                    if (hb[q]) lower_lds(s_r, ct_hot_slot(x[q].b), rb[q], x[q].key);
                     else lower_dev(r, x[q].b, rb[q], x[q].key);
                 }
             } else if (live && MODE == CT_MIN_PAIR) {
-                lower_lds(s_r, ha[q], ra[q], x[q].key);
+                lower_lds(s_r, pr[q], ra[q], x[q].key);
             } else if (live) {
                 if (MODE == CT_MIN_LDS) lower_lds(s_r, x[q].a, ra[q], x[q].key);
-                else if (ha[q] < CT_HOT) lower_lds(s_r, ha[q], ra[q], x[q].key);
+                else if (ha[q]) lower_lds(s_r, ct_hot_slot(x[q].a), ra[q], x[q].key);
                 else lower_dev(r, x[q].a, ra[q], x[q].key);
                 if (MODE == CT_MIN_LDS) lower_lds(s_r, x[q].b, rb[q], x[q].key);
-                else if (hb[q] < CT_HOT) lower_lds(s_r, hb[q], rb[q], x[q].key);
+                else if (hb[q]) lower_lds(s_r, ct_hot_slot(x[q].b), rb[q], x[q].key);
                 else lower_dev(r, x[q].b, rb[q], x[q].key);
             }
             const uint64_t mask = __ballot(live);
@@ -623,13 +621,14 @@ __device__ __forceinline__ uint32_t ct_pass(const CtArgs &A, int k, uint32_t L,
                                             uint64_t *r, uint64_t *s_r, uint32_t *s_tag,
                                             uint32_t *s_num, uint32_t *s_c)
 {
-    const uint32_t tid = threadIdx.x, wv = blockIdx.x * CE_WV + (tid >> 6);
+    // (a wave's numbers in scalar registers)
+    const uint32_t tid = threadIdx.x, wv = ct_uniform(blockIdx.x * CE_WV + (tid >> 6));
     const int lane = __lane_id();
     uint32_t live = 0;
     // every wave over its segments, one sweep each
 #define CT_SEGMENTS(MODE, READ)                                                               \
     for (uint32_t sg = wv; sg < A.W; sg += gridDim.x * CE_WV) {                               \
-        const uint32_t cnt = A.cw[sg];                                                        \
+        const uint32_t cnt = ct_uniform(A.cw[sg]);                                            \
         const uint32_t out = ct_sweep<ENDS, MODE>(A.list + (size_t)sg * A.segcap, cnt, map,   \
                                                   s_cum, r, s_r, s_tag, READ);                \
         if (ENDS == CT_MAP && lane == 0) A.cw[sg] = out;                                      \
@@ -668,7 +667,7 @@ __device__ __forceinline__ uint32_t ct_pass(const CtArgs &A, int k, uint32_t L,
     if (tid < 2) s_c[tid] = 0;
     __syncthreads();
     // the first edges of every wave are the sample
-    const uint32_t cnt0 = A.cw[wv];
+    const uint32_t cnt0 = ct_uniform(A.cw[wv]);
     uint32_t va = NONE32, vb = NONE32;
     if ((uint32_t)lane < cnt0) {
         const CtEdge *seg = A.list + (size_t)wv * A.segcap;
@@ -1062,7 +1061,7 @@ __global__ __launch_bounds__(CE_NT) void k_ct_between(CtArgs A, const uint32_t *
     Counters *c = A.cnt;
     if (c->err || !c->ct.phdone[0] || c->ct.ran[1][0]) return;
     const int lane = __lane_id();
-    const uint32_t wv = blockIdx.x * CE_WV + (threadIdx.x >> 6);
+    const uint32_t wv = ct_uniform(blockIdx.x * CE_WV + (threadIdx.x >> 6));
     const int64_t tiles = (A.m + CT_TILE - 1) / CT_TILE;
     CtEdge *seg = A.list + (size_t)wv * A.segcap;
     uint32_t out = 0;
