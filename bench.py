@@ -4,13 +4,14 @@
 Headline: MSF edges/s on an R-MAT graph of scale 22 (4,194,304 vertices,
 edge factor 16, a/b/c/d = .57/.19/.19/.05, permuted ids, duplicates and
 self-loops removed, float32 weights), one step = one msf_solve from
-device-resident COO edges to device-resident forest ids (adjacency build,
-every round, output compaction and the exact total).
+device-resident COO edges to device-resident forest ids (validation, every
+round, output compaction and the exact total).
 
 Also reported on the same JSON line:
-  roofline      the dominant kernel (most device time per step among the
-                build's placement, the run sort, the full sweep, the head
-                sweep, the level-1 and level-2 partitions): its algorithmic
+  roofline      the dominant unit of the solve (most device time per step
+                among the selection of the light edges, the first round and
+                all later rounds; with an adjacency matrix among its build,
+                the run sort and the head sweeps): its algorithmic
                 bytes per launch over its average
                 launch time, both taken inside the timed steps from device
                 events that the library records on the stream those kernels
@@ -896,6 +897,22 @@ def main():
         "heads": (kt["heads"][0] / steps, kt["heads"][1] / steps,
                   "k_heads + k_heads_rest (head sweeps of one solve; 24 B per run and sweep)"),
     }
+    if r["stats"]["path"] == 4:
+        # rounds over a contracted edge list: no adjacency is built.  The
+        # selection reads the input once (12 m) and writes 16 bytes an edge of
+        # the first list; what follows the first round reads the input's ends
+        # once more (8 m) and, a round, 16 bytes an edge still on the list.
+        on_list = [x / 2 for x in r["stats"]["active_nnz"]]
+        first_ms = r["build_ms"] - r["adjacency_ms"]
+        units = {
+            "select": (r["adjacency_ms"], 12.0 * m + 16.0 * on_list[0],
+                       "k_ct_init, k_ct_threshold, k_ct_select (light edges' list)"),
+            "first_round": (first_ms, 16.0 * on_list[0] + 16.0 * n,
+                            "k_ct_edges<true>, k_ct_hook, k_ct_chase (first round)"),
+            "rounds": (r["rounds_ms"], 8.0 * m + 16.0 * sum(on_list[1:]),
+                       "k_ct_edges, k_ct_hook, k_ct_chase, k_ct_compose, k_ct_between, the "
+                       "output (all after the first round)"),
+        }
     dom = max(units, key=lambda k: units[k][0])
     d_ms, d_bytes, d_name = units[dom]
     achieved = (d_bytes / 1e9) / (d_ms / 1e3) if d_ms > 0 else 0.0
@@ -919,7 +936,7 @@ def main():
                    "rounds_ms": r["rounds_ms"]},
         "roofline": {"bound": "hbm", "kernel": d_name,
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(dom),
+                     "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(dom) if dom in KERNELS else None,
                      "avg_launch_ms": d_ms, "bytes_per_launch": d_bytes,
                      "units_ms_per_step": {k: v[0] for k, v in units.items()},
                      "kernel_ms_per_step": {k: v[0] / steps for k, v in kt.items()}},
