@@ -906,7 +906,7 @@ def main():
         first_ms = r["build_ms"] - r["adjacency_ms"]
         units = {
             "select": (r["adjacency_ms"], 12.0 * m + 16.0 * on_list[0],
-                       "k_ct_init, k_ct_threshold, k_ct_select (light edges' list)"),
+                       "k_ct_init, k_ct_select (light edges' list)"),
             "first_round": (first_ms, 16.0 * on_list[0] + 16.0 * n,
                             "k_ct_edges<true>, k_ct_hook, k_ct_chase (first round)"),
             "rounds": (r["rounds_ms"], 8.0 * m + 16.0 * sum(on_list[1:]),

@@ -64,8 +64,8 @@ bool contract_settings(const Ctx *c);
 size_t ct_maps_words(int32_t n);
 size_t ct_wpart_bytes();
 
-void ct_init(hipStream_t s, const CtArgs &A, size_t flag_words);
-void ct_threshold(hipStream_t s, const CtArgs &A, int64_t light);
+// Set-up, and the threshold for about the `light` lightest edges.
+void ct_init(hipStream_t s, const CtArgs &A, size_t flag_words, int64_t light);
 void ct_select(hipStream_t s, const CtArgs &A);
 // One round; big: also the kernels that a round with many vertices needs
 // (bound: the most vertices it can have).
@@ -73,7 +73,7 @@ void ct_round(hipStream_t s, const CtArgs &A, int k, bool big, uint32_t bound);
 // Trees of phase 0 per vertex, the largest one's membership bits, and the
 // list of the edges between different trees.
 void ct_between(hipStream_t s, const CtArgs &A, uint32_t *comp, uint32_t *bits);
-// Exact total; sets cnt->ct.fin once every phase is done.
-void ct_total(hipStream_t s, const CtArgs &A, int last_phase);
+// Partial weight sums that graphs of n vertices use.
+uint32_t ct_wslots_host(int32_t n);
 
 }  // namespace msf

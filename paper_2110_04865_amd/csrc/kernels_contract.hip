@@ -40,6 +40,8 @@ namespace {
 
 constexpr int CE_NT = 1024;               // threads of the list kernels
 constexpr int CE_WV = CE_NT / 64;
+constexpr int CI_NT = 256;                // of the set-up
+constexpr int TIE_NT = 512;               // of the hook
 constexpr uint32_t CT_DEAD = 0x80000000u; // a finished tree's number
 constexpr uint32_t CT_SAMPLES = 2048;
 
@@ -83,6 +85,13 @@ __device__ __forceinline__ void lower_lds(uint64_t *r, uint32_t i, uint64_t cur,
     if (x < cur) __hip_atomic_fetch_min(r + i, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// Workgroups of the largest round's hook, a slot of partial sums each.
+__host__ __device__ inline uint32_t ct_wslots(int32_t n)
+{
+    const uint32_t g = ((uint32_t)n + 2 * TIE_NT - 1) / (2 * TIE_NT);
+    return g < 1 ? 1 : g < CT_WSLOTS ? g : CT_WSLOTS;
+}
+
 unsigned grid_for(size_t n, unsigned block, unsigned cap)
 {
     size_t g = (n + block - 1) / block;
@@ -91,53 +100,29 @@ unsigned grid_for(size_t n, unsigned block, unsigned cap)
 
 }  // namespace
 
+uint32_t ct_wslots_host(int32_t n) { return ct_wslots(n); }
+
 size_t ct_maps_words(int32_t n) { return ct_map_at(n, 34) + 64; }
 
 size_t ct_wpart_bytes() { return 8 * (size_t)CT_WSLOTS * WS_WORDS; }
 
 // ----------------------------------------------------------------- set-up --
 
-__global__ __launch_bounds__(256) void k_ct_init(CtArgs A, size_t flag_words)
-{
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (blockIdx.x == 0) {
-        uint32_t *c = reinterpret_cast<uint32_t *>(A.cnt);
-        for (uint32_t i = threadIdx.x; i < sizeof(Counters) / 4; i += 256) c[i] = 0u;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            A.cnt->ct.L[0][0] = (uint32_t)A.n;
-            A.cnt->ct.T = KEY_INF;
-            A.cnt->ct.clk[0] = wall_clock64();
-        }
-    }
-    uint32_t *fl = reinterpret_cast<uint32_t *>(A.flags);
-    for (size_t i = i0; i < (size_t)A.n; i += stride) A.r[0][i] = KEY_INF;
-    for (size_t i = i0; i < flag_words; i += stride) fl[i] = 0u;
-    for (size_t i = i0; i < (size_t)CT_WSLOTS * WS_WORDS; i += stride) A.wpart[i] = 0;
-    for (size_t i = i0; i < CT_PAIR * CT_PAIR; i += stride) A.mat[i] = KEY_INF;
-}
-
-void ct_init(hipStream_t s, const CtArgs &A, size_t flag_words)
-{
-    k_ct_init<<<grid_for(std::max<size_t>((size_t)A.n, flag_words), 256, 4096), 256, 0, s>>>(
-        A, flag_words);
-}
-
 // The rank-th smallest key of a sample of CT_SAMPLES edges (one from each of
 // as many equal stretches of the input, at a mixed place): the threshold of
-// phase 0.  One workgroup, samples in registers, eight bits per step until
+// phase 0.  One workgroup beside those of the set-up (a launch of its own
+// takes 6 us more), samples in registers, eight bits per step until
 // the bin holds one sample (the second or third step, unless weights repeat).
-__global__ __launch_bounds__(CE_NT) void k_ct_threshold(CtArgs A, uint32_t rank)
+__device__ void ct_threshold(const CtArgs &A, uint32_t rank)
 {
     __shared__ uint32_t s_hist[256];
     __shared__ uint32_t s_bin, s_rank, s_num;
-    constexpr int PER = CT_SAMPLES / CE_NT;
+    constexpr int PER = CT_SAMPLES / CI_NT;
     uint64_t key[PER];
     const uint64_t m = (uint64_t)A.m;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        const uint32_t i = q * CE_NT + threadIdx.x;
+        const uint32_t i = q * CI_NT + threadIdx.x;
         const uint64_t lo = m * i / CT_SAMPLES, hi = m * (i + 1) / CT_SAMPLES;
         uint32_t x = i * 0x9E3779B9u + 0x7F4A7C15u;
         x ^= x >> 15;
@@ -185,12 +170,48 @@ __global__ __launch_bounds__(CE_NT) void k_ct_threshold(CtArgs A, uint32_t rank)
     }
 }
 
-void ct_threshold(hipStream_t s, const CtArgs &A, int64_t light)
+// rank: of the threshold in the sample, which one more workgroup takes, or
+// NONE32 for every edge.
+__global__ __launch_bounds__(CI_NT) void k_ct_init(CtArgs A, size_t flag_words, uint32_t rank)
 {
-    if (light >= A.m) return;  // every edge (the threshold starts at the largest key)
-    const double f = (double)light / (double)A.m;
-    const uint32_t rank = std::min<uint32_t>((uint32_t)(f * CT_SAMPLES), CT_SAMPLES - 1);
-    k_ct_threshold<<<1, CE_NT, 0, s>>>(A, rank);
+    const uint32_t blocks = gridDim.x - (rank != NONE32);
+    if (blockIdx.x == blocks) {
+        ct_threshold(A, rank);
+        return;
+    }
+    const size_t stride = (size_t)blocks * blockDim.x;
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (blockIdx.x == 0) {
+        uint32_t *c = reinterpret_cast<uint32_t *>(A.cnt);
+        // (the threshold is set elsewhere, or to every key below)
+        const uint32_t t = offsetof(Counters, ct.T) / 4;
+        for (uint32_t i = threadIdx.x; i < sizeof(Counters) / 4; i += CI_NT)
+            if (i != t && i != t + 1) c[i] = 0u;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            A.cnt->ct.L[0][0] = (uint32_t)A.n;
+            if (rank == NONE32) A.cnt->ct.T = KEY_INF;
+            A.cnt->ct.clk[0] = wall_clock64();
+        }
+    }
+    uint32_t *fl = reinterpret_cast<uint32_t *>(A.flags);
+    for (size_t i = i0; i < (size_t)A.n; i += stride) A.r[0][i] = KEY_INF;
+    for (size_t i = i0; i < flag_words; i += stride) fl[i] = 0u;
+    const uint32_t slots = ct_wslots(A.n);
+    for (size_t i = i0; i < (size_t)slots * WS_WORDS; i += stride)
+        A.wpart[i / slots * CT_WSLOTS + i % slots] = 0;
+    for (size_t i = i0; i < CT_PAIR * CT_PAIR; i += stride) A.mat[i] = KEY_INF;
+}
+
+void ct_init(hipStream_t s, const CtArgs &A, size_t flag_words, int64_t light)
+{
+    uint32_t rank = NONE32;
+    if (light < A.m) {  // else every edge
+        const double f = (double)light / (double)A.m;
+        rank = std::min<uint32_t>((uint32_t)(f * CT_SAMPLES), CT_SAMPLES - 1);
+    }
+    const unsigned g = grid_for(std::max<size_t>((size_t)A.n, flag_words), CI_NT, 4096);
+    k_ct_init<<<g + (rank != NONE32), CI_NT, 0, s>>>(A, flag_words, rank);
 }
 
 // ------------------------------------------------------- list of phase 0 --
@@ -819,7 +840,6 @@ __device__ __forceinline__ bool ct_big_round(const CtArgs &A, int k, uint32_t L)
 // for its hook.  A tile is IT x 512 consecutive vertices; the numbers keep
 // the vertices' order inside it (item-major, then wave, then lane) and each
 // tile takes its range with one atomic, so neighbours stay neighbours.
-constexpr int TIE_NT = 512;
 
 template <int IT, int WT>
 __device__ __forceinline__ uint32_t ct_hook_tiles(const CtArgs &A, int k, uint32_t L,
@@ -1136,44 +1156,6 @@ void ct_between(hipStream_t s, const CtArgs &A, uint32_t *comp, uint32_t *bits)
     } else {
         k_ct_between<false><<<A.W / CE_WV, CE_NT, 0, s>>>(A, comp, nullptr);
     }
-}
-
-// ------------------------------------------------------------------ total --
-
-template <int WT>
-__global__ __launch_bounds__(CE_NT) void k_ct_total(CtArgs A, int last_phase)
-{
-    __shared__ int64_t s_sum[CE_WV * (ACC_DIGITS + 1)];
-    __shared__ int64_t s_tot[WS_WORDS];
-    Counters *c = A.cnt;
-    if (c->err || !c->ct.phdone[last_phase]) return;
-    WSum ws;
-    for (uint32_t i = threadIdx.x; i < CT_WSLOTS; i += CE_NT) {
-        if (WT == MSF_W_U32) {
-            ws.su += (uint64_t)A.wpart[i];
-        } else {
-#pragma unroll
-            for (int d = 0; d < ACC_DIGITS; ++d) ws.acc[d] += A.wpart[(size_t)(1 + d) * CT_WSLOTS + i];
-            ws.pinf += (uint32_t)A.wpart[(size_t)(1 + ACC_DIGITS) * CT_WSLOTS + i];
-            ws.ninf += (uint32_t)A.wpart[(size_t)(2 + ACC_DIGITS) * CT_WSLOTS + i];
-        }
-    }
-    const uint32_t wl = c->ct.wl;
-    for (uint32_t i = threadIdx.x; i < wl; i += CE_NT) wsum_add<WT>(ws, A.wlist[i]);
-    wsum_block<CE_NT, WT>(ws, s_sum, s_tot, 1);
-    if (threadIdx.x == 0) {
-        c->total_u64 = WT == MSF_W_U32 ? (uint64_t)s_tot[0] : 0;
-        c->total_f64 = exact_total_f64((uint64_t)s_tot[0], s_tot + 1,
-                                       (uint32_t)s_tot[1 + ACC_DIGITS],
-                                       (uint32_t)s_tot[2 + ACC_DIGITS], WT);
-        c->ct.fin = 1;
-    }
-}
-
-void ct_total(hipStream_t s, const CtArgs &A, int last_phase)
-{
-    if (A.wt == MSF_W_F32) k_ct_total<MSF_W_F32><<<1, CE_NT, 0, s>>>(A, last_phase);
-    else k_ct_total<MSF_W_U32><<<1, CE_NT, 0, s>>>(A, last_phase);
 }
 
 }  // namespace msf

@@ -624,16 +624,55 @@ __device__ __forceinline__ uint32_t count_flags(const uint32_t (&fw)[OUT_IT / 4]
 // address cost 13 ns each.
 constexpr unsigned OUT_WG = 512;
 
+// The contracted rounds' exact total, by one workgroup.
+template <int WT>
+__device__ __forceinline__ void output_total(Counters *c, const OutputTotal &t)
+{
+    __shared__ int64_t s_sum[(OUT_NT / 64) * (ACC_DIGITS + 1)];
+    __shared__ int64_t s_tot[WS_WORDS];
+    WSum ws;
+    for (uint32_t i = threadIdx.x; i < t.slots; i += OUT_NT) {
+        if (WT == MSF_W_U32) {
+            ws.su += (uint64_t)t.wpart[i];
+        } else {
+#pragma unroll
+            for (int d = 0; d < ACC_DIGITS; ++d)
+                ws.acc[d] += t.wpart[(size_t)(1 + d) * t.stride + i];
+            ws.pinf += (uint32_t)t.wpart[(size_t)(1 + ACC_DIGITS) * t.stride + i];
+            ws.ninf += (uint32_t)t.wpart[(size_t)(2 + ACC_DIGITS) * t.stride + i];
+        }
+    }
+    const uint32_t wl = c->ct.wl;
+    for (uint32_t i = threadIdx.x; i < wl; i += OUT_NT) wsum_add<WT>(ws, t.wlist[i]);
+    wsum_block<OUT_NT, WT>(ws, s_sum, s_tot, 1);
+    if (threadIdx.x == 0) {
+        c->total_u64 = WT == MSF_W_U32 ? (uint64_t)s_tot[0] : 0;
+        c->total_f64 = exact_total_f64((uint64_t)s_tot[0], s_tot + 1,
+                                       (uint32_t)s_tot[1 + ACC_DIGITS],
+                                       (uint32_t)s_tot[2 + ACC_DIGITS], WT);
+        c->ct.fin = 1;
+    }
+}
+
+// WT: of the total (TOTAL), which the last workgroup of the grid takes.
+template <bool TOTAL, int WT>
 __global__ __launch_bounds__(OUT_NT) void k_output_count(const uint8_t *__restrict__ flags,
                                                         int64_t m, uint32_t ntiles,
                                                         uint32_t *tile_cnt,
                                                         uint32_t *__restrict__ tile_off,
-                                                        Counters *cnt, const uint32_t *go)
+                                                        Counters *cnt, OutputTotal t)
 {
-    if (go && !*go) return;
+    const uint32_t blocks = gridDim.x - TOTAL;
+    if (TOTAL) {
+        if (cnt->err || !cnt->ct.phdone[t.last_phase]) return;
+        if (blockIdx.x == blocks) {
+            output_total<WT>(cnt, t);
+            return;
+        }
+    }
     __shared__ uint32_t s_lds[OUT_NT / 64 + 1];
     __shared__ uint32_t s_last;
-    for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    for (uint32_t tile = blockIdx.x; tile < ntiles; tile += blocks) {
         const int64_t base = (int64_t)tile * OUT_TILE + (int64_t)threadIdx.x * OUT_IT;
         uint32_t fw[OUT_IT / 4];
         load_flags(flags, m, base, fw);
@@ -642,7 +681,7 @@ __global__ __launch_bounds__(OUT_NT) void k_output_count(const uint8_t *__restri
     }
     if (threadIdx.x == 0) {
         __builtin_amdgcn_s_waitcnt(0);
-        s_last = atomicAdd(&cnt->oticket, 1u) == gridDim.x - 1;
+        s_last = atomicAdd(&cnt->oticket, 1u) == blocks - 1;
     }
     __syncthreads();
     if (!s_last) return;
@@ -719,7 +758,7 @@ size_t output_part_bytes(int64_t m)
 }
 
 msf_status launch_output(Ctx *c, const uint8_t *in_forest, int64_t m, const void *w,
-                         msf_wtype wt, int32_t *ids, void *part, const uint32_t *go)
+                         msf_wtype wt, int32_t *ids, void *part, const OutputTotal *tot)
 {
     const int64_t ntiles = output_tiles(m);
     if (ntiles == 0) return MSF_OK;
@@ -728,10 +767,20 @@ msf_status launch_output(Ctx *c, const uint8_t *in_forest, int64_t m, const void
     // per-tile counts and their exclusive scan
     uint32_t *tcnt = reinterpret_cast<uint32_t *>(part);
     uint32_t *toff = tcnt + ntiles;
-    k_output_count<<<(unsigned)std::min<int64_t>(ntiles, OUT_WG), OUT_NT, 0, s>>>(
-        in_forest, m, (uint32_t)ntiles, tcnt, toff, c->dcnt, go);
-    k_output_ids<<<(unsigned)ntiles, OUT_NT, 0, s>>>(in_forest, m, toff, ids, go);
-    if (!go) k_total<<<1, 64, 0, s>>>(c->dcnt, (int)wt);
+    const unsigned blocks = (unsigned)std::min<int64_t>(ntiles, OUT_WG);
+    const uint32_t nt = (uint32_t)ntiles;
+    if (!tot)
+        k_output_count<false, 0><<<blocks, OUT_NT, 0, s>>>(in_forest, m, nt, tcnt, toff, c->dcnt,
+                                                           OutputTotal{});
+    else if (wt == MSF_W_F32)
+        k_output_count<true, MSF_W_F32><<<blocks + 1, OUT_NT, 0, s>>>(in_forest, m, nt, tcnt, toff,
+                                                                      c->dcnt, *tot);
+    else
+        k_output_count<true, MSF_W_U32><<<blocks + 1, OUT_NT, 0, s>>>(in_forest, m, nt, tcnt, toff,
+                                                                      c->dcnt, *tot);
+    k_output_ids<<<(unsigned)ntiles, OUT_NT, 0, s>>>(in_forest, m, toff, ids,
+                                                     tot ? &c->dcnt->ct.fin : nullptr);
+    if (!tot) k_total<<<1, 64, 0, s>>>(c->dcnt, (int)wt);
     MSF_HIP(hipGetLastError());
     return MSF_OK;
 }

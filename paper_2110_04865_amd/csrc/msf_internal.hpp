@@ -512,10 +512,18 @@ msf_status build_runs(Ctx *c, const Runs &R, const uint32_t *row_ptr, int32_t n,
                       const uint32_t *col, const uint64_t *key, uint32_t nnz_max, int eb);
 void launch_heads(hipStream_t s, const Runs &R, uint32_t nruns, const uint32_t *col,
                   const uint64_t *key, const uint32_t *p, uint64_t *r, Counters *dcnt, int parity);
-// go (nullable, device): nothing is written while it is 0, and the total has
-// been rounded already.
+// tot: contracted rounds, which sum their weights here (in one more workgroup
+// of the first pass) and set cnt->ct.fin once every phase is complete; nothing
+// is written before that.
+struct OutputTotal {
+    const int64_t *wpart;   // partial sums, word j of slot i at j * stride + i
+    uint32_t stride, slots;
+    const uint32_t *wlist;  // weight keys
+    int last_phase;
+};
 msf_status launch_output(Ctx *c, const uint8_t *in_forest, int64_t m, const void *w,
-                         msf_wtype wt, int32_t *ids, void *part, const uint32_t *go = nullptr);
+                         msf_wtype wt, int32_t *ids, void *part,
+                         const OutputTotal *tot = nullptr);
 
 // Shortcut of an arbitrary parent vector (msf_shortcut).
 void launch_check_parents(hipStream_t s, const uint32_t *p, int32_t n, Counters *dcnt);

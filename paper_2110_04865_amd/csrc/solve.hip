@@ -259,9 +259,9 @@ static msf_status contract_enqueue(Ctx *c, int ph, int k0, uint32_t bound)
         MSF_TRY(contract_rounds(c, A, mid ? k0 : 0, mid ? bound : (uint32_t)S.n,
                                 mid ? (double)bound : (double)S.n / (p ? 4.0 : 1.0)));
     }
-    ct_total(c->stream, A, S.two_phase ? 1 : 0);
+    const OutputTotal tot{A.wpart, CT_WSLOTS, ct_wslots_host(S.n), A.wlist, S.two_phase ? 1 : 0};
     MSF_TRY(launch_output(c, S.b.flags, S.m, S.w, S.wt, S.ids,
-                          (uint8_t *)c->ws[WS_PART].ptr + ct_wpart_bytes(), &c->dcnt->ct.fin));
+                          (uint8_t *)c->ws[WS_PART].ptr + ct_wpart_bytes(), &tot));
     return end_step(c, 8);
 }
 
@@ -291,8 +291,7 @@ static msf_status contract_start(Ctx *c)
     CtArgs A;
     MSF_TRY(contract_args(c, &A));
     S.b.flags = A.flags;
-    ct_init(c->stream, A, S.ct_words);
-    if (S.two_phase) ct_threshold(c->stream, A, light);
+    ct_init(c->stream, A, S.ct_words, S.two_phase ? light : S.m);
     ct_select(c->stream, A);
     return contract_enqueue(c, 0, 0, (uint32_t)S.n);
 }
