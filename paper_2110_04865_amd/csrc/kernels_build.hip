@@ -60,6 +60,14 @@ void launch_fill_u32(hipStream_t s, uint32_t *p, uint32_t v, size_t n)
     if (n) k_fill_u32<<<grid_for(n), 256, 0, s>>>(p, v, n);
 }
 
+__global__ void k_clear_err_done(Counters *cnt)
+{
+    cnt->err = 0;
+    cnt->gdone = 0;
+}
+
+void launch_clear_err_done(hipStream_t s, Counters *dcnt) { k_clear_err_done<<<1, 1, 0, s>>>(dcnt); }
+
 __global__ __launch_bounds__(256) void k_publish(const uint64_t *__restrict__ src,
                                                  uint64_t *__restrict__ dst, uint32_t words,
                                                  uint32_t end_clk)

@@ -3,10 +3,11 @@
 //
 // The forest is unique under the order of the keys (weight, edge id), so an
 // edge that joins two vertices of one tree of the forest of all lighter
-// edges is not in it (the cycle property).  Phase 0 therefore takes only the
-// lightest edges (about n ln(4 m / n) / 2 of them, by a sampled threshold on
-// the key) and builds their forest; one pass over the input then drops every
-// edge inside a tree of it, and phase 1 continues with the few edges left
+// edges is not in it (the cycle property).  From half a million edges on,
+// phase 0 therefore takes only the lightest edges (about 0.4 n ln(4 m / n) of
+// them, by a sampled threshold on the key) and builds their forest; one pass
+// over the input then drops every edge inside a tree of it, and phase 1
+// continues with the few edges left
 // between the trees.  Each phase runs the rounds of Algorithm 2:
 //   edges   the multilinear kernel of section 3.1 with the projection: every
 //           edge {a, b} with key x lowers r[a] and r[b] to x.  After the
@@ -26,8 +27,14 @@
 // and an in-place store: no barrier and no counter.  Kernels take their
 // sizes from the counters on the device and return at once when there is
 // nothing to do, so a whole solve is enqueued without a host round trip.
-// A round of at most CT_SMALL vertices needs only the edge pass: its last
+// A round of at most CT_FINISH vertices needs only the edge pass: its last
 // workgroup to finish does the rest of the round in LDS.
+//
+// Measured, us a solve over an adjacency matrix / over the list: R-MAT s16
+// (0.91M edges) 672 / 190, grid 101^3 1671 / 475, R-MAT s22 (64M edges) 4436 /
+// 1946, grid 256^3 (47.6M) 8735 / 3423.  Large rounds are bound by lookups
+// (57-205 G/s by the table's size) and device-scope minima (27 G/s), small
+// ones by chains of dependent accesses of 1 us each.
 #include <algorithm>
 
 #include "contract.hpp"

@@ -425,6 +425,7 @@ void launch_chunk_rows(hipStream_t s, const uint32_t *row_ptr, int32_t n, uint32
 // Multilinear sweep (+ optional compaction into out_*).
 void launch_fill_u64(hipStream_t s, uint64_t *p, uint64_t v, size_t n);
 void launch_fill_u32(hipStream_t s, uint32_t *p, uint32_t v, size_t n);
+void launch_clear_err_done(hipStream_t s, Counters *dcnt);
 void launch_iota_u32(hipStream_t s, uint32_t *p, size_t n);
 // p = h = identity over n vertices, r = empty when non-null, `words`
 // words of flags cleared, in one launch.

@@ -75,9 +75,9 @@ def ruler(n):
     return path_graph(n, np.log2((i & -i).astype(np.float64)).astype(np.uint32))
 
 
-# vertices around the sizes where minima move to LDS (4096), one workgroup
-# finishes a round (8192) and a tie tile of 4 x 512 ends; edges around a
-# wave's tile (256) and a sweep of every wave over one tile
+# vertices around powers of two near the sizes where one workgroup finishes a
+# round (2048) and minima move to LDS (7680); edges around a wave's tile (256)
+# and a sweep of every wave over one tile
 @pytest.mark.parametrize("n,m", [(2, 1), (3, 255), (60, 256), (300, 257), (2047, 9000),
                                  (2049, 6000), (4096, 4095), (4097, 40000), (8191, 30000),
                                  (8192, 30000), (8193, 30000), (16385, 20000),
