@@ -754,7 +754,9 @@ __device__ __forceinline__ uint32_t ct_pass(const CtArgs &A, int k, uint32_t L,
 // one a cycle) are slower than two more launches above CT_FINISH, only if
 // those launches follow (3000 vertices, grid 60^3: 26 us alone, 14 us by hook
 // and chase; 1000: 11 us alone).  From a phase's first such round on all are
-// (the maps since are composed into one).
+// (the maps since are composed into one).  A line at 1024 / 2048 / 3072, us a
+// solve: R-MAT s16 194 / 190 / 199, R-MAT s19 423 / 412 / 414, grid 60^3 264 /
+// 270 / 286.
 __device__ __forceinline__ bool ct_one_finishes(uint32_t L, uint32_t tl1, bool big)
 {
     return L <= (big && !tl1 ? CT_FINISH : CT_SMALL);
