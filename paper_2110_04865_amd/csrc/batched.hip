@@ -101,12 +101,13 @@ __global__ __launch_bounds__(256) void k_split(const int32_t *__restrict__ gids,
 }
 
 
-// out[0..count) = ids, unless a graph of the batch failed.
+// out[0..count) = ids, unless a graph of the batch failed (err null: the host
+// knows that none did).
 __global__ __launch_bounds__(256) void k_batch_ids(const int32_t *__restrict__ ids,
                                                    int32_t *__restrict__ out, int64_t count,
                                                    const uint32_t *__restrict__ err)
 {
-    if (*err) return;
+    if (err && *err) return;
     const int64_t stride = (int64_t)gridDim.x * 256;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += stride)
         out[i] = ids[i];
@@ -259,17 +260,19 @@ msf_status batched_persistent(Ctx *c, int32_t G, const BatchBlock &D, const Batc
         c->stats.batch_grid = (int32_t)grid;
     }
     // the ids to the caller's array and the results to the host, in one wait
+    // (behind the kernel's error word; once graphs were solved one by one the
+    // host has seen every status, and without a launch there is no word)
     const int64_t N = vtx_off[G];
-    auto ids_out = [&]() -> msf_status {
+    auto ids_out = [&](const uint32_t *err) -> msf_status {
         if (!d_out || N == 0) return MSF_OK;
         const size_t blocks = ((size_t)N + 1023) / 1024;
         k_batch_ids<<<(unsigned)std::min<size_t>(blocks, 4096), 256, 0, s>>>(d_stage, d_out, N,
-                                                                            D.ctl + 1);
+                                                                            err);
         MSF_HIP(hipGetLastError());
         return MSF_OK;
     };
     if (Gs > 0) {
-        if (large.empty() && (rc = ids_out())) return rc;
+        if (large.empty() && (rc = ids_out(D.ctl + 1))) return rc;
         MSF_HIP(hipMemcpyAsync(H.ctl, D.ctl, 8 + 24 * (size_t)G, hipMemcpyDeviceToHost, s));
         MSF_HIP(hipStreamSynchronize(s));
         float ms = 0.f;
@@ -292,7 +295,7 @@ msf_status batched_persistent(Ctx *c, int32_t G, const BatchBlock &D, const Batc
         H.tu[g] = tot.u64;
         H.tf[g] = tot.f64;
     }
-    return large.empty() ? MSF_OK : ids_out();
+    return large.empty() ? MSF_OK : ids_out(nullptr);
 }
 
 

@@ -321,3 +321,35 @@ def test_batched_sizes(pkg, config):
         else:
             os.environ["MSF_BATCH_CONFIG"] = old
         c.close()
+
+
+@pytest.mark.parametrize("before", ["large total", "refused"])
+def test_batch_of_large_graphs_only(pkg, before):
+    """A batch in which every graph is above the one-workgroup limits writes
+    the caller's ids whatever the call before it left in the workspace: a
+    total above 2^32 where the error word of two graphs lies, or a refused
+    batch of as many graphs."""
+    c = pkg.Context(0)
+    if before == "large total":
+        c.solve_batched(np.array([0, 3]), np.array([0, 2]), dev(np.array([[0, 1], [1, 2]], np.int32)),
+                        dev(np.full(2, 0xFFFFFFF0, np.uint32)), wtype=U32)
+    else:
+        with pytest.raises(pkg.MSFError):
+            c.solve_batched(np.array([0, 2, 4]), np.array([0, 1, 2]),
+                            dev(np.array([[0, 1], [0, 2]], np.int32)),
+                            dev(np.ones(2, np.uint32)), wtype=U32)
+    rng = np.random.default_rng(29)
+    n, m = (1 << 20) + 1, 3000
+    e = rng.integers(0, n, size=(2 * m, 2)).astype(np.int32)
+    w = rng.integers(0, 1000, size=2 * m).astype(np.uint32)
+    out = torch.full((2 * n,), -7, dtype=torch.int32, device="cuda:0")
+    ids, counts, totals = c.solve_batched(np.array([0, n, 2 * n]), np.array([0, m, 2 * m]), dev(e),
+                                          dev(w), wtype=U32, out=out)
+    torch.cuda.synchronize()
+    assert c.stats()["batch_large"] == 2
+    got = out.cpu().numpy().astype(np.int64)
+    for g in range(2):
+        want, cnt, tot = oracle.msf(n, e[g * m:(g + 1) * m], w[g * m:(g + 1) * m], U32)
+        assert counts[g] == cnt and totals[g][0] == tot[0], g
+        assert np.array_equal(got[g * n:g * n + cnt], want), g
+    c.close()
