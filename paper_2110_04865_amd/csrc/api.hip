@@ -351,9 +351,10 @@ msf_status msf_get_stats(const msf_ctx *ctx, msf_stats *out)
         MSF_HIP(hipEventSynchronize(c->sev[1]));
         float ms = 0.f, gms = 0.f;
         MSF_HIP(hipEventElapsedTime(&ms, c->sev[0], c->sev[1]));
-        MSF_HIP(hipEventElapsedTime(&gms, c->kev[0], c->kev[1]));
+        if (c->stats.pass_bytes[0] > 0)
+            MSF_HIP(hipEventElapsedTime(&gms, c->kev[c->ml_at], c->kev[c->ml_at + 1]));
         c->stats.sweep_ms[0] = ms;
-        c->stats.pass_ms[0] = c->stats.pass_bytes[0] > 0 ? gms : 0.0;
+        c->stats.pass_ms[0] = gms;
         c->ml_pending = false;
     }
     *out = c->stats;
@@ -511,25 +512,33 @@ msf_status msf_multilinear(msf_ctx *ctx, const msf_graph *g, const uint32_t *p, 
     const uint32_t *pg = p;
     void *vq = nullptr;
     if (g->perm && (rc = ws_get(c, WS_Q, 4 * (size_t)n, &vq))) return rc;
+    // the events of the gather: the pair that the last accepted call's
+    // statistics do not use (a refused call leaves those as they are)
+    const int at = c->ml_at ? 0 : 4;
     clear_err_done(c);
     launch_check_parents(c->stream, p, n, c->dcnt);
     launch_publish(c, offsetof(Counters, ct));
     MSF_HIP(hipGetLastError());
-    MSF_HIP(hipEventRecord(c->ev[3], c->stream));
+    MSF_HIP(hipEventRecord(c->kev[at], c->stream));
     // device events around the gather of p into the graph's vertex order
     // and around the sweep kernel (statistics: one round whose sweep_ms /
     // sweep_bytes describe the sweep; pass_ms[0] / pass_bytes[0] the gather).
     // The gather (into the workspace only) runs while the host waits for the
-    // check's event alone (a call on R-MAT s11, 2^15 edges, 58 us with the wait
-    // for the stream in front of the gather, 43 us; R-MAT s22 524 and 516 us).
-    MSF_HIP(hipEventRecord(c->kev[0], c->stream));
+    // check's event alone.  The wait for the stream in front of the gather /
+    // this, us: a call among others on R-MAT s11 (2^15 edges) 54 / 38, on
+    // R-MAT s22 560 / 550; a call that the host waits for 51 / 62 and 566 /
+    // 567 (the wait at its end then takes in the whole call's commands).
     if (g->perm) {
         launch_relabel_gather(c->stream, p, g->perm, n, (uint32_t *)vq);
         pg = (const uint32_t *)vq;
+        MSF_HIP(hipEventRecord(c->kev[at + 1], c->stream));
     }
-    MSF_HIP(hipEventRecord(c->kev[1], c->stream));
-    MSF_HIP(hipEventSynchronize(c->ev[3]));
-    if ((rc = decode_err(c->hcnt->err))) return rc;
+    MSF_HIP(hipEventSynchronize(c->kev[at]));
+    if ((rc = decode_err(c->hcnt->err))) {
+        // the caller may free p: nothing reads it any more
+        MSF_HIP(hipStreamSynchronize(c->stream));
+        return rc;
+    }
     launch_fill_u64(c->stream, r, KEY_INF, (size_t)n);
     MSF_HIP(hipEventRecord(c->sev[0], c->stream));
     launch_sweep(c->stream, g->a, pg, r, c->dcnt, false, nullptr, true, g->long_rows);
@@ -541,6 +550,7 @@ msf_status msf_multilinear(msf_ctx *ctx, const msf_graph *g, const uint32_t *p, 
     c->stats.sweep_bytes[0] = 12.0 * g->a.nnz + 8.0 * g->a.segs + 4.0;
     c->stats.pass_bytes[0] = g->perm ? 12.0 * n : 0.0;
     c->ml_pending = true;
+    c->ml_at = at;
     return MSF_OK;
 }
 
@@ -594,14 +604,15 @@ msf_status msf_multilinear_rows(msf_ctx *ctx, const msf_graph *g, const uint32_t
     launch_fill_u64(s, r, KEY_INF, (size_t)n);
     // device events as in msf_multilinear
     const uint32_t *pg = p;
-    MSF_HIP(hipEventRecord(c->kev[0], s));
+    const int at = c->ml_at ? 0 : 4;
+    MSF_HIP(hipEventRecord(c->kev[at], s));
     if (g->perm) {
         void *vq;
         if ((rc = ws_get(c, WS_Q, 4 * (size_t)n, &vq))) return rc;
         launch_relabel_gather(s, p, g->perm, n, (uint32_t *)vq);
         pg = (const uint32_t *)vq;
     }
-    MSF_HIP(hipEventRecord(c->kev[1], s));
+    MSF_HIP(hipEventRecord(c->kev[at + 1], s));
     MSF_HIP(hipEventRecord(c->sev[0], s));
     launch_sweep(s, a, pg, r, c->dcnt, false, nullptr, true, g->long_rows);
     MSF_HIP(hipEventRecord(c->sev[1], s));
@@ -612,6 +623,7 @@ msf_status msf_multilinear_rows(msf_ctx *ctx, const msf_graph *g, const uint32_t
     c->stats.sweep_bytes[0] = 12.0 * a.nnz + 8.0 * a.segs + 4.0;
     c->stats.pass_bytes[0] = g->perm ? 12.0 * n : 0.0;
     c->ml_pending = true;
+    c->ml_at = at;
     return MSF_OK;
 }
 

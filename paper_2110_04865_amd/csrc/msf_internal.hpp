@@ -290,9 +290,11 @@ struct Ctx {
     int rec1 = 0, rec2 = 0;
     int sub2 = 2;  // bytes of the separate row-in-bucket array per level-2 entry
     msf_stats stats{};
-    // msf_multilinear recorded sev[0..1] around its sweep; msf_get_stats
-    // turns them into sweep_ms[0] once they have completed
+    // msf_multilinear recorded sev[0..1] around its sweep and kev[ml_at],
+    // kev[ml_at + 1] around its gather; msf_get_stats turns them into
+    // sweep_ms[0] and pass_ms[0] once they have completed
     bool ml_pending = false;
+    int ml_at = 0;
     int filter_mode = 1;        // 0 never, 1 adaptive, 2 every round
     double filter_threshold = 0.30;
     bool check_rounds = false;  // read back error flags after every shortcut

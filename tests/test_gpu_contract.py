@@ -353,3 +353,36 @@ def test_batch_of_large_graphs_only(pkg, before):
         assert counts[g] == cnt and totals[g][0] == tot[0], g
         assert np.array_equal(got[g * n:g * n + cnt], want), g
     c.close()
+
+
+def test_refused_multilinear_leaves_nothing_behind(pkg):
+    """A multilinear call refused for its parents returns with nothing left
+    on the stream (the caller may free them), and the statistics stay those
+    of the last accepted call."""
+    c = pkg.Context(0)
+    e, w = gen.er(1000, 4000, seed=31)
+    small, big_n = c.graph(1000, dev(e), dev(w), wtype=U32), 1 << 26
+    be = (e.astype(np.int64) * 67000).astype(np.int32)  # few edges, many vertices
+    big = c.graph(big_n, dev(be), dev(w), wtype=U32)
+    p = torch.arange(big_n, dtype=torch.int32, device="cuda:0")
+    r = torch.zeros(big_n, dtype=torch.int64, device="cuda:0")
+    c.multilinear(big, p, r)
+    bad = torch.full((1000,), 1000, dtype=torch.int32, device="cuda:0")
+    r2 = torch.zeros(1000, dtype=torch.int64, device="cuda:0")
+    with pytest.raises(pkg.MSFError):
+        c.multilinear(small, bad, r2)
+    st = c.stats()
+    # the gather of the big call: 12 bytes a vertex, not above memory's peak
+    assert st["pass_bytes"][0] == 12.0 * big_n
+    assert st["pass_bytes"][0] <= st["pass_ms"][0] * 1e-3 * 8e12, st["pass_ms"]
+    torch.cuda.synchronize()
+    p[7] = big_n
+    before = r.clone()
+    torch.cuda.synchronize()
+    with pytest.raises(pkg.MSFError, match="parent") as ex:
+        c.multilinear(big, p, r)
+    idle = torch.cuda.current_stream().query()
+    assert idle and ex.value.status == 1
+    torch.cuda.synchronize()
+    assert torch.equal(r, before) and int(r2.abs().sum()) == 0
+    c.close()
