@@ -386,3 +386,25 @@ def test_refused_multilinear_leaves_nothing_behind(pkg):
     torch.cuda.synchronize()
     assert torch.equal(r, before) and int(r2.abs().sum()) == 0
     c.close()
+
+
+# hooks that all point along the path make one chain of its length; the last
+# size gives a thread of the chase more than 64 vertices
+@pytest.mark.parametrize("n", [1 << 21, 40 * 10 ** 6])
+@pytest.mark.parametrize("falling", [False, True])
+def test_long_chains(pkg, n, falling):
+    """Paths with rising or falling weights: every edge is in the forest, and
+    a chain of n hooks takes neither n steps nor n / 1000."""
+    import time
+    c = pkg.Context(0)
+    i = torch.arange(n, dtype=torch.int32, device="cuda:0")
+    e = torch.stack([i[:-1], i[1:]], 1).reshape(-1).contiguous()
+    w = (i[:-1].flip(0) if falling else i[:-1]).contiguous()
+    ids, cnt, tot = c.solve(n, e, w, wtype=U32)
+    t0 = time.perf_counter()
+    ids, cnt, tot = c.solve(n, e, w, wtype=U32)
+    ms = (time.perf_counter() - t0) * 1e3
+    assert cnt == n - 1 and torch.equal(ids[:cnt], i[:-1]) and tot[0] == (n - 1) * (n - 2) // 2
+    assert c.stats()["path"] == 4
+    assert ms < 50.0, ms  # (0.3 and 3 ms; a step per vertex and thread: 1 s and more)
+    c.close()
