@@ -408,3 +408,42 @@ def test_long_chains(pkg, n, falling):
     assert c.stats()["path"] == 4
     assert ms < 50.0, ms  # (0.3 and 3 ms; a step per vertex and thread: 1 s and more)
     c.close()
+
+
+@pytest.mark.parametrize("n", [6000, 20000, 22667])
+@pytest.mark.parametrize("falling", [False, True])
+def test_long_chains_in_one_workgroup(pkg, n, falling):
+    """The same in one workgroup, alone and in a batch whose targets lie in
+    LDS as 16-bit numbers and in device memory."""
+    import time
+    c = pkg.Context(0)
+
+    def path(n):
+        i = torch.arange(n, dtype=torch.int32, device="cuda:0")
+        return (torch.stack([i[:-1], i[1:]], 1).reshape(-1).contiguous(),
+                (i[:-1].flip(0) if falling else i[:-1]).contiguous(), i)
+
+    e, w, i = path(n)
+    c.solve(n, e, w, wtype=U32)
+    t0 = time.perf_counter()
+    ids, cnt, tot = c.solve(n, e, w, wtype=U32)
+    ms = (time.perf_counter() - t0) * 1e3
+    assert cnt == n - 1 and torch.equal(ids[:cnt], i[:-1]) and c.stats()["path"] == 1
+    sizes = [n, 40000, 70000, 2]
+    parts = [path(k) for k in sizes]
+    vo, eo = np.cumsum([0] + sizes), np.cumsum([0] + [k - 1 for k in sizes])
+    be, bw = torch.cat([p[0] for p in parts]), torch.cat([p[1] for p in parts])
+    os.environ["MSF_BATCH_CONFIG"] = "7"
+    try:
+        ids, counts, totals = c.solve_batched(vo, eo, be, bw, wtype=U32)
+        t0 = time.perf_counter()
+        ids, counts, totals = c.solve_batched(vo, eo, be, bw, wtype=U32)
+        batch_ms = (time.perf_counter() - t0) * 1e3
+    finally:
+        os.environ.pop("MSF_BATCH_CONFIG")
+    for g, k in enumerate(sizes):
+        assert counts[g] == k - 1 and totals[g][0] == (k - 1) * (k - 2) // 2, k
+        assert torch.equal(ids[vo[g]:vo[g] + k - 1], parts[g][2][:-1]), k
+    if n >= 20000:  # (0.1 and 1.4 ms; a step per vertex and thread: 13 ms and more)
+        assert ms < 5.0 and batch_ms < 20.0, (ms, batch_ms)
+    c.close()
