@@ -142,7 +142,7 @@ template <int NT>
 struct PCtl {
     uint32_t cnt[2][NT / 64];  // kept edges per wave, alternating tiles
     uint32_t hist[256];
-    uint32_t bin, rank;
+    uint32_t bin, rank, same;
     uint32_t live, dead, hooks;
     uint32_t g;     // graph being solved (NONE32: queue empty)
     uint32_t err;   // ERR_* seen by this workgroup
@@ -774,9 +774,12 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
         pc.gerr = 0;
         pc.dead = 0;
     }
-    uint32_t T = 0xFFFFFFFFu;
+    uint64_t T = ~0ull;  // weight key, edge
     if (two) {
-        // the threshold: the weight at the light edges' share of a sample
+        // the threshold: the weight at the light edges' share of a sample, and
+        // the last edge of that weight (with the weight alone, equal weights
+        // would all be light: 3 graphs of 10^6 vertices and 3 * 10^6 edges of
+        // one weight 102 ms, 52 ms with the edge)
         const uint32_t pos = (uint32_t)((uint64_t)m * tid / NT) +
                              (tid * 0x9E3779B9u >> 8) % max(1u, m / NT);
         const uint32_t wk = weight_key(W[min(pos, m - 1)], WT);
@@ -796,6 +799,7 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
                     if (want >= ex && want < ex + c[q]) {
                         pc.bin = tid * 4 + q;
                         pc.rank = want - ex;
+                        pc.same = c[q];
                     }
                     ex += c[q];
                 }
@@ -805,7 +809,17 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
             want = uniform(pc.rank);
             __syncthreads();
         }
-        T = pre;
+        T = ((uint64_t)pre << 32) | 0xFFFFFFFFu;
+        if (uniform(pc.same) > 1) {
+            // (the sample lies in the order of the edges)
+            const uint64_t eq = __ballot(wk == pre);
+            if (__lane_id() == 0) pc.hist[tid >> 6] = (uint32_t)__popcll(eq);
+            __syncthreads();
+            for (uint32_t k = 0; k < (tid >> 6); ++k) want -= pc.hist[k];
+            if (wk == pre && (uint32_t)__popcll(eq & lanemask_lt()) == want) pc.rank = pos;
+            __syncthreads();
+            T = ((uint64_t)pre << 32) | uniform(pc.rank);
+        }
     }
     __syncthreads();
     // the list: every edge read and checked, those up to the threshold kept;
@@ -851,7 +865,8 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
                 if (WT == MSF_W_F32 && (x[q].w & 0x7FFFFFFFu) > 0x7F800000u) bad |= ERR_NAN;
                 err |= bad;
                 x[q].w = weight_key(x[q].w, WT);
-                keep[q] = base + (me + 64u * q) < m && !bad && x[q].a != x[q].b && x[q].w <= T;
+                keep[q] = base + (me + 64u * q) < m && !bad && x[q].a != x[q].b &&
+                          (((uint64_t)x[q].w << 32) | x[q].e) <= T;
                 const uint64_t mask = __ballot(keep[q]);
                 pos[q] = c + (uint32_t)__popcll(mask & lanemask_lt());
                 c += (uint32_t)__popcll(mask);

@@ -447,3 +447,47 @@ def test_long_chains_in_one_workgroup(pkg, n, falling):
     if n >= 20000:  # (0.1 and 1.4 ms; a step per vertex and thread: 13 ms and more)
         assert ms < 5.0 and batch_ms < 20.0, (ms, batch_ms)
     c.close()
+
+
+@pytest.mark.parametrize("config", [0, 2, 7])
+def test_batched_equal_weights(pkg, config):
+    """Where the threshold of a batch's light edges falls among equal
+    weights, the edge decides: the same forests, and a graph of one weight
+    takes no longer than one of many."""
+    c = pkg.Context(0)
+    rng = np.random.default_rng(37)
+    sizes = [(512, 2048), (512, 2049), (1000, 4100), (3000, 20000), (20000, 70000), (70000, 300000)]
+    e = np.concatenate([rng.integers(0, n, size=(m, 2)) for n, m in sizes]).astype(np.int32)
+    vo = np.cumsum([0] + [n for n, _ in sizes])
+    eo = np.cumsum([0] + [m for _, m in sizes])
+    wide = rng.integers(0, 1 << 32, size=len(e), dtype=np.uint64).astype(np.uint32)
+    os.environ["MSF_BATCH_CONFIG"] = str(config)
+    try:
+        for w, wt, label in ((np.full(len(e), 0xFFFFFFFF, np.uint32), U32, "largest"),
+                             (np.zeros(len(e), np.uint32), U32, "zero"),
+                             (np.where(wide & 1, wide, np.uint32(1 << 20)), U32, "half equal"),
+                             (np.arange(len(e), dtype=np.uint32) // 5000, U32, "rising blocks"),
+                             (np.full(len(e), -0.0, np.float32), F32, "float")):
+            print("[gpu-case] equal weights", config, label, flush=True)
+            ids, counts, totals = c.solve_batched(vo, eo, dev(e), dev(w), wtype=wt)
+            torch.cuda.synchronize()
+            ids = ids.cpu().numpy()
+            for g, (n, m) in enumerate(sizes):
+                wi, wc, wtot = oracle.msf(n, e[eo[g]:eo[g + 1]], w[eo[g]:eo[g + 1]], wt)
+                assert counts[g] == wc and totals[g][1] == wtot[1], (label, n)
+                assert np.array_equal(ids[vo[g]:vo[g] + wc].astype(np.int64), wi), (label, n)
+        if config == 7:
+            n, m, G = 40000, 160000, 200
+            de = dev(np.tile(rng.integers(0, n, size=(m, 2)).astype(np.int32), (G, 1)))
+            vo, eo = np.arange(G + 1) * n, np.arange(G + 1) * m
+            ms = []
+            for w in (rng.integers(0, 1 << 32, size=G * m, dtype=np.uint64).astype(np.uint32),
+                      np.ones(G * m, np.uint32)):
+                dw = dev(w)
+                for _ in range(3):
+                    c.solve_batched(vo, eo, de, dw, wtype=U32)
+                ms.append(c.stats()["batch_ms"])
+            assert ms[1] < 1.4 * ms[0], ms  # (0.9; 1.9 with every edge light)
+    finally:
+        os.environ.pop("MSF_BATCH_CONFIG")
+        c.close()
