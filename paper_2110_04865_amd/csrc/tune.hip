@@ -3,10 +3,11 @@
 // The launch configuration (threads per workgroup, edges per thread and
 // load round, dynamic LDS per workgroup) is picked per batch shape by
 // timing every candidate on a sample of the batch.  The choice is cached
-// per (architecture, log2 of the mean vertex count, log2 of the mean stored
-// entries per vertex, weight type), in memory for the process and, when
-// MSF_TUNE_CACHE names a file, in that file across processes (one line per
-// shape: arch nb db wt candidate).  MSF_BATCH_CONFIG=<index> forces a
+// per (architecture and form of the kernel, log2 of the mean vertex count,
+// log2 of the mean stored entries per vertex, weight type), in memory for the
+// process and, when MSF_TUNE_CACHE names a file, in that file across processes
+// (one line per shape: arch/form nb db wt candidate; lines of another form
+// are passed over).  MSF_BATCH_CONFIG=<index> forces a
 // candidate.  Every candidate computes the same forests (the result does
 // not depend on the schedule); only the time differs.
 #include <cmath>
@@ -111,7 +112,8 @@ msf_status persist_pick(Ctx *c, const BatchShape &shape, int wt, const PersistTu
         *chosen = i;
         return MSF_OK;
     }
-    const Key key(arch_of(c->device), ilog2(shape.mean_n), ilog2(shape.mean_deg), wt);
+    const Key key(arch_of(c->device) + "/" + std::to_string(PERSIST_FORM), ilog2(shape.mean_n),
+                  ilog2(shape.mean_deg), wt);
     {
         std::lock_guard<std::mutex> lk(g_mu);
         load_cache();

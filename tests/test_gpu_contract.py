@@ -491,3 +491,44 @@ def test_batched_equal_weights(pkg, config):
     finally:
         os.environ.pop("MSF_BATCH_CONFIG")
         c.close()
+
+
+TUNED_BATCH = """
+import numpy as np, torch
+import paper_2110_04865_amd as pkg
+rng = np.random.default_rng(41)
+n, m, G = 40000, 160000, 20
+e = torch.from_numpy(rng.integers(0, n, size=2 * G * m).astype(np.int32)).to("cuda:0")
+w = torch.from_numpy(rng.integers(0, 1 << 30, size=G * m).astype(np.int32)).to("cuda:0")
+c = pkg.Context(0)
+c.solve_batched(np.arange(G + 1) * n, np.arange(G + 1) * m, e, w, wtype=pkg.W_U32)
+print("config", c.stats()["batch_config"], flush=True)
+"""
+
+
+def test_saved_choice_of_an_older_kernel(pkg, tmp_path):
+    """The tuner passes over choices saved for an older form of the kernel
+    (or for none) and keeps to those of its own."""
+    import subprocess
+    import sys
+    path = tmp_path / "tune.txt"
+    env = {k: v for k, v in os.environ.items() if k != "MSF_BATCH_CONFIG"}
+    env.update(MSF_TUNE_CACHE=str(path),
+               PYTHONPATH=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+
+    def run():
+        out = subprocess.run([sys.executable, "-c", TUNED_BATCH], env=env, capture_output=True,
+                             text=True, timeout=100)
+        assert out.returncode == 0, out.stderr[-2000:]
+        return int(out.stdout.split("config")[1])
+
+    shape = "15 3 0"  # log2 of 40000 vertices and of 8 entries each, uint32
+    path.write_text(f"gfx950 {shape} 0\ngfx950/1 {shape} 0\n")
+    first = run()
+    assert first != 0  # (256 threads and 32 KB: several times the fastest)
+    lines = path.read_text().split("\n")
+    assert len(lines) == 4 and lines[2].split()[1:] == f"{shape} {first}".split(), lines
+    mine = lines[2].split()[0]
+    path.write_text(f"{mine} {shape} 3\n")
+    assert run() == 3
+    assert path.read_text() == f"{mine} {shape} 3\n"
