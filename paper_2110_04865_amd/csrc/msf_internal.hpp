@@ -334,9 +334,9 @@ struct Ctx {
     // in a separate 2-byte array (0)
     int tl_row_in_col = 1;
     // rounds over a contracted edge list, light edges first, instead of an
-    // adjacency matrix: 0 never, 1 for graphs too large for one workgroup
-    // while the settings above have their defaults (small_m above 0), 2
-    // always
+    // adjacency matrix: 0 never, 1 while the settings above have their
+    // defaults (small_m above 0), 2 always (msf_solve has small graphs solved
+    // by one workgroup first, the server in shared launches)
     int contract = 1;
     // failure-path test hook (MSF_TEST_FAIL_ALLOC_AFTER): after this many
     // workspace allocations the next one is refused once, without calling

@@ -213,3 +213,47 @@ def test_shared_launches_equal_slots(ctx, pkg):
         k += 1
         wi, wc, wt = oracle.msf(n, e, w, F32)
         assert cnt == wc and np.array_equal(ids.astype(np.int64), wi) and tot[1] == wt[1]
+
+
+def test_requests_beside_the_shared_launches(pkg, monkeypatch):
+    """Requests too large for the shared launches take the contracted rounds
+    even where msf_solve would have one workgroup solve them: a smaller
+    request is not the slower one.  With the shared launches off, requests
+    down to one edge take them too."""
+    c = pkg.Context(0)
+    rng = np.random.default_rng(43)
+
+    def graph(n, m):
+        return (n, rng.integers(0, n, size=(m, 2)).astype(np.int32),
+                rng.integers(0, 1 << 32, size=m, dtype=np.uint64).astype(np.uint32))
+
+    def served(srv, n, e, w):
+        t = srv.submit(n, e, w, wtype=U32)
+        ids, cnt, tot = srv.result(t, n)
+        want_ids, want_cnt, want_tot = oracle.msf(n, e, w, U32)
+        assert cnt == want_cnt and tot == want_tot
+        assert np.array_equal(ids.astype(np.int64), want_ids)
+
+    srv = pkg.Server(c, 4 << 30)
+    ms = {}
+    for n, m in ((8000, 22000), (10000, 20000), (16000, 40000)):
+        g = graph(n, m)
+        served(srv, *g)
+        lat = []
+        for _ in range(40):
+            t = srv.submit(*g, wtype=U32)
+            while not srv.poll(t):
+                time.sleep(1e-5)
+            lat.append(srv.latency(t) * 1e3)
+            srv.result(t, n)
+        ms[n] = sorted(lat)[20]
+    say("latency of requests of their own", ms)
+    # (0.2-0.3 ms each; over an adjacency matrix the first two took 0.6 and 0.7)
+    assert ms[8000] < 1.6 * ms[16000] and ms[10000] < 1.6 * ms[16000], ms
+    srv.close()
+    monkeypatch.setenv("MSF_SERVER_BATCH", "0")
+    srv = pkg.Server(c, 4 << 30)
+    for n, m in ((1, 0), (1, 3), (2, 1), (2, 0), (30, 100), (300, 255), (1000, 257), (7000, 5000)):
+        served(srv, *graph(n, m))
+    srv.close()
+    c.close()
