@@ -193,6 +193,7 @@ msf_status ctx_init(Ctx *c, int device, hipStream_t stream, bool async_alloc)
     if (const char *f = getenv("MSF_GRAPH_ROUNDS_MAX_N")) c->graph_rounds_max_n = atoll(f);
     if (const char *f = getenv("MSF_TL_ROW_IN_COL")) c->tl_row_in_col = atoi(f);
     if (const char *f = getenv("MSF_CONTRACT")) c->contract = atoi(f);
+    if (const char *f = getenv("MSF_CONTRACT_SWEEPS")) c->contract_sweeps = std::max(1, atoi(f));
     if (const char *f = getenv("MSF_TEST_FAIL_ALLOC_AFTER")) c->fail_alloc_after = atoll(f);
     return MSF_OK;
 }

@@ -53,6 +53,7 @@ struct CtArgs {
     uint64_t *mat = nullptr;   // pair minima of a phase's last vertices
     uint8_t *flags = nullptr;
     int64_t *wpart = nullptr;
+    uint32_t sweeps = 0;  // visits of a large round's chase to a vertex
     Counters *cnt = nullptr;
 };
 
@@ -70,6 +71,9 @@ void ct_select(hipStream_t s, const CtArgs &A);
 // One round; big: also the kernels that a round with many vertices needs
 // (bound: the most vertices it can have).
 void ct_round(hipStream_t s, const CtArgs &A, int k, bool big, uint32_t bound);
+// Round k (of L vertices), whose chase gave up, to its end: every chain
+// shortened by launches of its own, then the chase.
+void ct_far(hipStream_t s, CtArgs A, int k, uint32_t L);
 // Trees of phase 0 per vertex, the largest one's membership bits, and the
 // list of the edges between different trees.
 void ct_between(hipStream_t s, const CtArgs &A, uint32_t *comp, uint32_t *bits);

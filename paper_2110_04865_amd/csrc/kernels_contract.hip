@@ -971,13 +971,19 @@ __global__ __launch_bounds__(TIE_NT) void k_ct_hook(CtArgs A, int k)
 // takes its number; improvements are written back, so other chains get
 // shorter (the hooks form no cycle after the tie break).  A thread takes at
 // most CT_WALK steps for one of its vertices and comes back to those that
-// are not there yet after all its others: the length of every chain is then
-// divided by CT_WALK + 1 each time, as long as all workgroups are on the chip
-// (at most CHASE_WG).  Walked to the end at once, a chain that leads from
-// early vertices to late ones, which nobody has shortened yet, takes a step
-// per vertex: a path of 2 * 10^6 vertices with falling weights 1165 ms a
-// solve, 0.26 ms with this (4 / 8 / 16 steps: 16 * 10^6 vertices 1.31 / 1.39 /
-// 1.60 ms; R-MAT s22, grids and random graphs even).
+// are not there yet after all its others.  Where that does not end within
+// A.sweeps visits, the solve stops (ERR_FAR) and goes on behind ct_far.
+//
+// Walked to the end at once, a chain that leads from early vertices to late
+// ones, which nobody has shortened yet, takes a step per vertex: a path of 2 *
+// 10^6 vertices with falling weights 1165 ms a solve, 0.26 ms with this (4 /
+// 8 / 16 steps: 16 * 10^6 vertices 1.31 / 1.39 / 1.60 ms; R-MAT s22, grids and
+// random graphs even).  All workgroups are on the chip together (CHASE_WG),
+// which makes the chains shrink everywhere at once; but a compute die's L2 can
+// hold a target as it was first read, so only the end of a launch is sure to
+// show every improvement (with 16 unrolled steps the same path fell back to
+// 157 ms at 4 * 10^6 vertices).  Giving up after 1 / 16 visits, us a solve:
+// falling paths of 5 * 10^5 and 4 * 10^6 vertices 198 / 152 and 502 / 420.
 constexpr int CT_WALK = 8;
 constexpr unsigned CHASE_WG = 2048;
 
@@ -992,7 +998,7 @@ __global__ __launch_bounds__(256) void k_ct_chase(CtArgs A, int k)
     const uint64_t stride = (uint64_t)gridDim.x * 256;
     const uint64_t i0 = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     uint64_t left = ~0ull;  // its vertices to look at (the last bit: all from the 64th on)
-    for (uint32_t sweep = 0; left; ++sweep) {
+    for (uint32_t sweep = 0; left && sweep < A.sweeps; ++sweep) {
         uint64_t far = 0, bit = 1;
         for (uint64_t i = i0; i < L; i += stride) {
             if (left & bit) {
@@ -1013,15 +1019,44 @@ __global__ __launch_bounds__(256) void k_ct_chase(CtArgs A, int k)
             if (bit << 1) bit <<= 1;
         }
         left = far;
-        if (far && sweep > L / CT_WALK) {  // cannot happen: a cycle of hooks
-            atomicOr(&c->err, ERR_CYCLE);
-            break;
-        }
+    }
+    if (__ballot(left != 0) && __lane_id() == 0) {
+        c->ct.far = (uint32_t)(A.ph * CT_ROUNDS + k);
+        if (!(load_relaxed_u32(&c->err) & ERR_FAR)) atomicOr(&c->err, ERR_FAR);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         c->ct.done[A.ph][k] = 1;
         if (Ln == 0) c->ct.phdone[A.ph] = 1;
     }
+}
+
+// CT_WALK steps along every chain of round k.  Each launch sees what the one
+// before it wrote, so it leaves at most 1 / (CT_WALK + 1) of every chain.
+__global__ __launch_bounds__(256) void k_ct_jump(CtArgs A, int k)
+{
+    const uint32_t L = A.cnt->ct.L[A.ph][k];
+    const uint64_t stride = (uint64_t)gridDim.x * 256;
+    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < L; i += stride) {
+        const uint32_t x0 = load_relaxed_u32(A.h + i);
+        uint32_t x = x0;
+        for (int q = 0; q < CT_WALK; ++q) {
+            const uint32_t y = load_relaxed_u32(A.h + x);
+            if (y == x) break;
+            x = y;
+        }
+        if (x != x0) store_relaxed_u32(A.h + i, x);
+    }
+}
+
+__global__ void k_ct_jumped(CtArgs A) { A.cnt->err = 0; }
+
+void ct_far(hipStream_t s, CtArgs A, int k, uint32_t L)
+{
+    for (uint64_t len = L; len > 1; len = (len + CT_WALK) / (CT_WALK + 1))
+        k_ct_jump<<<grid_for(L, 256, 8192), 256, 0, s>>>(A, k);
+    k_ct_jumped<<<1, 1, 0, s>>>(A);
+    A.sweeps = 1;
+    k_ct_chase<<<grid_for(L, 256, CHASE_WG), 256, 0, s>>>(A, k);
 }
 
 void ct_round(hipStream_t s, const CtArgs &A, int k, bool big, uint32_t bound)

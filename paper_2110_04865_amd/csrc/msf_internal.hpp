@@ -53,7 +53,8 @@ enum : uint32_t {
     ERR_NAN = 2u,
     ERR_PARENT = 4u,
     ERR_CYCLE = 8u,
-    ERR_STAR = 16u  // round check: a tree that is not a star after shortcutting
+    ERR_STAR = 16u,  // round check: a tree that is not a star after shortcutting
+    ERR_FAR = 32u    // contracted rounds: chains that the chase gave up
 };
 
 // ---------------------------------------------------------------- device --
@@ -160,7 +161,7 @@ struct Counters {
         uint32_t giant;                // the tree most sampled edges lie in
         uint32_t fin;                  // every phase complete, total known
         uint32_t E0[2];                // edges on a phase's list
-        uint32_t pad;
+        uint32_t far;                  // ERR_FAR: phase * CT_ROUNDS + round
         uint64_t T;                    // phase 0 takes keys up to this one
         uint64_t clk[4];               // device clock: start, list made, first round done, end
     } ct;
@@ -263,6 +264,7 @@ struct SolveState {
     size_t ct_words = 0;      // its buffers: words of the flags
     uint32_t ct_W = 0;        // its list segments
     uint32_t ct_pass = 0;     // waves of its edge passes
+    int ct_far = -1;          // the last round whose chase gave up
     int ri = 0, ai = 0, rounds = 0;
     int sweep_events = 0;     // rounds whose sweep start/end events were recorded
     double live_frac = 1.0;
@@ -338,6 +340,10 @@ struct Ctx {
     // defaults (small_m above 0), 2 always (msf_solve has small graphs solved
     // by one workgroup first, the server in shared launches)
     int contract = 1;
+    // visits to a vertex after which a large round's chase gives up its
+    // chains to launches of their own (MSF_CONTRACT_SWEEPS, for tests: any
+    // number gives the same forests)
+    int contract_sweeps = 16;
     // failure-path test hook (MSF_TEST_FAIL_ALLOC_AFTER): after this many
     // workspace allocations the next one is refused once, without calling
     // the allocator (-1: never)

@@ -224,6 +224,7 @@ static msf_status contract_args(Ctx *c, CtArgs *A)
     A->mat = (uint64_t *)(A->wlist + 2 * CT_SMALL);
     A->flags = (uint8_t *)v[8];
     A->wpart = (int64_t *)v[9];
+    A->sweeps = (uint32_t)c->contract_sweeps;
     A->cnt = c->dcnt;
     return MSF_OK;
 }
@@ -308,6 +309,19 @@ static msf_status contract_advance(Ctx *c)
         return MSF_EDEVICE;
     }
     MSF_TRY(decode_err(h->err));
+    if (h->err & ERR_FAR) {
+        const int ph = (int)(h->ct.far / CT_ROUNDS), k = (int)(h->ct.far % CT_ROUNDS);
+        if (c->ss.ct_far == (int)h->ct.far) {
+            set_error("internal error: hook cycle detected");
+            return MSF_EDEVICE;
+        }
+        c->ss.ct_far = (int)h->ct.far;
+        CtArgs A;
+        MSF_TRY(contract_args(c, &A));
+        A.ph = ph;
+        ct_far(c->stream, A, k, h->ct.L[ph][k]);
+        return contract_enqueue(c, ph, k + 1, h->ct.L[ph][k + 1]);
+    }
     if (!h->ct.fin) {
         // more rounds than were enqueued: go on from the first open one
         const int ph = h->ct.phdone[0] ? 1 : 0;

@@ -532,3 +532,43 @@ def test_saved_choice_of_an_older_kernel(pkg, tmp_path):
     path.write_text(f"{mine} {shape} 3\n")
     assert run() == 3
     assert path.read_text() == f"{mine} {shape} 3\n"
+
+
+@pytest.mark.parametrize("sweeps", [1, 2, 3])
+def test_chains_given_up(pkg, sweeps):
+    """Where the chase of a large round gives up, the solve goes on behind
+    launches that follow the chains: in either phase, more than once a
+    solve, and after it on the same context."""
+    old = {k: os.environ.get(k) for k in ("MSF_CONTRACT", "MSF_SMALL_M", "MSF_CONTRACT_SWEEPS")}
+    os.environ.update(MSF_CONTRACT="2", MSF_SMALL_M="0", MSF_CONTRACT_SWEEPS=str(sweeps))
+    try:
+        c = pkg.Context(0)
+    finally:
+        for k, v in old.items():
+            if v is None:
+                os.environ.pop(k, None)
+            else:
+                os.environ[k] = v
+    rng = np.random.default_rng(47)
+    n = 300000
+    check(c, *path_graph(n, np.arange(n - 1, 0, -1)), U32, "falling path")
+    check(c, *path_graph(n, np.arange(n - 1)), U32, "rising path")
+    # chains of 100 vertices, joined by random heavier edges: long chains in
+    # a first round, others in the next
+    i = np.arange(n - 1)
+    check(c, *path_graph(n, np.where(i % 100 == 99, (1 << 20) + i[::-1], i[::-1])), U32, "pieces")
+    # phase 1: loops are the light edges
+    loops = np.stack([np.arange(n)] * 2, 1).astype(np.int32)
+    e = np.concatenate([loops] * 6 + [path_graph(n, i)[1]])
+    w = np.concatenate([np.zeros(6 * n), 5 + i[::-1]]).astype(np.uint32)
+    check(c, n, e, w, U32, "falling path among light loops")
+    e, w = gen.er(n, 4 * n, seed=48)
+    check(c, n, e, w, U32, "random")
+    e = rng.permutation(n).astype(np.int32)[path_graph(n, i)[1]]
+    check(c, n, e, i[::-1].astype(np.uint32), U32, "permuted falling path")
+    be = path_graph(n, i)[1].copy()
+    be[77, 1] = n
+    with pytest.raises(pkg.MSFError):
+        c.solve(n, dev(be), dev(i.astype(np.uint32)), wtype=U32)
+    check(c, n, *gen.er(n, n, seed=49), U32, "after a refused one")
+    c.close()
