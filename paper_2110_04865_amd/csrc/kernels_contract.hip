@@ -523,9 +523,10 @@ __device__ void ct_pair_rounds(const CtArgs &A, int k, uint32_t L, const CtSmall
 // would take one atomic after another on one address, 3 ns each: the read
 // in front of an atomic sees what its XCD's L2 holds, not the latest value.
 // Each workgroup samples its edges, and the vertices with at least one in
-// CT_HOT_SHARE of the live ones (and CT_HOT_MIN of them) keep their minimum in
-// LDS until the end of the pass.
-constexpr uint32_t CT_HOT = 512, CT_HOT_MIN = 4, CT_HOT_SHARE = 64;
+// CT_HOT_SHARE of the live ones (and CT_HOT_MIN of them: with 4 the few edges
+// of late rounds fill many slots by chance, grid 60^3 274 us a solve, 270 with
+// 8) keep their minimum in LDS until the end of the pass.
+constexpr uint32_t CT_HOT = 512, CT_HOT_MIN = 8, CT_HOT_SHARE = 64;
 constexpr uint32_t CT_READ = 320;  // edges of a wave above which minima are read first
 
 __device__ __forceinline__ uint32_t ct_hot_slot(uint32_t v) { return (v * 0x9E3779B1u) >> 23; }
@@ -689,10 +690,10 @@ __device__ __forceinline__ uint32_t ct_pass(const CtArgs &A, int k, uint32_t L,
     }
     for (uint32_t i = tid; i < CT_HOT; i += CE_NT) {
         s_tag[i] = NONE32;
-        s_num[i] = 0;
+        s_num[i] = s_num[CT_HOT + i] = 0;
         s_r[i] = KEY_INF;
     }
-    if (tid < 2) s_c[tid] = 0;
+    if (tid < 4) s_c[tid] = 0;
     __syncthreads();
     // the first edges of every wave are the sample
     const uint32_t cnt0 = ct_uniform(A.cw[wv]);
@@ -717,17 +718,40 @@ __device__ __forceinline__ uint32_t ct_pass(const CtArgs &A, int k, uint32_t L,
     if (lane == 0 && lv) atomicAdd(&s_c[1], (uint32_t)__popcll(lv));
     __syncthreads();
     const uint32_t hot = max(CT_HOT_MIN, s_c[1] / CT_HOT_SHARE);
-    if (va != vb) {
-        if (s_num[ct_hot_slot(va)] >= hot) {
-            s_tag[ct_hot_slot(va)] = va;
-            s_c[0] = 1;
+    // the vertex of each slot with that many ends: any of them is proposed and
+    // its own ends are counted, the next one if they are too few (a slot's
+    // other vertices: with the last one written taken unseen, a hub lost its
+    // slot to a leaf in one workgroup of ten: a star of 10^6 vertices 804 us a
+    // solve, 146 us with the count; 2 * 10^6 edges of 3 hubs 1690 / 265 us)
+    uint32_t *s_hit = s_num + CT_HOT;
+    const uint32_t la = ct_hot_slot(va), lb = ct_hot_slot(vb);
+    bool ca = va != vb && s_num[la] >= hot, cb = va != vb && s_num[lb] >= hot;
+    if (ca || cb) s_c[0] = 1;
+    for (int t = 0; t < 4; ++t) {
+        if (ca) s_tag[la] = va;
+        if (cb) s_tag[lb] = vb;
+        __syncthreads();
+        if (!s_c[0] || s_c[2] != (uint32_t)t) break;
+        const uint32_t ta = ca ? s_tag[la] : NONE32, tb = cb ? s_tag[lb] : NONE32;
+        if (ca && ta == va) atomicAdd(&s_hit[la], 1u);
+        if (cb && tb == vb) atomicAdd(&s_hit[lb], 1u);
+        __syncthreads();
+        const bool ha = ca && s_hit[la] >= hot, hb = cb && s_hit[lb] >= hot;
+        __syncthreads();
+        if (ca && !ha && ta == va) {
+            s_tag[la] = NONE32;
+            s_hit[la] = 0;
         }
-        if (s_num[ct_hot_slot(vb)] >= hot) {
-            s_tag[ct_hot_slot(vb)] = vb;
-            s_c[0] = 1;
+        if (cb && !hb && tb == vb) {
+            s_tag[lb] = NONE32;
+            s_hit[lb] = 0;
         }
+        ca = ca && !ha && ta != va;
+        cb = cb && !hb && tb != vb;
+        if (ca || cb) s_c[2] = t + 1;
+        if (ha || hb) s_c[3] = 1;
+        __syncthreads();
     }
-    __syncthreads();
     // Whether minima are read before an atomic.  A wave with few edges sends
     // them all at once, before any read could show a minimum, and reading
     // lines that atomics change is slow (passes over 271 / 113 / 70 / 60 edges
@@ -735,7 +759,7 @@ __device__ __forceinline__ uint32_t ct_pass(const CtArgs &A, int k, uint32_t L,
     // the read, 62 / 48 / 26 / 26 us without; over 472 edges a wave, phase 1
     // of R-MAT s22: 150 us with it, 336 us without).
     const bool read = cnt0 > CT_READ;
-    if (s_c[0]) {
+    if (s_c[3]) {
         CT_SEGMENTS(CT_MIN_HOT, read)
         __syncthreads();
         for (uint32_t i = tid; i < CT_HOT; i += CE_NT) {
@@ -773,7 +797,7 @@ __global__ __launch_bounds__(CE_NT, 8) void k_ct_edges(CtArgs A, int k, int big)
     __shared__ uint32_t s_cnt[CE_WV];
     __shared__ uint32_t s_c[4];
     static_assert(2 * (sizeof s_r + sizeof s_cum + 256) <= 160 << 10, "two workgroups a CU");
-    static_assert(sizeof s_cum >= 8 * CT_HOT, "tags and counts in the map's place");
+    static_assert(sizeof s_cum >= 12 * CT_HOT, "tags and counts in the map's place");
     Counters *c = A.cnt;
     if (A.ph == 0 && k <= 1 && blockIdx.x == 0 && threadIdx.x == 0 && !c->ct.clk[1 + k])
         c->ct.clk[1 + k] = wall_clock64();

@@ -572,3 +572,34 @@ def test_chains_given_up(pkg, sweeps):
         c.solve(n, dev(be), dev(i.astype(np.uint32)), wtype=U32)
     check(c, n, *gen.er(n, n, seed=49), U32, "after a refused one")
     c.close()
+
+
+def test_hubs_cost_no_more_than_random_edges(pkg):
+    """Edges that all lead to a few hubs (a star among them) lower their
+    minima in LDS in every workgroup, whatever other vertices share the hubs'
+    places in the table: about the time of as many random edges."""
+    import time
+    c = pkg.Context(0)
+    rng = np.random.default_rng(53)
+    n, m = 500000, 2000000
+
+    def ms(e, w):
+        de, dw = dev(e), dev(w)
+        best = 1e9
+        for _ in range(5):
+            t0 = time.perf_counter()
+            ids, cnt, tot = c.solve(n, de, dw, wtype=U32)
+            best = min(best, (time.perf_counter() - t0) * 1e3)
+        want_ids, want_cnt, want_tot = oracle.msf(n, e, w, U32)
+        assert cnt == want_cnt and tot[0] == want_tot[0]
+        assert np.array_equal(ids.cpu().numpy().astype(np.int64), want_ids)
+        return best
+
+    w = rng.integers(0, 1 << 32, size=m, dtype=np.uint64).astype(np.uint32)
+    spread = ms(rng.integers(0, n, size=(m, 2)).astype(np.int32), w)
+    for k in (1, 3, 40):
+        e = np.stack([rng.integers(0, k, size=m) * (n // k), rng.integers(0, n, size=m)], 1)
+        hubs = ms(e.astype(np.int32), w)
+        print("[gpu-case]", k, "hubs", hubs, "ms, random edges", spread, flush=True)
+        assert hubs < 1.5 * spread, (k, hubs, spread)
+    c.close()
