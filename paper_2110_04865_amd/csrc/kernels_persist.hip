@@ -740,6 +740,13 @@ __device__ __forceinline__ void graph_results(const PersistArgs &A, uint32_t g, 
     __syncthreads();
 }
 
+// The edge that thread t samples for the threshold of the light edges.
+template <int NT>
+__device__ __forceinline__ uint32_t sampled_edge(uint32_t t, uint32_t m)
+{
+    return min((uint32_t)((uint64_t)m * t / NT) + (t * 0x9E3779B9u >> 8) % max(1u, m / NT), m - 1);
+}
+
 // The forest of graph g; flags (one byte per edge, in the slot) are set for
 // its edges.  Returns false if the graph failed validation.
 template <int NT, int U, int WT, bool P16>
@@ -774,15 +781,13 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
         pc.gerr = 0;
         pc.dead = 0;
     }
-    uint64_t T = ~0ull;  // weight key, edge
+    uint32_t T = 0xFFFFFFFFu, Te = 0xFFFFFFFFu;  // weight key, edge
     if (two) {
         // the threshold: the weight at the light edges' share of a sample, and
         // the last edge of that weight (with the weight alone, equal weights
         // would all be light: 3 graphs of 10^6 vertices and 3 * 10^6 edges of
         // one weight 102 ms, 52 ms with the edge)
-        const uint32_t pos = (uint32_t)((uint64_t)m * tid / NT) +
-                             (tid * 0x9E3779B9u >> 8) % max(1u, m / NT);
-        const uint32_t wk = weight_key(W[min(pos, m - 1)], WT);
+        const uint32_t wk = weight_key(W[sampled_edge<NT>(tid, m)], WT);
         uint32_t pre = 0, want = (uint32_t)((uint64_t)light * NT / m);
         for (int sh = 24; sh >= 0; sh -= 8) {
             for (uint32_t k = tid; k < 256; k += NT) pc.hist[k] = 0;
@@ -809,16 +814,20 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
             want = uniform(pc.rank);
             __syncthreads();
         }
-        T = ((uint64_t)pre << 32) | 0xFFFFFFFFu;
+        T = pre;
         if (uniform(pc.same) > 1) {
-            // (the sample lies in the order of the edges)
-            const uint64_t eq = __ballot(wk == pre);
-            if (__lane_id() == 0) pc.hist[tid >> 6] = (uint32_t)__popcll(eq);
+            // (the sample lies in the order of the edges; read once more, since
+            // held in registers it slows the rest down by 2%)
+            const uint32_t t = opaque_tid(), pos = sampled_edge<NT>(t, m);
+            const bool same = weight_key(W[pos], WT) == T;
+            const uint64_t eq = __ballot(same);
+            if (__lane_id() == 0) pc.hist[t >> 6] = (uint32_t)__popcll(eq);
             __syncthreads();
-            for (uint32_t k = 0; k < (tid >> 6); ++k) want -= pc.hist[k];
-            if (wk == pre && (uint32_t)__popcll(eq & lanemask_lt()) == want) pc.rank = pos;
+            uint32_t at = (uint32_t)__popcll(eq & lanemask_lt());
+            for (uint32_t k = 0; k < (t >> 6); ++k) at += pc.hist[k];
+            if (same && at == want) pc.rank = pos;
             __syncthreads();
-            T = ((uint64_t)pre << 32) | uniform(pc.rank);
+            Te = uniform(pc.rank);
         }
     }
     __syncthreads();
@@ -847,6 +856,9 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
             PEdge x[U];
             uint32_t pos[U], c = 0;
             bool keep[U];
+            // edges of the threshold's weight up to the tile that holds the
+            // last of them
+            const uint32_t Tt = base <= Te ? T : T - 1, mt = base <= Te || T ? m : 0u;
 #pragma unroll
             for (int q = 0; q < U; ++q)
                 x[q] = PEdge{(uint32_t)uv[q].x, (uint32_t)uv[q].y, wn[q],
@@ -865,8 +877,7 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
                 if (WT == MSF_W_F32 && (x[q].w & 0x7FFFFFFFu) > 0x7F800000u) bad |= ERR_NAN;
                 err |= bad;
                 x[q].w = weight_key(x[q].w, WT);
-                keep[q] = base + (me + 64u * q) < m && !bad && x[q].a != x[q].b &&
-                          (((uint64_t)x[q].w << 32) | x[q].e) <= T;
+                keep[q] = base + (me + 64u * q) < mt && !bad && x[q].a != x[q].b && x[q].w <= Tt;
                 const uint64_t mask = __ballot(keep[q]);
                 pos[q] = c + (uint32_t)__popcll(mask & lanemask_lt());
                 c += (uint32_t)__popcll(mask);
