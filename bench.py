@@ -14,7 +14,8 @@ Also reported on the same JSON line:
                 the run sort and the head sweeps): its algorithmic
                 bytes per launch over its average
                 launch time, both taken inside the timed steps from device
-                events that the library records on the stream those kernels
+                events (contracted rounds: stamps of the device's
+                clock) that the library records on the stream those kernels
                 run on; `traffic` is the counter-measured bytes per launch
                 from the committed profile, reported only when the sources
                 built here are the ones that profile was taken on (else

@@ -141,8 +141,8 @@ typedef struct {
        events from the solve's start to the end of the placement; build_ms
        also holds the head sweep's run set-up and the host step between
        them).  On path 4 there is no adjacency matrix: the selection of the
-       light edges' list, and build_ms also holds the first round's edge
-       pass.  0 with the other builds. */
+       light edges' list, and build_ms also holds the whole first round
+       (device clock).  0 with the other builds. */
     double adjacency_ms;
 } msf_stats;
 

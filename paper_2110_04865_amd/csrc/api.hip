@@ -915,7 +915,9 @@ msf_status msf_solve_starcheck(msf_ctx *ctx, const msf_graph *g, uint8_t *in_for
 
 size_t msf_request_footprint(int32_t n, int64_t m)
 {
-    // the most any path of a solve holds, per edge: input copy (12),
+    // the most any path of a solve holds (the contracted edge list less: per
+    // edge 12 of input, 16 to 32 of list, 1 of flags, per vertex about 48),
+    // that over an adjacency matrix: per edge: input copy (12),
     // two-level build staging (two 16-byte records and a 2-byte row per
     // stored direction: 68), adjacency (24), the filtered twin of the full
     // sweep or the head sweep's run arrays (at most 24.2), forest flags (1)

@@ -19,20 +19,22 @@
 //           the vertices that stay get the next round's numbers, those
 //           without an edge (a finished tree) a tree number;
 //   chase   complete shortcutting (section 4.2), giving every vertex the
-//           number of its new tree.
+//           number of its new tree (chains of hooks that it cannot follow
+//           are left to launches of their own behind a host step, ct_far).
 // So a round costs its live edges once and its vertices a few times, and
 // both shrink; no adjacency matrix is built.
 //
 // Every wave owns one segment of the list, so the compaction is a ballot
 // and an in-place store: no barrier and no counter.  Kernels take their
 // sizes from the counters on the device and return at once when there is
-// nothing to do, so a whole solve is enqueued without a host round trip.
+// nothing to do, so a whole solve is enqueued without a host round trip (one
+// follows if a phase needs more rounds, or a chain is given up).
 // A round of at most CT_FINISH vertices needs only the edge pass: its last
 // workgroup to finish does the rest of the round in LDS.
 //
 // Measured, us a solve over an adjacency matrix / over the list: R-MAT s16
-// (0.91M edges) 672 / 190, grid 101^3 1671 / 475, R-MAT s22 (64M edges) 4436 /
-// 1946, grid 256^3 (47.6M) 8735 / 3423.  Large rounds are bound by lookups
+// (0.91M edges) 672 / 188, grid 101^3 1671 / 459, R-MAT s22 (64M edges) 4436 /
+// 1894, grid 256^3 (47.6M) 8735 / 3407.  Large rounds are bound by lookups
 // (57-205 G/s by the table's size) and device-scope minima (27 G/s), small
 // ones by chains of dependent accesses of 1 us each.
 #include <algorithm>
@@ -603,11 +605,13 @@ __device__ __forceinline__ uint32_t ct_sweep(CtEdge *seg, uint32_t cnt,
             if (ENDS != CT_CUM && MODE != CT_MIN_LDS && MODE != CT_MIN_PAIR) {
                 // the list is in the input's order, where edges often come in
                 // runs of one first end: a run's minimum (within 16 lanes)
-                // leaves from its last lane alone (first round of grid 256^3, 31M light
-                // edges: 361 us, 520 us with one atomic per end; 1.1M random
-                // edges on 10^6 vertices: 90 us either way), and the runs of
-                // the input stay runs while the ends are mapped (R-MAT s19, 4M
-                // edges, a solve: 454 us with the first round only, 421 us)
+                // leaves from its last lane alone (first round of grid 256^3,
+                // 16.4M light edges: 366 us, 522 us with one atomic per end;
+                // random edges either way alike), and the runs of the input
+                // stay runs while the ends are mapped (a solve with one atomic
+                // per end / this: R-MAT s19 527 / 463 us, s20 860 / 737, grid
+                // 101^3 480 / 455, 2^22 vertices and 2^24 random edges 2155 /
+                // 2155)
                 const uint32_t a = live ? x[q].a : NONE32;
                 uint64_t m = live ? x[q].key : KEY_INF;
                 run_min<DPP_ROW_SHR1>(a, m);
@@ -756,8 +760,9 @@ __device__ __forceinline__ uint32_t ct_pass(const CtArgs &A, int k, uint32_t L,
     // them all at once, before any read could show a minimum, and reading
     // lines that atomics change is slow (passes over 271 / 113 / 70 / 60 edges
     // a wave, 10^6 edges on 10^6 vertices and less: 81 / 82 / 51 / 56 us with
-    // the read, 62 / 48 / 26 / 26 us without; over 472 edges a wave, phase 1
-    // of R-MAT s22: 150 us with it, 336 us without).
+    // the read, 62 / 48 / 26 / 26 us without; over 1720 edges a
+    // wave, the first two passes of R-MAT s22: 206 and 292 us with it, 372 and
+    // 389 without).
     const bool read = cnt0 > CT_READ;
     if (s_c[3]) {
         CT_SEGMENTS(CT_MIN_HOT, read)

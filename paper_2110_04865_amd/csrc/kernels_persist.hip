@@ -39,7 +39,7 @@
 // 42.3 ms by an earlier form, which swept the edge list with a parent vector
 // in LDS and the minima in global memory; 7.6 ms by the list; 7.1 ms with the
 // loops over vertices batched (PC_B) and the ids written through LDS.  It
-// moves 22 GB (13 read, 9 written).  The passes over the input run at 4.8
+// moves 21 GB (13.0 read, 8.4 written).  The passes over the input run at 4.8
 // TB/s, memory's rate; between them a graph's one workgroup on its compute
 // unit waits for device memory 70% of the time.
 // Smaller graphs, registers against the list before: 10^4 of 1000 vertices
@@ -748,7 +748,7 @@ __device__ __forceinline__ uint32_t sampled_edge(uint32_t t, uint32_t m)
 }
 
 // The forest of graph g; flags (one byte per edge, in the slot) are set for
-// its edges.  Returns false if the graph failed validation.
+// its edges.  A graph that failed validation writes no ids (pc.gerr).
 template <int NT, int U, int WT, bool P16>
 __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t g, uint8_t *smem,
                                                  uint8_t *slot, PCtl<NT> &pc, int64_t *s_sum, int64_t *s_tot, uint32_t *s_scan)
@@ -762,8 +762,9 @@ __device__ __forceinline__ void solve_contracted(const PersistArgs &A, uint32_t 
     const int2 *E = reinterpret_cast<const int2 *>(A.edges) + e0;
     const uint32_t *W = A.w + e0;
     const size_t S = A.lds_bytes;
-    // light edges: n ln(4 m / n) / 2 (kernels_contract.hip); below a few
-    // thousand edges, or with few edges per vertex, every edge at once
+    // light edges: n ln(4 m / n) / 2, which balances the edges of the two
+    // phases (here an edge costs much the same in both); below a few thousand
+    // edges, or with few edges per vertex, every edge at once
     const uint32_t light = (uint32_t)(0.5f * n * __logf(4.0f * (float)m / (float)(n ? n : 1u)));
     const bool two = !A.round_hooks && m >= PERSIST_TWO_PHASE_M && m >= 2 * n && light * 5ull <= m * 3ull;
     // the slot: list 16 m, flags m (16 at a time), hook records 8 n, maps 8 n

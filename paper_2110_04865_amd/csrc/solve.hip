@@ -177,9 +177,13 @@ static bool contract_eligible(const Ctx *c, int32_t n, int64_t m)
 // edges a fraction of about 2 exp(-2 f) of the rest still joins different
 // trees (Erdos-Renyi), so n ln(4 m / n) / 2 balances the edges of the two
 // phases; a fifth fewer is best, since an edge costs more in phase 0, where
-// its ends are the graph's vertices (factor 0.3 / 0.4 / 0.5 / 0.6: R-MAT s22
-// 2.16 / 2.23 / 2.27 / 2.29 ms, grid 256^3 5.13 / 3.68 / 3.82 / 4.27 ms: a
-// grid's light edges stop forming one large tree below about 0.9 n).
+// its ends are the graph's vertices (a solve by factor 0.3 / 0.4 / 0.5, us:
+// R-MAT s19 432 / 462 / 492, s21 1167 / 1177 / 1212; grid 101^3 1125 / 454 /
+// 476, 200^3 2742 / 1848 / 1867; random edges, vertices and edges 2^20, 2^21
+// 717 / 552 / 887; 2^20, 2^24 1065 / 1074 / 1238; 2^22, 2^25 2631 / 2746 /
+// 2944; 2^23, 2^24 3582 / 3254 / 4967; an image of 3000^2 with 256 weights 2556
+// / 2305 / 1923: a graph of few edges a vertex has no large tree among its
+// light edges below about 0.9 n).
 static int64_t contract_light(int32_t n, int64_t m)
 {
     const double f = 0.4 * std::log(std::max(1.0, 4.0 * (double)m / (double)n));
@@ -283,9 +287,14 @@ static msf_status contract_start(Ctx *c)
     const int64_t tiles = (S.m + CT_TILE - 1) / CT_TILE;
     const int64_t light = contract_light(S.n, S.m);
     S.two_phase = S.m > CT_ONE_PHASE && light * 2 <= S.m;
-    // the passes over the input want two workgroups of 16 waves on each
-    // compute unit, those over the list one, up to 2^23 edges (4096 / 8192
-    // waves: R-MAT s22 2.15 / 2.21 ms, grid 256^3 3.81 / 3.67 ms)
+    // one workgroup of 16 waves on each compute unit up to 2^23 edges, two
+    // above, for the passes over the input and over the list alike.  A solve
+    // by 4096 / 8192 waves, us, over the input: grid 140^3 (7.8M edges) 809 /
+    // 839, R-MAT s20 (16M) 775 / 740, 2^24 random edges on 2^20 vertices 1108 /
+    // 1081 and on 2^22 2153 / 2159, grid 200^3 (22.8M) 1935 / 1854.  Over the
+    // list, up to 7M edges on it: R-MAT s21 1182 / 1202, grid 200^3 1849 / 1862,
+    // 2^22 vertices and 2^24 edges 2160 / 2196, 2^23 and 2^24 3252 / 3279; grid
+    // 256^3 (16.4M on it) 3810 / 3670.
     const int64_t list = S.two_phase ? light : S.m;
     const int64_t waves = S.m > ((int64_t)1 << 23) ? CT_MAX_WAVES : CT_MAX_WAVES / 2;
     S.ct_W = (uint32_t)std::min<int64_t>(waves, (tiles + 15) / 16 * 16);
