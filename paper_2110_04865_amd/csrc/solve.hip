@@ -287,19 +287,16 @@ static msf_status contract_start(Ctx *c)
     const int64_t tiles = (S.m + CT_TILE - 1) / CT_TILE;
     const int64_t light = contract_light(S.n, S.m);
     S.two_phase = S.m > CT_ONE_PHASE && light * 2 <= S.m;
-    // one workgroup of 16 waves on each compute unit up to 2^23 edges, two
-    // above, for the passes over the input and over the list alike.  A solve
-    // by 4096 / 8192 waves, us, over the input: grid 140^3 (7.8M edges) 809 /
-    // 839, R-MAT s20 (16M) 775 / 740, 2^24 random edges on 2^20 vertices 1108 /
-    // 1081 and on 2^22 2153 / 2159, grid 200^3 (22.8M) 1935 / 1854.  Over the
-    // list, up to 7M edges on it: R-MAT s21 1182 / 1202, grid 200^3 1849 / 1862,
-    // 2^22 vertices and 2^24 edges 2160 / 2196, 2^23 and 2^24 3252 / 3279; grid
-    // 256^3 (16.4M on it) 3810 / 3670.
-    const int64_t list = S.two_phase ? light : S.m;
+    // the passes over the input want two workgroups of 16 waves on each
+    // compute unit from 2^23 edges on (a solve by 4096 / 8192 waves, us: grid
+    // 140^3, 7.8M edges, 809 / 839; R-MAT s20, 16M, 775 / 740; 2^24 random edges
+    // on 2^20 vertices 1108 / 1081, on 2^22 2153 / 2159; grid 200^3, 22.8M, 1935 /
+    // 1854), those over the list one (R-MAT s21 1182 / 1202; grid 200^3 1849 /
+    // 1862; 2^22 vertices and 2^24 edges 2160 / 2196, 2^23 and 2^24 3252 / 3279,
+    // 2^24 and 2^25 6494 / 6512; grid 256^3 3397 / 3397)
     const int64_t waves = S.m > ((int64_t)1 << 23) ? CT_MAX_WAVES : CT_MAX_WAVES / 2;
     S.ct_W = (uint32_t)std::min<int64_t>(waves, (tiles + 15) / 16 * 16);
-    S.ct_pass = list > ((int64_t)1 << 23) ? S.ct_W
-                                          : std::min<uint32_t>(S.ct_W, CT_MAX_WAVES / 2);
+    S.ct_pass = std::min<uint32_t>(S.ct_W, CT_MAX_WAVES / 2);
     S.ct_words = ((size_t)S.m + 3) / 4;
     CtArgs A;
     MSF_TRY(contract_args(c, &A));
